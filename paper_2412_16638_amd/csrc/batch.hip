@@ -328,7 +328,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
       // ---- C1: p_new = z + beta p_old ; q = M p_new ; (p, q) ----
       const S* pold = (its & 1) ? (const S*)P.p1 : (const S*)P.p0;
       S* pnew = (its & 1) ? (S*)P.p0 : (S*)P.p1;
-      InAxpy<C, S, 1> f{z, pold, (C)beta, its > 0};
+      const InAxpy<C, S, 1> f{z, its > 0 ? pold : z, its > 0 ? (C)beta : C(0)};
       double acc3[BND] = {0.0, 0.0, 0.0, 0.0};
       for (int it0 = 0; it0 < nit; it0 += RU) {
         int row[RU];
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
         rows_of<RU>(r0, r1, nit, it0, row, val);
         C pc[RU][1], w[RU][1];
 #pragma unroll
-        for (int k = 0; k < RU; ++k) stencil_group<C, 1>(P.geo, M, row[k], f, pc[k], w[k]);
+        for (int k = 0; k < RU; ++k) stencil_group<C, 1, 0, S>(P.geo, M, row[k], f, pc[k], w[k]);
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
           if (val[k]) {
@@ -791,7 +791,7 @@ static void batch_problems(mprk_batch* b, std::vector<BProb>& hp, std::vector<in
     const mprk_problem& q = b->probs[p];
     BProb& P = hp[p];
     const int N = b->N[p];
-    P.geo = Geo{q.grid.nx, q.grid.ny, q.grid.nz, q.grid.bc, N, q.grid.nx * q.grid.ny};
+    P.geo = make_geo(q.grid.nx, q.grid.ny, q.grid.nz, q.grid.bc);
     P.K = operator_coef(q.grid, q.op);
     P.sigma = q.dt * a;
     P.dt = q.dt;

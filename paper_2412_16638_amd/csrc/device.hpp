@@ -2,8 +2,10 @@
 //
 // Layout and launch conventions used by every grid kernel:
 //   * vectors are lexicographic, x fastest (index i + nx j + nx ny k);
-//   * a thread owns "groups" of VEC consecutive x-values (VEC = 4 when nx % 4 == 0,
-//     else 1), so a group never straddles an x-row;
+//   * a thread owns "groups" of VEC consecutive values (16 bytes of the LP type, 32 of FP64).
+//     Where VEC divides nx a group lies in one x-row (FL = 0); else groups are flat (FL = 1):
+//     VEC consecutive unknowns whatever rows they belong to, the grid's last group possibly
+//     partial, neighbour rows read at element alignment (see stencil_group);
 //   * a block owns a contiguous range of nit*TPB groups; the block index is remapped so
 //     that the 8 XCDs (each with its own L2) each own one contiguous eighth of the grid
 //     (hardware dispatch sends block b to XCD b % 8), which keeps stencil halo planes of
@@ -31,15 +33,41 @@ constexpr int MAXRED = MAXD + 2;     // max values of one grid reduction (dots +
 constexpr int MAXS = 8;              // max RK stages
 constexpr int BJ_MAX = 8;            // max block-Jacobi block size
 
+// Exact quotient by a fixed divisor d >= 1 of any 0 <= n < 2^31: n m >> s with m = 1, s = log2 d
+// for a power of two, else s = 32 + floor(log2 d) and m = floor(2^s / d) + 1 (m < 2^32, and
+// m d - 2^s <= d, so the error n (m d - 2^s) / (d 2^s) < n / 2^s stays below 1 / d).  A
+// multiply and a shift in place of the ~25 instructions of an integer division by a kernel
+// argument.
+struct FastDiv {
+  unsigned m;
+  int s;
+  __host__ __device__ __forceinline__ int div(int n) const {
+    return (int)(((unsigned long long)(unsigned)n * m) >> s);
+  }
+};
+
+inline FastDiv make_fastdiv(int d) {
+  int l = 0;
+  while ((2LL << l) <= d) ++l;  // floor(log2 d)
+  if ((1LL << l) == d) return FastDiv{1u, l};
+  return FastDiv{(unsigned)((1ULL << (32 + l)) / (unsigned)d + 1), 32 + l};
+}
+
 struct Geo {
   int nx, ny, nz, bc;  // bc: 0 zero Dirichlet, 1 periodic
   int N, plane;        // nx*ny*nz, nx*ny
+  FastDiv dx, dy;      // division by nx and ny
 };
 
+inline Geo make_geo(int nx, int ny, int nz, int bc) {
+  return Geo{nx, ny, nz, bc, nx * ny * nz, nx * ny, make_fastdiv(nx), make_fastdiv(ny)};
+}
+
 struct Launch {
-  int ng;   // number of groups (N / VEC, or rows for CSR kernels)
+  int ng;   // number of groups (N / VEC rounded up, or rows for CSR kernels)
   int nit;  // groups per thread
   int G;    // blocks (a multiple of 8)
+  int n;    // unknowns N (flat groups: the last one may hold fewer than VEC)
 };
 
 // 7-point stencil coefficients: w = c v + xm v[x-1] + xp v[x+1] + ym v[y-1] + ...
@@ -201,6 +229,81 @@ __device__ __forceinline__ C rnd(C x) {
   return (C)(S)x;
 }
 
+// The same with the rounding pinned for FP16 storage under FP32 arithmetic, where the compiler
+// is otherwise free to fold the conversion into the FMA before it: gfx950's mixed FMA rounds
+// a b + c to FP16 once, the separate instructions twice, and the two differ in about 5e-5 of
+// random values -- enough to move a stage's result by its FP16 rounding noise when a kernel's
+// code around it changes.  rnd2: two roundings; rnd_fma: a b + c rounded once.
+template <typename S, typename C>
+__device__ __forceinline__ C rnd2(C x) {
+  if constexpr (sizeof(S) == 2 && sizeof(C) == 4) asm("" : "+v"(x));
+  return (C)(S)x;
+}
+
+// x as an FP32 value the compiler does not trace back to FP16: two products of such values
+// would otherwise be added by a two-term dot instruction, which rounds differently.
+template <typename S, typename C>
+__device__ __forceinline__ C as_fp32(C x) {
+  if constexpr (sizeof(S) == 2 && sizeof(C) == 4) asm("" : "+v"(x));
+  return x;
+}
+
+template <typename S, typename C>
+__device__ __forceinline__ C rnd_fma(C a, C b, C c) {
+  if constexpr (sizeof(S) == 2 && sizeof(C) == 4) {
+    unsigned d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return (C)__builtin_bit_cast(half_t, (unsigned short)d);
+  } else {
+    c += a * b;
+    return (C)(S)c;
+  }
+}
+
+// VEC values of p at element e of a vector of n values, e + VEC <= n, at the element type's own
+// alignment (16-byte loads all the same: gfx950 takes them at any alignment).
+template <typename C, typename S, int V>
+__device__ __forceinline__ void loadu(const S* __restrict__ p, C (&o)[V]) {
+  struct __attribute__((packed)) U {
+    S v[V];
+  };
+  const U t = *reinterpret_cast<const U*>(p);
+#pragma unroll
+  for (int i = 0; i < V; ++i) o[i] = (C)t.v[i];
+}
+
+// Group at e of a vector of n values: FL = 0 aligned and whole; FL = 1 at element alignment,
+// the part past n read as zero and not written.
+template <typename C, typename S, int V, int FL>
+__device__ __forceinline__ void loadg(const S* __restrict__ p, int e, int n, C (&o)[V]) {
+  if constexpr (FL == 0) {
+    loadv<C, S, V>(p + e, o);
+  } else if (e + V <= n) {
+    loadu<C, S, V>(p + e, o);
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i) o[i] = e + i < n ? (C)p[e + i] : C(0);
+  }
+}
+
+template <typename S, typename C, int V, int FL>
+__device__ __forceinline__ void storeg(S* __restrict__ p, int e, int n, const C (&o)[V]) {
+  if constexpr (FL == 0) {
+    storev<S, C, V>(p + e, o);
+  } else if (e + V <= n) {
+    struct __attribute__((packed)) U {
+      S v[V];
+    } t;
+#pragma unroll
+    for (int i = 0; i < V; ++i) t.v[i] = (S)o[i];
+    *reinterpret_cast<U*>(p + e) = t;
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (e + i < n) p[e + i] = (S)o[i];
+  }
+}
+
 __device__ __forceinline__ int xcd_block(int G) {
   const int b = blockIdx.x;
   return (b & 7) * (G >> 3) + (b >> 3);
@@ -277,7 +380,7 @@ __device__ __forceinline__ double load_dev(const double* p) {
 // Grid reduction of nd (<= ND <= 64) per-thread values in fixed order: wave64 shuffle tree,
 // block sum over the waves, one partial per block; the last block of each group of RGRP blocks
 // sums the group's partials (one wave, lane = block within the group); the last group to finish
-// sums the group sums.  Returns true in that final block, where tot[0..nd) (shared memory)
+// sums the group sums (a grid of one group, at most RGRP blocks, is done after the first level).  Returns true in that final block, where tot[0..nd) (shared memory)
 // holds the totals.  The order of every addition depends only on G and the block indices, so
 // results are bitwise reproducible for a given launch shape.
 template <int ND>
@@ -319,16 +422,21 @@ __device__ bool reduce_to_last(const double (&v)[ND], int nd, const Red& red, in
     for (int d = 0; d < ND; ++d) {
       if (d < nd) {
         const double s = wave_sum(x[d]);
-        if (lane == d) store_dev(red.p2 + (size_t)d * red.s2 + grp, s);
+        if (ngrp == 1) {  // one group: its sums are the totals
+          if (lane == d) tot[d] = s;
+        } else if (lane == d) {
+          store_dev(red.p2 + (size_t)d * red.s2 + grp, s);
+        }
       }
     }
     if (lane == 0) {
       __hip_atomic_store(red.tick + TSTRIDE * (1 + grp), 0u, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
-      stage = publish_ticket(red.tick) == (unsigned)(ngrp - 1) ? 2 : 0;
+      stage = ngrp == 1 ? 3 : publish_ticket(red.tick) == (unsigned)(ngrp - 1) ? 2 : 0;
     }
   }
   __syncthreads();
+  if (stage == 3) return true;
   if (stage != 2) return false;
   // final block: every thread sums a strided slice of each value's group sums, then a fixed
   // shuffle tree and a fixed-order combine of the waves
@@ -360,10 +468,10 @@ struct Nbr {
 
 template <int VEC>
 __device__ __forceinline__ Nbr neighbours(const Geo& g, int e) {
-  const int x0 = e % g.nx;
-  const int t = e / g.nx;
-  const int y = t % g.ny;
-  const int z = t / g.ny;
+  const int t = g.dx.div(e);
+  const int x0 = e - t * g.nx;
+  const int z = g.dy.div(t);
+  const int y = t - z * g.ny;
   const bool per = g.bc == 1;
   Nbr n;
   n.xm = x0 > 0 ? e - 1 : (per ? e + g.nx - 1 : -1);
@@ -384,9 +492,129 @@ __device__ __forceinline__ Nbr neighbours(const Geo& g, int e) {
 struct NoPre {
   __device__ __forceinline__ void operator()() const {}
 };
-template <typename C, int VEC, typename F, typename P = NoPre>
+// SR: storage type the result is rounded through with its last product (void: not rounded).
+// The FMAs are written out so that every place a value is formed in adds them alike.
+// XF: the sum starts from the left neighbour (as the FP64 operator does), else from the centre.
+template <typename C, typename SR, int XF = std::is_same<SR, void>::value>
+__device__ __forceinline__ C stencil_sum(const Coef<C>& k, C c, C xm, C xp, C ym, C yp, C zm, C zp) {
+  auto fma = [](C a, C b, C d) {
+    if constexpr (sizeof(C) == 4) return __builtin_fmaf(a, b, d);
+    else return __builtin_fma(a, b, d);
+  };
+  C acc = XF ? fma(k.c, c, k.xm * xm) : fma(k.xm, xm, k.c * c);
+  acc = fma(k.xp, xp, acc);
+  acc = fma(k.ym, ym, acc);
+  acc = fma(k.yp, yp, acc);
+  acc = fma(k.zm, zm, acc);
+  if constexpr (std::is_same<SR, void>::value) acc = fma(k.zp, zp, acc);
+  else acc = rnd_fma<SR, C>(k.zp, zp, acc);
+  return acc;
+}
+
+// Flat groups (FL = 1, any nx): the VEC unknowns from e on may end one x-row and begin the next.
+// Such a group is still read as five vectors (its y and z neighbours lie at the same distance
+// for both parts) plus the values left and right of it; where the row ends inside it, the two
+// x neighbours across the end are replaced by the wrapped values (periodic) or zero.  A group
+// whose parts differ in which neighbours exist (the first and last rows of a plane), the
+// grid's partial last group and grids with nx < VEC go value by value: about 3 / ny of the
+// groups that straddle.  f reads at element alignment here.
+template <typename C, int VEC, typename SR, typename F, typename P>
+__device__ __forceinline__ void stencil_group_flat(const Geo& g, const Coef<C>& k, int e, const F& f,
+                                                   C (&ctr)[VEC], C (&out)[VEC], const P& pre) {
+  const int t = g.dx.div(e);
+  const int x0 = e - t * g.nx;
+  const int z = g.dy.div(t);
+  const int y = t - z * g.ny;
+  const bool per = g.bc == 1;
+  const int m = g.nx - x0;  // values of the group's first row from e on
+  const bool str = m < VEC;
+  if (g.nx >= VEC && e + VEC <= g.N && (!str || (y >= 1 && y + 2 < g.ny))) {
+    const int il = x0 > 0 ? e - 1 : (per ? e + g.nx - 1 : -1);
+    const int ir = m != VEC ? e + VEC : (per ? e + VEC - g.nx : -1);
+    const int iym = y > 0 ? e - g.nx : (per ? e + (g.ny - 1) * g.nx : -1);
+    const int iyp = y < g.ny - 1 ? e + g.nx : (per ? e - (g.ny - 1) * g.nx : -1);
+    const int izm = z > 0 ? e - g.plane : (per ? e + (g.nz - 1) * g.plane : -1);
+    const int izp = z < g.nz - 1 ? e + g.plane : (per ? e - (g.nz - 1) * g.plane : -1);
+    C l = f.one(il >= 0 ? il : e);
+    C r = f.one(ir >= 0 ? ir : e);
+    C wl = C(0), wr = C(0);  // across the row end inside the group
+    if (per) {
+      wl = f.one(str ? e + m + g.nx - 1 : e);
+      wr = f.one(str ? e + m - g.nx : e);
+    }
+    C ym[VEC], yp[VEC], zm[VEC], zp[VEC];
+    f.uvec(e, ctr);
+    f.uvec(iym >= 0 ? iym : e, ym);
+    f.uvec(iyp >= 0 ? iyp : e, yp);
+    f.uvec(izm >= 0 ? izm : e, zm);
+    f.uvec(izp >= 0 ? izp : e, zp);
+    if constexpr (!std::is_same<P, NoPre>::value) {
+      pre();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (il < 0) l = C(0);
+    if (ir < 0) r = C(0);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      if (iym < 0) ym[v] = C(0);
+      if (iyp < 0) yp[v] = C(0);
+      if (izm < 0) zm[v] = C(0);
+      if (izp < 0) zp[v] = C(0);
+    }
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      C left = v > 0 ? ctr[v - 1] : l;
+      C right = v < VEC - 1 ? ctr[v + 1] : r;
+      if (v > 0 && v == m) left = wl;
+      if (v < VEC - 1 && v == m - 1) right = wr;
+      out[v] = stencil_sum<C, SR>(k, ctr[v], left, right, ym[v], yp[v], zm[v], zp[v]);
+    }
+  } else {
+    // four values at a time, their 28 loads in flight together (an index past the grid reads the
+    // last unknown and is dropped)
+    constexpr int W = VEC < 4 ? VEC : 4;
+#pragma unroll
+    for (int v0 = 0; v0 < VEC; v0 += W) {
+      C a[W][7];
+      Nbr n[W];
+#pragma unroll
+      for (int v = 0; v < W; ++v) {
+        const int i = min(e + v0 + v, g.N - 1);
+        n[v] = neighbours<1>(g, i);
+        a[v][0] = f.one(i);
+        a[v][1] = f.one(n[v].xm >= 0 ? n[v].xm : i);
+        a[v][2] = f.one(n[v].xp >= 0 ? n[v].xp : i);
+        a[v][3] = f.one(n[v].ym >= 0 ? n[v].ym : i);
+        a[v][4] = f.one(n[v].yp >= 0 ? n[v].yp : i);
+        a[v][5] = f.one(n[v].zm >= 0 ? n[v].zm : i);
+        a[v][6] = f.one(n[v].zp >= 0 ? n[v].zp : i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < W; ++v) {
+        if (n[v].xm < 0) a[v][1] = C(0);
+        if (n[v].xp < 0) a[v][2] = C(0);
+        if (n[v].ym < 0) a[v][3] = C(0);
+        if (n[v].yp < 0) a[v][4] = C(0);
+        if (n[v].zm < 0) a[v][5] = C(0);
+        if (n[v].zp < 0) a[v][6] = C(0);
+        const bool in = e + v0 + v < g.N;
+        const C o = stencil_sum<C, SR>(k, a[v][0], a[v][1], a[v][2], a[v][3], a[v][4], a[v][5], a[v][6]);
+        ctr[v0 + v] = in ? a[v][0] : C(0);
+        out[v0 + v] = in ? o : C(0);
+      }
+    }
+  }
+}
+
+template <typename C, int VEC, int FL = 0, typename SR = void, typename F, typename P = NoPre>
 __device__ __forceinline__ void stencil_group(const Geo& g, const Coef<C>& k, int e, const F& f,
                                               C (&ctr)[VEC], C (&out)[VEC], const P& pre = P()) {
+  // (SR: flat groups and pinned inputs; the caller rounds the rest)
+  if constexpr (FL == 1) {
+    stencil_group_flat<C, VEC, SR>(g, k, e, f, ctr, out, pre);
+    return;
+  }
   const Nbr n = neighbours<VEC>(g, e);
   // every load is issued unconditionally (a missing Dirichlet neighbour reads the group itself)
   // and masked afterwards, so the seven loads are in flight together
@@ -415,6 +643,12 @@ __device__ __forceinline__ void stencil_group(const Geo& g, const Coef<C>& k, in
   for (int v = 0; v < VEC; ++v) {
     const C left = v > 0 ? ctr[v - 1] : l;
     const C right = v < VEC - 1 ? ctr[v + 1] : r;
+    if constexpr (F::pin > 0) {
+      out[v] = (v == 0) == (F::pin == 2)
+                   ? stencil_sum<C, SR, 1>(k, ctr[v], left, right, ym[v], yp[v], zm[v], zp[v])
+                   : stencil_sum<C, SR, 0>(k, ctr[v], left, right, ym[v], yp[v], zm[v], zp[v]);
+      continue;
+    }
     C acc = k.c * ctr[v];
     acc += k.xm * left;
     acc += k.xp * right;
@@ -427,44 +661,61 @@ __device__ __forceinline__ void stencil_group(const Geo& g, const Coef<C>& k, in
 }
 
 // Input functor: plain array in storage type S, converted to C.
+// pin: the order the stencil's first two products are added in is fixed instead of the compiler's
+// choice, so that it does not move with the code around: 1 = the group's first value starts from
+// its centre and the others from their left neighbour, 2 = the other way round; the sum is then
+// rounded through SR with its last product.
 template <typename C, typename S, int VEC>
 struct In1 {
+  static constexpr int pin = sizeof(S) == 8 ? 2 : 0;
   const S* __restrict__ a;
   __device__ __forceinline__ void vec(int i, C (&o)[VEC]) const { loadv<C, S, VEC>(a + i, o); }
+  __device__ __forceinline__ void uvec(int i, C (&o)[VEC]) const { loadu<C, S, VEC>(a + i, o); }
   __device__ __forceinline__ C one(int i) const { return (C)a[i]; }
 };
 
 // Input functor: a + beta * b (CG search direction), with rounding through S so that every
-// reader sees exactly the values the owner stores.
+// reader sees exactly the values the owner stores.  Where there is no b yet, b = a with beta = 0:
+// a branch on that between the two loads of a value would make the compiler wait for the first
+// before it issues the second, fourteen memory round trips in a row per stencil group.
 template <typename C, typename S, int VEC>
 struct InAxpy {
+  static constexpr int pin = sizeof(S) == 2 && sizeof(C) == 4 ? 1 : 0;
   const S* __restrict__ a;
   const S* __restrict__ b;
   C beta;
-  int use_b;
   __device__ __forceinline__ void vec(int i, C (&o)[VEC]) const {
+    C t[VEC];
     loadv<C, S, VEC>(a + i, o);
-    if (use_b) {
-      C t[VEC];
-      loadv<C, S, VEC>(b + i, t);
+    loadv<C, S, VEC>(b + i, t);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) o[v] = rnd<S, C>(o[v] + beta * t[v]);
-    }
+    for (int v = 0; v < VEC; ++v) o[v] = rnd_fma<S, C>(beta, t[v], o[v]);
+  }
+  __device__ __forceinline__ void uvec(int i, C (&o)[VEC]) const {
+    C t[VEC];
+    loadu<C, S, VEC>(a + i, o);
+    loadu<C, S, VEC>(b + i, t);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) o[v] = rnd_fma<S, C>(beta, t[v], o[v]);
   }
   __device__ __forceinline__ C one(int i) const {
-    C o = (C)a[i];
-    if (use_b) o = rnd<S, C>(o + beta * (C)b[i]);
-    return o;
+    return rnd_fma<S, C>(beta, (C)b[i], (C)a[i]);
   }
 };
 
 // Input functor: s * a (a scaled stored vector)
 template <typename C, typename S, int VEC>
 struct InScaled {
+  static constexpr int pin = 0;
   const S* __restrict__ a;
   C s;
   __device__ __forceinline__ void vec(int i, C (&o)[VEC]) const {
     loadv<C, S, VEC>(a + i, o);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) o[v] *= s;
+  }
+  __device__ __forceinline__ void uvec(int i, C (&o)[VEC]) const {
+    loadu<C, S, VEC>(a + i, o);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) o[v] *= s;
   }
@@ -492,12 +743,20 @@ __host__ __device__ inline size_t bj_chunks(long nrows, int vec) {
 // of mode 3) are stored in one type chosen per chunk, tag[c] = 0 FP8 E4M3, 1 FP16, 2 FP32,
 // 3 FP64, from byte offset aoff[c] of the inverse area; within a chunk, row r = VEC g + q of the
 // lane group g is at entry (q * 64 + g % 64) * BS of the chunk's type.
+// Mode 5 (matrix-free operators, nx > BS): the diagonal block of BS consecutive rows of a
+// constant-coefficient stencil depends only on where an x-row ends inside it, so BS + 1 stored
+// inverses serve the whole grid: slot 0 for a block inside one x-row, slot k (1 <= k < BS) for a
+// block whose first k rows end an x-row, slot BS for the short last block.  The slot follows
+// from the row number alone.  Mode 6 is the case BS | nx (slot 0 everywhere).
 struct BJDesc {
   const void* inv;
   const int* idx;
   int mode;
   const int* tag;
   const long long* aoff;
+  int nx, N;   // mode 5
+  FastDiv dx;  // division by nx
+  int lay;     // mode 4: rows per lane of the layout (VEC, or 1 under flat groups)
 };
 
 template <typename S>
@@ -507,11 +766,39 @@ struct BJ {
   int mode;
   const int* __restrict__ tag;
   const long long* __restrict__ aoff;
+  int nx, N;
+  FastDiv dx;
+  int lay;
 };
 
 template <typename S>
 __host__ __device__ inline BJ<S> bj_typed(const BJDesc& d) {
-  return BJ<S>{(const S*)d.inv, d.idx, d.mode, d.tag, d.aoff};
+  return BJ<S>{(const S*)d.inv, d.idx, d.mode, d.tag, d.aoff, d.nx, d.N, d.dx, d.lay};
+}
+
+// Slot of the block that starts at row b0 (modes 5 and 6).
+template <int BS>
+__host__ __device__ __forceinline__ int bj_slot_of(int mode, int b0, int nx, int N, const FastDiv& dx) {
+  if (mode == 6) return 0;
+  const int k = nx - (b0 - dx.div(b0) * nx);  // rows left in the x-row
+  if (b0 + BS > N) return BS;
+  return k < BS ? k : 0;
+}
+
+// Where mode 4 keeps the rows of the lane that owns rows e .. e + VEC - 1: their chunk, the first
+// row's entry in it and the entries between rows.  A layout of single rows (lay = 1) holds a
+// chunk's 64 rows in order, and VEC consecutive rows that start at a multiple of VEC share one.
+struct BJPlace {
+  int ch;
+  size_t ent, step;
+};
+template <typename S, int VEC, int BS>
+__device__ __forceinline__ BJPlace bj_place(const BJ<S>& dinv, int e) {
+  if (dinv.lay == VEC) {
+    const int g = e / VEC;
+    return BJPlace{g >> 6, (size_t)(g & 63) * BS, (size_t)64 * BS};
+  }
+  return BJPlace{e >> 6, (size_t)(e & 63) * BS, (size_t)BS};
 }
 
 // One row of an adaptive-precision inverse, converted to the compute type (tag 0 FP8 E4M3,
@@ -575,18 +862,22 @@ __device__ __forceinline__ void bj_offsets(const BJ<S>& dinv, int e, bool valid,
 
 // Row q (0 <= q < NR, lane row i0 + q) of the lane's block-Jacobi product, from its stored
 // inverse row `row` and the lane's inputs r (BS <= VEC) or the block's gathered inputs rb.
-template <typename C, typename S, int VEC, int BS>
+// RND: 0 as computed; the result rounded through S with its last product (1: rnd_fma) or after
+// it (2: rnd2).
+template <typename C, typename S, int VEC, int BS, int RND = 0>
 __device__ __forceinline__ C bj_row_dot(const Vec<S, BS>& row, int q, const C (&r)[VEC],
                                         const C* rb) {
   C acc = C(0);
-  if constexpr (BS > VEC) {
+  const C* x = r + q / BS * BS;  // the block within the lane
+  if constexpr (BS > VEC) x = rb;
+  if constexpr (RND == 1) {
 #pragma unroll
-    for (int k = 0; k < BS; ++k) acc += (C)row.v[k] * rb[k];
-  } else {
-    const int sb = q / BS;  // block within the lane
-#pragma unroll
-    for (int k = 0; k < BS; ++k) acc += (C)row.v[k] * r[sb * BS + k];
+    for (int k = 0; k < BS - 1; ++k) acc += (C)row.v[k] * x[k];
+    return rnd_fma<S, C>((C)row.v[BS - 1], x[BS - 1], acc);
   }
+#pragma unroll
+  for (int k = 0; k < BS; ++k) acc += (C)row.v[k] * x[k];
+  if constexpr (RND == 2) acc = rnd2<S, C>(acc);
   return acc;
 }
 
@@ -620,13 +911,14 @@ __host__ __device__ constexpr int bj_type_tag() {
 // Rows of a chunk stored in a narrower type than S (W 32-bit words per row), kept as raw bits
 // in the first W words of each row of S.
 template <typename S, int VEC, int BS, int W>
-__device__ __forceinline__ void bj_load_narrow(const char* base, int g, BJRows<S, VEC, BS>& R) {
+__device__ __forceinline__ void bj_load_narrow(const char* base, const BJPlace& pl,
+                                               BJRows<S, VEC, BS>& R) {
   if constexpr (W > 0 && W * 4 <= (int)sizeof(S) * BS && (W * 4) % BS == 0) {
     constexpr int NW = (int)sizeof(S) * BS / 4;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       const Vec<unsigned, W> u =
-          *reinterpret_cast<const Vec<unsigned, W>*>(base + ((size_t)i * 64 + (g & 63)) * (W * 4));
+          *reinterpret_cast<const Vec<unsigned, W>*>(base + (pl.ent + i * pl.step) / BS * (W * 4));
       Vec<unsigned, NW> full{};
 #pragma unroll
       for (int k = 0; k < W; ++k) full.v[k] = u.v[k];
@@ -674,32 +966,81 @@ __device__ __forceinline__ void bj_decode_narrow(const Vec<S, BS>& row, int tag,
   }
 }
 
-// AD = 1: the adaptive-precision layout (mode 4) is possible; kernels are instantiated apart for
-// it, so that its conversions cost the other layouts no registers.
+// z = D^{-1} r from the table of modes 5 and 6 when a lane holds whole blocks (BS <= VEC).  The
+// inverse of the blocks inside an x-row is the same for every lane, so its entries are read
+// through the scalar cache into scalar registers and cost the vector memory path nothing; only
+// lanes whose block an x-row ends in read their own rows.  RND: as bj_row_dot.
+template <typename C, typename S, int VEC, int BS, int RND>
+__device__ __forceinline__ void bj_table_mul(const BJ<S>& dinv, int e, bool valid, const C (&r)[VEC],
+                                             C (&z)[VEC]) {
+  static_assert(BS <= VEC, "a lane holds whole blocks");
+  typedef const __attribute__((address_space(4))) unsigned* cptr;  // never written by a kernel
+  constexpr int NW = (BS * BS * (int)sizeof(S) + 3) / 4;
+  Vec<unsigned, NW> raw;
+  cptr t = (cptr)(unsigned long long)dinv.inv;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    raw.v[i] = t[i];
+    // keeps the conversion of a 16-bit entry next to its product, where it folds into a
+    // mixed-precision FMA reading the scalar register (hoisted out of the caller's loop, the
+    // converted entries would take 64 vector registers)
+    if constexpr (sizeof(S) == 2) asm volatile("" : "+s"(raw.v[i]));
+  }
+  Vec<S, BS> T[BS];
+  __builtin_memcpy(T, &raw, sizeof(T));
+#pragma unroll
+  for (int q = 0; q < VEC; ++q) z[q] = bj_row_dot<C, S, VEC, BS, RND>(T[q % BS], q, r, nullptr);
+  if (dinv.mode == 5 && BS > 1) {
+#pragma unroll
+    for (int b = 0; b < VEC / BS; ++b) {
+      const int slot = valid ? bj_slot_of<BS>(5, e + b * BS, dinv.nx, dinv.N, dinv.dx) : 0;
+      if (slot > 0) {
+        const S* rows = dinv.inv + (size_t)slot * BS * BS;
+#pragma unroll
+        for (int q = 0; q < BS; ++q)
+          z[b * BS + q] = bj_row_dot<C, S, VEC, BS, RND>(
+              *reinterpret_cast<const Vec<S, BS>*>(rows + q * BS), b * BS + q, r, nullptr);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < VEC; ++q) z[q] = valid ? z[q] : C(0);
+}
+
+// AD = 1: the adaptive-precision layout (mode 4) is possible; AD = 2: the table of modes 5 and
+// 6.  Kernels are instantiated apart for them, so that their code costs the other layouts no
+// registers.
 template <typename S, int VEC, int BS, int AD = 0>
 __device__ __forceinline__ void bj_load(const BJ<S>& dinv, int e, bool valid, BJRows<S, VEC, BS>& R) {
   R.late = false;
-  if (AD && dinv.mode == 4) {
+  if constexpr (AD == 2) {
+    if constexpr (BS > VEC) {  // a block spans lanes: each reads its rows of the block's slot
+      const int slot = valid ? bj_slot_of<BS>(dinv.mode, e & ~(BS - 1), dinv.nx, dinv.N, dinv.dx) : 0;
+      const S* rows = dinv.inv + ((size_t)slot * BS + (e & (BS - 1))) * BS;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) R.row[i] = *reinterpret_cast<const Vec<S, BS>*>(rows + i * BS);
+    }
+    return;
+  }
+  if (AD == 1 && dinv.mode == 4) {
     // adaptive precision: a chunk stored in the storage type or a narrower one is loaded here
     // (a narrower row's bits fill the first bytes of a row of S); a wider one where the rows are
     // applied
     constexpr int TS = bj_type_tag<S>();
-    const int g = valid ? e / VEC : 0;
-    const int ch = g >> 6;
-    const int tag = dinv.tag[ch];
+    const BJPlace pl = bj_place<S, VEC, BS>(dinv, valid ? e : 0);
+    const int tag = dinv.tag[pl.ch];
     R.tag = tag;
-    const char* base = (const char*)dinv.inv + dinv.aoff[ch];
+    const char* base = (const char*)dinv.inv + dinv.aoff[pl.ch];
     if (tag == TS) {
 #pragma unroll
       for (int i = 0; i < VEC; ++i)
-        R.row[i] = *reinterpret_cast<const Vec<S, BS>*>((const S*)base +
-                                                         ((size_t)i * 64 + (g & 63)) * BS);
+        R.row[i] = *reinterpret_cast<const Vec<S, BS>*>((const S*)base + pl.ent + i * pl.step);
     } else if (tag == 0 && TS > 0 && BS % 4 == 0) {
-      bj_load_narrow<S, VEC, BS, BS / 4>(base, g, R);
+      bj_load_narrow<S, VEC, BS, BS / 4>(base, pl, R);
     } else if (tag == 1 && TS > 1 && BS % 2 == 0) {
-      bj_load_narrow<S, VEC, BS, BS / 2>(base, g, R);
+      bj_load_narrow<S, VEC, BS, BS / 2>(base, pl, R);
     } else if (tag == 2 && TS > 2) {
-      bj_load_narrow<S, VEC, BS, BS>(base, g, R);
+      bj_load_narrow<S, VEC, BS, BS>(base, pl, R);
     } else {
       R.late = true;
     }
@@ -713,18 +1054,23 @@ __device__ __forceinline__ void bj_load(const BJ<S>& dinv, int e, bool valid, BJ
 
 // z = D^{-1} r with rows loaded by bj_load, or (mode 4) loaded here (every lane of the wave
 // must call this).
-template <typename C, typename S, int VEC, int BS>
+// (RND as bj_row_dot)
+template <typename C, typename S, int VEC, int BS, int RND = 0>
 __device__ __forceinline__ void bj_mul(const BJRows<S, VEC, BS>& R, bool valid, const C (&r)[VEC],
                                        C (&z)[VEC]);
-template <typename C, typename S, int VEC, int BS, int AD = 0>
+template <typename C, typename S, int VEC, int BS, int AD = 0, int RND = 0>
 __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool valid,
                                               const C (&r)[VEC], C (&z)[VEC]);
-template <typename C, typename S, int VEC, int BS, int AD = 0>
+template <typename C, typename S, int VEC, int BS, int AD = 0, int RND = 0>
 __device__ __forceinline__ void bj_mul(const BJ<S>& dinv, int e, const BJRows<S, VEC, BS>& R,
                                        bool valid, const C (&r)[VEC], C (&z)[VEC]) {
-  if (AD && dinv.mode == 4 && R.late) {
+  if constexpr (AD == 2 && BS <= VEC) {
+    bj_table_mul<C, S, VEC, BS, RND>(dinv, e, valid, r, z);
+    return;
+  }
+  if (AD == 1 && dinv.mode == 4 && R.late) {
     bj_apply_lane<C, S, VEC, BS, AD>(dinv, e, valid, r, z);
-  } else if (AD && dinv.mode == 4 && R.tag != bj_type_tag<S>()) {
+  } else if (AD == 1 && dinv.mode == 4 && R.tag != bj_type_tag<S>()) {
     C rb[BS > VEC ? BS : 1];
     bj_gather<C, VEC, BS>(r, rb);
 #pragma unroll
@@ -743,18 +1089,18 @@ __device__ __forceinline__ void bj_mul(const BJ<S>& dinv, int e, const BJRows<S,
       z[q] = valid ? acc : C(0);
     }
   } else {
-    bj_mul<C, S, VEC, BS>(R, valid, r, z);
+    bj_mul<C, S, VEC, BS, RND>(R, valid, r, z);
   }
 }
 
-template <typename C, typename S, int VEC, int BS>
+template <typename C, typename S, int VEC, int BS, int RND>
 __device__ __forceinline__ void bj_mul(const BJRows<S, VEC, BS>& R, bool valid, const C (&r)[VEC],
                                        C (&z)[VEC]) {
   C rb[BS > VEC ? BS : 1];
   bj_gather<C, VEC, BS>(r, rb);
 #pragma unroll
   for (int q = 0; q < VEC; ++q) {
-    const C acc = bj_row_dot<C, S, VEC, BS>(R.row[q], q, r, rb);
+    const C acc = bj_row_dot<C, S, VEC, BS, RND>(R.row[q], q, r, rb);
     z[q] = valid ? acc : C(0);
   }
 }
@@ -763,20 +1109,24 @@ __device__ __forceinline__ void bj_mul(const BJRows<S, VEC, BS>& R, bool valid, 
 // rows; when BS > VEC a block spans BS/VEC consecutive lanes whose values are exchanged by
 // shuffles (every lane of the wave must call this).  Inverse rows are loaded without branches,
 // RCH rows in flight at a time.  Mode 4 reads each row in its chunk's type.
-template <typename C, typename S, int VEC, int BS, int AD>
+template <typename C, typename S, int VEC, int BS, int AD, int RND>
 __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool valid,
                                               const C (&r)[VEC], C (&z)[VEC]) {
+  if constexpr (AD == 2 && BS <= VEC) {
+    bj_table_mul<C, S, VEC, BS, RND>(dinv, e, valid, r, z);
+    return;
+  }
   C rb[BS > VEC ? BS : 1];
   bj_gather<C, VEC, BS>(r, rb);
-  if (AD && dinv.mode == 4) {
-    const int g = valid ? e / VEC : 0;  // an invalid lane reads chunk 0 and discards the result
-    const int ch = g >> 6;
-    const int tag = dinv.tag[ch];
-    const void* base = (const char*)dinv.inv + dinv.aoff[ch];
+  if (AD == 1 && dinv.mode == 4) {
+    // an invalid lane reads chunk 0 and discards the result
+    const BJPlace pl = bj_place<S, VEC, BS>(dinv, valid ? e : 0);
+    const int tag = dinv.tag[pl.ch];
+    const void* base = (const char*)dinv.inv + dinv.aoff[pl.ch];
 #pragma unroll
     for (int q = 0; q < VEC; ++q) {
       C w[BS];
-      bj_row_adaptive<C, BS>(base, tag, ((size_t)q * 64 + (g & 63)) * BS, w);
+      bj_row_adaptive<C, BS>(base, tag, pl.ent + q * pl.step, w);
       C acc = C(0);
       if constexpr (BS > VEC) {
 #pragma unroll
@@ -791,7 +1141,13 @@ __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool val
     return;
   }
   size_t off[VEC];
-  bj_offsets<S, VEC, BS>(dinv, e, valid, off);
+  if constexpr (AD == 2) {
+    const int slot = valid ? bj_slot_of<BS>(dinv.mode, e & ~(BS - 1), dinv.nx, dinv.N, dinv.dx) : 0;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) off[i] = ((size_t)slot * BS + (e & (BS - 1)) + i) * BS;
+  } else {
+    bj_offsets<S, VEC, BS>(dinv, e, valid, off);
+  }
   constexpr int RCH = VEC < 4 ? VEC : 4;
 #pragma unroll
   for (int i0 = 0; i0 < VEC; i0 += RCH) {
@@ -800,7 +1156,7 @@ __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool val
     for (int i = 0; i < RCH; ++i) row[i] = *reinterpret_cast<const Vec<S, BS>*>(dinv.inv + off[i0 + i]);
 #pragma unroll
     for (int i = 0; i < RCH; ++i) {
-      const C acc = bj_row_dot<C, S, VEC, BS>(row[i], i0 + i, r, rb);
+      const C acc = bj_row_dot<C, S, VEC, BS, RND>(row[i], i0 + i, r, rb);
       z[i0 + i] = valid ? acc : C(0);
     }
   }

@@ -64,7 +64,8 @@ struct EngineCtx {
   hipStream_t stream;
   Geo geo;
   int fmt;            // 0 stencil, 1 CSR
-  int vec;            // values per group of the LP kernels: 8 (FP16, nx % 8 == 0), 4 or 1
+  int vec;            // values per group of the LP kernels: 8 or 4
+  int flat;           // groups are flat (vec does not divide nx)
   Launch ln_vec;      // groups of `vec` elements (streaming kernels)
   Launch ln_row;      // CSR rows (VEC = 1)
   Launch ln_mv;       // launch of the SpMV kernels (= ln_vec for stencil, ln_row for CSR)
@@ -177,14 +178,17 @@ inline Coef<C> cast_coef(const Coef<double>& a) {
 
 template <typename S, typename C>
 class EngineT final : public Engine {
-  // 16-byte groups for 2-byte storage; wider types never use an 8-wide group
-  static constexpr int V8 = sizeof(S) == 2 ? 8 : 4;
-  // the block-Jacobi kernels' instantiation for the adaptive-precision layout (mode 4)
+  // the block-Jacobi kernels' instantiation for the adaptive-precision layout (mode 4) and the
+  // table of a constant-coefficient operator's distinct blocks (modes 5, 6)
   template <int BS, typename F>
   static void with_ad(const BJDesc& d, F&& f) {
     if constexpr (BS > 0) {
       if (d.mode == 4) {
         f(IC<1>{});
+        return;
+      }
+      if (d.mode == 5 || d.mode == 6) {
+        f(IC<2>{});
         return;
       }
     }
@@ -216,52 +220,56 @@ class EngineT final : public Engine {
   }
 
   // ---------------- CG ----------------
-  template <int VEC, int BS>
+  template <int VEC, int BS, int FL>
   void cg_begin_t(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv) {
     S* z = BS > 0 ? (S*)c.z : (S*)c.r;
     with_ad<BS>(dinv, [&](auto ad) {
       constexpr int AD = decltype(ad)::value;
-      MPRK_LAUNCH_KC(c, KC_CG_BEGIN, (k_cg_begin<S, C, VEC, BS, AD>), c.ln_red, c.ln_red, c.res, (S*)c.r, z,
+      MPRK_LAUNCH_KC(c, KC_CG_BEGIN, (k_cg_begin<S, C, VEC, BS, AD, FL>), c.ln_red, c.ln_red, c.res, (S*)c.r, z,
                     bj_typed<S>(dinv), cfg, c.ctl, c.red);
     });
   }
   hipError_t cg_begin(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv) override {
     if (c.fdm_on) {
-      dispatch_vec(c, [&](auto vec) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         constexpr int VEC = decltype(vec)::value;
-        MPRK_LAUNCH_KC(c, KC_CG_BEGIN, (k_cg_begin_ext<S, C, VEC>), c.ln_red, c.ln_red, c.res, (S*)c.r,
+        constexpr int FL = decltype(fl)::value;
+        MPRK_LAUNCH_KC(c, KC_CG_BEGIN, (k_cg_begin_ext<S, C, VEC, FL>), c.ln_red, c.ln_red, c.res, (S*)c.r,
                        cfg, c.ctl, c.red);
       });
       fdm_apply(c, cfg.sigma, c.r, c.z);
       cg_rz_t<1>(c);
       return hipGetLastError();
     }
-    dispatch_vec_bs(c, [&](auto vec, auto bs) { cg_begin_t<decltype(vec)::value, decltype(bs)::value>(c, cfg, dinv); });
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+      cg_begin_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, cfg, dinv);
+    });
     return hipGetLastError();
   }
   template <int BEGIN>
   void cg_rz_t(const EngineCtx& c) {
-    dispatch_vec(c, [&](auto vec) {
+    dispatch_vec(c, [&](auto vec, auto fl) {
       constexpr int VEC = decltype(vec)::value;
-      MPRK_LAUNCH_KC(c, KC_CG_RZ, (k_cg_rz<S, C, VEC, BEGIN>), c.ln_red, c.ln_red, (const S*)c.r,
+      constexpr int FL = decltype(fl)::value;
+      MPRK_LAUNCH_KC(c, KC_CG_RZ, (k_cg_rz<S, C, VEC, BEGIN, FL>), c.ln_red, c.ln_red, (const S*)c.r,
                      (const S*)c.z, c.ctl, c.red);
     });
   }
 
-  template <int VEC, int FMT>
+  template <int VEC, int FMT, int FL>
   void cg_dir_t(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc, const S* z,
                 const S* pold, S* pnew) {
     const Coef<C> M = cast_coef<C>(Mc);
     const C msig = (C)(cfg.sigma * c.kscale);
-    MPRK_LAUNCH_KC(c, KC_CG_DIR, (k_cg_dir<S, C, VEC, FMT>), c.ln_mv_red, c.ln_mv_red, c.geo, M, c.csr,
+    MPRK_LAUNCH_KC(c, KC_CG_DIR, (k_cg_dir<S, C, VEC, FMT, FL>), c.ln_mv_red, c.ln_mv_red, c.geo, M, c.csr,
                 (const S*)c.mval, msig, z, pold, pnew, (S*)c.q, c.ctl, c.red);
   }
-  template <int VEC, int BS>
+  template <int VEC, int BS, int FL>
   void cg_upd_t(const EngineCtx& c, const SolveCfg& cfg, const S* p, const BJDesc& dinv) {
     S* z = BS > 0 ? (S*)c.z : (S*)c.r;
     with_ad<BS>(dinv, [&](auto ad) {
       constexpr int AD = decltype(ad)::value;
-      MPRK_LAUNCH_KC(c, KC_CG_UPD, (k_cg_upd<S, C, VEC, BS, AD>), c.ln_red, c.ln_red, (S*)c.x, p, (S*)c.r,
+      MPRK_LAUNCH_KC(c, KC_CG_UPD, (k_cg_upd<S, C, VEC, BS, AD, FL>), c.ln_red, c.ln_red, (S*)c.x, p, (S*)c.r,
                     (const S*)c.q, z, bj_typed<S>(dinv), cfg, c.ctl, c.red);
     });
   }
@@ -276,20 +284,24 @@ class EngineT final : public Engine {
     const S* z = (c.bs > 0 || c.fdm_on) ? (const S*)c.z : (const S*)c.r;
     const S* pold = (it & 1) ? (const S*)c.p1 : (const S*)c.p0;
     S* pnew = (it & 1) ? (S*)c.p0 : (S*)c.p1;
-    if (c.fmt == 1) cg_dir_t<1, 1>(c, cfg, Mc, z, pold, pnew);
-    else if (c.vec == 8) cg_dir_t<V8, 0>(c, cfg, Mc, z, pold, pnew);
-    else if (c.vec == 4) cg_dir_t<4, 0>(c, cfg, Mc, z, pold, pnew);
-    else cg_dir_t<1, 0>(c, cfg, Mc, z, pold, pnew);
+    if (c.fmt == 1) {
+      cg_dir_t<1, 1, 0>(c, cfg, Mc, z, pold, pnew);
+    } else {
+      dispatch_vec(c, [&](auto vec, auto fl) {
+        cg_dir_t<decltype(vec)::value, 0, decltype(fl)::value>(c, cfg, Mc, z, pold, pnew);
+      });
+    }
     if (c.fdm_on) {
-      dispatch_vec(c, [&](auto vec) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         constexpr int VEC = decltype(vec)::value;
-        MPRK_LAUNCH_KC(c, KC_CG_UPD, (k_cg_upd_ext<S, C, VEC>), c.ln_red, c.ln_red, (S*)c.x,
+        constexpr int FL = decltype(fl)::value;
+        MPRK_LAUNCH_KC(c, KC_CG_UPD, (k_cg_upd_ext<S, C, VEC, FL>), c.ln_red, c.ln_red, (S*)c.x,
                        (const S*)pnew, (S*)c.r, (const S*)c.q, cfg, c.ctl, c.red);
       });
       return hipGetLastError();
     }
-    dispatch_vec_bs(c, [&](auto vec, auto bs) {
-      cg_upd_t<decltype(vec)::value, decltype(bs)::value>(c, cfg, pnew, dinv);
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+      cg_upd_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, cfg, pnew, dinv);
     });
     return hipGetLastError();
   }
@@ -445,42 +457,42 @@ class EngineT final : public Engine {
     return hipGetLastError();
   }
   hipError_t cg_finish(const EngineCtx& c) override {
-    if (c.vec == 8)
-      MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_promote<S, C, V8>), c.ln_vec, c.ln_vec, c.y, (const S*)c.x, c.ctl);
-    else if (c.vec == 4)
-      MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_promote<S, C, 4>), c.ln_vec, c.ln_vec, c.y, (const S*)c.x, c.ctl);
-    else
-      MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_promote<S, C, 1>), c.ln_vec, c.ln_vec, c.y, (const S*)c.x, c.ctl);
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_promote<S, C, decltype(vec)::value, decltype(fl)::value>), c.ln_vec,
+                     c.ln_vec, c.y, (const S*)c.x, c.ctl);
+    });
     return hipGetLastError();
   }
 
   // ---------------- GMRES ----------------
-  template <int VEC, int BS>
+  template <int VEC, int BS, int FL>
   void gm_begin_t(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv) {
     with_ad<BS>(dinv, [&](auto ad) {
       constexpr int AD = decltype(ad)::value;
-      MPRK_LAUNCH_KC(c, KC_GM_BEGIN, (k_gm_begin<S, C, VEC, BS, AD>), c.ln_red, c.ln_red, c.res, (S*)c.V,
+      MPRK_LAUNCH_KC(c, KC_GM_BEGIN, (k_gm_begin<S, C, VEC, BS, AD, FL>), c.ln_red, c.ln_red, c.res, (S*)c.V,
                        (S*)(c.Zb ? c.Zb : c.z), bj_typed<S>(dinv), cfg, c.ctl, c.red);
     });
   }
   hipError_t gm_begin(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv) override {
-    dispatch_vec_bs(c, [&](auto vec, auto bs) { gm_begin_t<decltype(vec)::value, decltype(bs)::value>(c, cfg, dinv); });
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+      gm_begin_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, cfg, dinv);
+    });
     if (c.fdm_on) fdm_chain<S, S>(c, cfg.sigma, (const S*)c.V, (S*)c.z, 1);  // z = P^-1 v_0
     return hipGetLastError();
   }
-  template <int VEC, int FMT, int PREC, int NDM>
+  template <int VEC, int FMT, int PREC, int NDM, int FL>
   void gm_matvec_t(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc) {
     const Coef<C> M = cast_coef<C>(Mc);
     const C msig = (C)(cfg.sigma * c.kscale);
-    MPRK_LAUNCH_KC(c, KC_GM_MATVEC, (k_gm_matvec<S, C, VEC, FMT, PREC, NDM>), c.ln_mv_red, c.ln_mv_red, c.geo, M, c.csr,
+    MPRK_LAUNCH_KC(c, KC_GM_MATVEC, (k_gm_matvec<S, C, VEC, FMT, PREC, NDM, FL>), c.ln_mv_red, c.ln_mv_red, c.geo, M, c.csr,
                 (const S*)c.mval, msig, (const S*)(c.Zb ? c.Zb : c.z), c.Zb ? c.vstride : (size_t)0,
                 (S*)c.V, c.vstride, cfg, c.ctl, c.red);
   }
-  template <int VEC, int BS, int NDM>
+  template <int VEC, int BS, int NDM, int FL>
   void gm_orth_t(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv) {
     with_ad<BS>(dinv, [&](auto ad) {
       constexpr int AD = decltype(ad)::value;
-      MPRK_LAUNCH_KC(c, KC_GM_ORTH, (k_gm_orth<S, C, VEC, BS, NDM, AD>), c.ln_red, c.ln_red, (S*)c.V, c.vstride,
+      MPRK_LAUNCH_KC(c, KC_GM_ORTH, (k_gm_orth<S, C, VEC, BS, NDM, AD, FL>), c.ln_red, c.ln_red, (S*)c.V, c.vstride,
                        (S*)(c.Zb ? c.Zb : c.z), c.Zb ? c.vstride : (size_t)0, bj_typed<S>(dinv), cfg,
                        c.ctl, c.red);
     });
@@ -506,18 +518,14 @@ class EngineT final : public Engine {
   }
   template <int NDM>
   void gm_zstep_n(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc, const BJDesc& dinv,
-                  int k) {
-    dispatch_vec_bs(c, [&](auto vec, auto bs) {
-      constexpr int V = decltype(vec)::value;
-      if constexpr (V > 1) gm_zstep_t<V, decltype(bs)::value, NDM>(c, cfg, Mc, dinv, k);
-    });
-  }
+                  int k);
   void gm_ziter(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc, const BJDesc& dinv,
                 int k) {
     if (k == 0) {
-      dispatch_vec(c, [&](auto vec) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         constexpr int V = decltype(vec)::value;
-        if constexpr (V > 1) gm_zfirst_t<V>(c, cfg, Mc);
+        constexpr int FL = decltype(fl)::value;
+        if constexpr (!FL) gm_zfirst_t<V>(c, cfg, Mc);
       });
     } else if (k < 4) {
       gm_zstep_n<4>(c, cfg, Mc, dinv, k);
@@ -530,49 +538,9 @@ class EngineT final : public Engine {
     }
   }
   template <int NDM>
-  void gm_zclose_n(const EngineCtx& c, const SolveCfg& cfg, int nsteps) {
-    dispatch_vec(c, [&](auto vec) {
-      constexpr int V = decltype(vec)::value;
-      MPRK_LAUNCH_KC(c, KC_GM_CLOSE, (k_gm_zclose<S, C, V, NDM>), c.ln_red, c.ln_red, (const S*)c.V,
-                     c.vstride, (const S*)c.zw[(nsteps - 1) & 1], cfg, c.ctl, c.red);
-    });
-  }
+  void gm_zclose_n(const EngineCtx& c, const SolveCfg& cfg, int nsteps);
   template <int NDM>
-  void gm_iter_t(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc, const BJDesc& dinv) {
-    const bool prec = c.bs > 0 || c.fdm_on;  // the product reads z = P^-1 v_j
-    if (c.gform == 1) {
-      const Coef<C> M = cast_coef<C>(Mc);
-      dispatch_vec(c, [&](auto vec) {
-        constexpr int V = decltype(vec)::value;
-        if constexpr (V > 1) {
-          if (prec)
-            MPRK_LAUNCH_KC_LDS(c, KC_GM_MATVEC, (k_gm_zmatvec<S, C, V, 1, NDM>), c.zl.G, c.zlds, c.zl,
-                               c.geo, M, (const S*)c.z, (S*)c.V, c.vstride, cfg, c.ctl, c.red);
-          else
-            MPRK_LAUNCH_KC_LDS(c, KC_GM_MATVEC, (k_gm_zmatvec<S, C, V, 0, NDM>), c.zl.G, c.zlds, c.zl,
-                               c.geo, M, (const S*)c.z, (S*)c.V, c.vstride, cfg, c.ctl, c.red);
-        }
-      });
-    } else if (c.fmt == 1) {
-      if (prec) gm_matvec_t<1, 1, 1, NDM>(c, cfg, Mc); else gm_matvec_t<1, 1, 0, NDM>(c, cfg, Mc);
-    } else if (c.vec == 8) {
-      if (prec) gm_matvec_t<V8, 0, 1, NDM>(c, cfg, Mc); else gm_matvec_t<V8, 0, 0, NDM>(c, cfg, Mc);
-    } else if (c.vec == 4) {
-      if (prec) gm_matvec_t<4, 0, 1, NDM>(c, cfg, Mc); else gm_matvec_t<4, 0, 0, NDM>(c, cfg, Mc);
-    } else {
-      if (prec) gm_matvec_t<1, 0, 1, NDM>(c, cfg, Mc); else gm_matvec_t<1, 0, 0, NDM>(c, cfg, Mc);
-    }
-    if (c.reorth) {
-      dispatch_vec(c, [&](auto vec) {
-        constexpr int V = decltype(vec)::value;
-        MPRK_LAUNCH_KC(c, KC_GM_REORTH, (k_gm_reorth<S, C, V, NDM>), c.ln_red, c.ln_red, (S*)c.V,
-                       c.vstride, cfg, c.ctl, c.red);
-      });
-    }
-    dispatch_vec_bs(c, [&](auto vec, auto bs) {
-      gm_orth_t<decltype(vec)::value, decltype(bs)::value, NDM>(c, cfg, dinv);
-    });
-  }
+  void gm_iter_t(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc, const BJDesc& dinv);
   hipError_t gm_iter(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc,
                      const BJDesc& dinv, int k) override {
     // z = P^-1 v_k, issued at the start of the step that reads it (v_0's comes with the
@@ -591,44 +559,16 @@ class EngineT final : public Engine {
     else gm_iter_t<MAXD>(c, cfg, Mc, dinv);
     return hipGetLastError();
   }
-  template <int VEC, int BS, int NDM>
+  template <int VEC, int BS, int NDM, int FL>
   void gm_finish_t(const EngineCtx& c, const BJDesc& dinv) {
     with_ad<BS>(dinv, [&](auto ad) {
       constexpr int AD = decltype(ad)::value;
-      MPRK_LAUNCH_KC(c, KC_GM_FINISH, (k_gm_finish<S, C, VEC, BS, NDM, AD>), c.ln_vec, c.ln_vec, c.y, (const S*)c.V,
+      MPRK_LAUNCH_KC(c, KC_GM_FINISH, (k_gm_finish<S, C, VEC, BS, NDM, AD, FL>), c.ln_vec, c.ln_vec, c.y, (const S*)c.V,
                     c.vstride, bj_typed<S>(dinv), c.ctl);
     });
   }
   template <int NDM>
-  void gm_finish_n(const EngineCtx& c, const BJDesc& dinv) {
-    if (c.fdm_on) {
-      // t = sum_i y_i v_i -> t1; z = P^-1 t (also after the cycle's end) -> t1; y += scale z
-      C* t1 = (C*)c.fdm_t[1];
-      dispatch_vec(c, [&](auto vec) {
-        constexpr int V = decltype(vec)::value;
-        MPRK_LAUNCH_KC(c, KC_GM_FINISH, (k_gm_combine_ext<S, C, V, NDM>), c.ln_vec, c.ln_vec, t1,
-                       (const S*)c.V, c.vstride, c.ctl);
-      });
-      fdm_chain<C, C>(c, c.fdm_sigma, t1, t1, 0);
-      dispatch_vec(c, [&](auto vec) {
-        constexpr int V = decltype(vec)::value;
-        MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_gm_update_ext<C, V>), c.ln_vec, c.ln_vec, c.y, t1, c.ctl);
-      });
-      return;
-    }
-    if (c.Zb) {
-      // y += scale * sum_i ysol_i vscale_i BJ(V_i): the stored directions, no inverse read
-      dispatch_vec(c, [&](auto vec) {
-        constexpr int V = decltype(vec)::value;
-        MPRK_LAUNCH_KC(c, KC_GM_FINISH, (k_gm_finish<S, C, V, 0, NDM, 0>), c.ln_vec, c.ln_vec, c.y,
-                       (const S*)c.Zb, c.vstride, BJ<S>{}, c.ctl);
-      });
-      return;
-    }
-    dispatch_vec_bs(c, [&](auto vec, auto bs) {
-      gm_finish_t<decltype(vec)::value, decltype(bs)::value, NDM>(c, dinv);
-    });
-  }
+  void gm_finish_n(const EngineCtx& c, const BJDesc& dinv);
   hipError_t gm_finish(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv,
                        int nsteps) override {
     if (c.gform == 2 && nsteps > 0) {  // the cycle's last column
@@ -645,34 +585,39 @@ class EngineT final : public Engine {
   }
 
   // ---------------- verification ----------------
-  template <int VEC, int FMT>
+  template <int VEC, int FMT, int FL>
   void apply_m_t(const EngineCtx& c, const Coef<double>& Mc, double sigma, const void* x, void* y) {
     const Coef<C> M = cast_coef<C>(Mc);
     const C msig = (C)(sigma * c.kscale);
-    MPRK_LAUNCH_KC(c, KC_APPLY64, (k_apply_lp<S, C, VEC, FMT>), c.ln_mv, c.ln_mv, c.geo, M, c.csr,
+    MPRK_LAUNCH_KC(c, KC_APPLY64, (k_apply_lp<S, C, VEC, FMT, FL>), c.ln_mv, c.ln_mv, c.geo, M, c.csr,
                 (const S*)c.mval, msig, (const S*)x, (S*)y);
   }
   hipError_t apply_m(const EngineCtx& c, const Coef<double>& Mc, double sigma, const void* x,
                      void* y) override {
-    if (c.fmt == 1) apply_m_t<1, 1>(c, Mc, sigma, x, y);
-    else if (c.vec == 8) apply_m_t<V8, 0>(c, Mc, sigma, x, y);
-    else if (c.vec == 4) apply_m_t<4, 0>(c, Mc, sigma, x, y);
-    else apply_m_t<1, 0>(c, Mc, sigma, x, y);
+    if (c.fmt == 1) {
+      apply_m_t<1, 1, 0>(c, Mc, sigma, x, y);
+    } else {
+      dispatch_vec(c, [&](auto vec, auto fl) {
+        apply_m_t<decltype(vec)::value, 0, decltype(fl)::value>(c, Mc, sigma, x, y);
+      });
+    }
     return hipGetLastError();
   }
-  template <int VEC, int BS>
+  template <int VEC, int BS, int FL>
   void apply_bj_t(const EngineCtx& c, const BJDesc& dinv, const void* x, void* y) {
     if constexpr (BS > 0) {
       with_ad<BS>(dinv, [&](auto ad) {
         constexpr int AD = decltype(ad)::value;
-        MPRK_LAUNCH_KC(c, KC_APPLY64, (k_bj_apply<S, C, VEC, BS, AD>), c.ln_vec, c.ln_vec, (const S*)x,
+        MPRK_LAUNCH_KC(c, KC_APPLY64, (k_bj_apply<S, C, VEC, BS, AD, FL>), c.ln_vec, c.ln_vec, (const S*)x,
                        (S*)y, bj_typed<S>(dinv));
       });
     }
   }
   hipError_t apply_bj(const EngineCtx& c, const BJDesc& dinv, const void* x, void* y) override {
     if (c.bs == 0) return hipErrorInvalidValue;
-    dispatch_vec_bs(c, [&](auto vec, auto bs) { apply_bj_t<decltype(vec)::value, decltype(bs)::value>(c, dinv, x, y); });
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+      apply_bj_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, dinv, x, y);
+    });
     return hipGetLastError();
   }
 
@@ -681,40 +626,138 @@ class EngineT final : public Engine {
   struct IC {
     static constexpr int value = V;
   };
+  // the group widths in use: 16 bytes of FP16 (8) where 8 | nx, else 4 where 4 | nx, else flat
+  // groups of 8; 4 (flat or not) for the wider types
   template <typename F>
   static void dispatch_vec(const EngineCtx& c, F&& f) {
-    if (c.vec == 8) f(IC<V8>{});
-    else if (c.vec == 4) f(IC<4>{});
-    else f(IC<1>{});
+    if constexpr (sizeof(S) == 2) {
+      if (c.flat) f(IC<8>{}, IC<1>{});
+      else if (c.vec == 8) f(IC<8>{}, IC<0>{});
+      else f(IC<4>{}, IC<0>{});
+    } else {
+      if (c.flat) f(IC<4>{}, IC<1>{});
+      else f(IC<4>{}, IC<0>{});
+    }
   }
   template <typename F>
   static void dispatch_vec_bs(const EngineCtx& c, F&& f) {
-    if (c.vec == 8) {
+    dispatch_vec(c, [&](auto vec, auto fl) {
       switch (c.bs) {
-        case 0: f(IC<V8>{}, IC<0>{}); break;
-        case 1: f(IC<V8>{}, IC<1>{}); break;
-        case 2: f(IC<V8>{}, IC<2>{}); break;
-        case 4: f(IC<V8>{}, IC<4>{}); break;
-        default: f(IC<V8>{}, IC<8>{}); break;
+        case 0: f(vec, IC<0>{}, fl); break;
+        case 1: f(vec, IC<1>{}, fl); break;
+        case 2: f(vec, IC<2>{}, fl); break;
+        case 4: f(vec, IC<4>{}, fl); break;
+        default: f(vec, IC<8>{}, fl); break;
       }
-    } else if (c.vec == 4) {
-      switch (c.bs) {
-        case 0: f(IC<4>{}, IC<0>{}); break;
-        case 1: f(IC<4>{}, IC<1>{}); break;
-        case 2: f(IC<4>{}, IC<2>{}); break;
-        case 4: f(IC<4>{}, IC<4>{}); break;
-        default: f(IC<4>{}, IC<8>{}); break;
-      }
-    } else {
-      switch (c.bs) {
-        case 0: f(IC<1>{}, IC<0>{}); break;
-        case 1: f(IC<1>{}, IC<1>{}); break;
-        case 2: f(IC<1>{}, IC<2>{}); break;
-        case 4: f(IC<1>{}, IC<4>{}); break;
-        default: f(IC<1>{}, IC<8>{}); break;
-      }
-    }
+    });
   }
 };
+
+// The GMRES launchers of one basis-size bound, defined outside the class so that the larger
+// bounds can be instantiated in a translation unit of their own (MPRK_ARNOLDI_LARGE): the kernels
+// behind them are most of an engine's compile time.
+template <typename S, typename C>
+template <int NDM>
+void EngineT<S, C>::gm_zstep_n(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc, const BJDesc& dinv,
+                  int k) {
+  dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+    constexpr int V = decltype(vec)::value;
+    if constexpr (!decltype(fl)::value) gm_zstep_t<V, decltype(bs)::value, NDM>(c, cfg, Mc, dinv, k);
+  });
+}
+
+template <typename S, typename C>
+template <int NDM>
+void EngineT<S, C>::gm_zclose_n(const EngineCtx& c, const SolveCfg& cfg, int nsteps) {
+  dispatch_vec(c, [&](auto vec, auto fl) {
+    constexpr int V = decltype(vec)::value;
+    if constexpr (!decltype(fl)::value)
+      MPRK_LAUNCH_KC(c, KC_GM_CLOSE, (k_gm_zclose<S, C, V, NDM>), c.ln_red, c.ln_red, (const S*)c.V,
+                   c.vstride, (const S*)c.zw[(nsteps - 1) & 1], cfg, c.ctl, c.red);
+  });
+}
+
+template <typename S, typename C>
+template <int NDM>
+void EngineT<S, C>::gm_iter_t(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc,
+                              const BJDesc& dinv) {
+  const bool prec = c.bs > 0 || c.fdm_on;  // the product reads z = P^-1 v_j
+  if (c.gform == 1) {
+    const Coef<C> M = cast_coef<C>(Mc);
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      constexpr int V = decltype(vec)::value;
+      if constexpr (!decltype(fl)::value) {
+        if (prec)
+          MPRK_LAUNCH_KC_LDS(c, KC_GM_MATVEC, (k_gm_zmatvec<S, C, V, 1, NDM>), c.zl.G, c.zlds, c.zl,
+                             c.geo, M, (const S*)c.z, (S*)c.V, c.vstride, cfg, c.ctl, c.red);
+        else
+          MPRK_LAUNCH_KC_LDS(c, KC_GM_MATVEC, (k_gm_zmatvec<S, C, V, 0, NDM>), c.zl.G, c.zlds, c.zl,
+                             c.geo, M, (const S*)c.z, (S*)c.V, c.vstride, cfg, c.ctl, c.red);
+      }
+    });
+  } else if (c.fmt == 1) {
+    if (prec) gm_matvec_t<1, 1, 1, NDM, 0>(c, cfg, Mc); else gm_matvec_t<1, 1, 0, NDM, 0>(c, cfg, Mc);
+  } else {
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      constexpr int V = decltype(vec)::value;
+      constexpr int FL = decltype(fl)::value;
+      if (prec) gm_matvec_t<V, 0, 1, NDM, FL>(c, cfg, Mc); else gm_matvec_t<V, 0, 0, NDM, FL>(c, cfg, Mc);
+    });
+  }
+  if (c.reorth) {
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      MPRK_LAUNCH_KC(c, KC_GM_REORTH, (k_gm_reorth<S, C, decltype(vec)::value, NDM, decltype(fl)::value>),
+                     c.ln_red, c.ln_red, (S*)c.V, c.vstride, cfg, c.ctl, c.red);
+    });
+  }
+  dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+    gm_orth_t<decltype(vec)::value, decltype(bs)::value, NDM, decltype(fl)::value>(c, cfg, dinv);
+  });
+}
+
+template <typename S, typename C>
+template <int NDM>
+void EngineT<S, C>::gm_finish_n(const EngineCtx& c, const BJDesc& dinv) {
+  if (c.fdm_on) {
+    // t = sum_i y_i v_i -> t1; z = P^-1 t (also after the cycle's end) -> t1; y += scale z
+    C* t1 = (C*)c.fdm_t[1];
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      constexpr int V = decltype(vec)::value;
+      constexpr int FL = decltype(fl)::value;
+      MPRK_LAUNCH_KC(c, KC_GM_FINISH, (k_gm_combine_ext<S, C, V, NDM, FL>), c.ln_vec, c.ln_vec, t1,
+                     (const S*)c.V, c.vstride, c.ctl);
+    });
+    fdm_chain<C, C>(c, c.fdm_sigma, t1, t1, 0);
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      constexpr int V = decltype(vec)::value;
+      constexpr int FL = decltype(fl)::value;
+      MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_gm_update_ext<C, V, FL>), c.ln_vec, c.ln_vec, c.y, t1, c.ctl);
+    });
+    return;
+  }
+  if (c.Zb) {
+    // y += scale * sum_i ysol_i vscale_i BJ(V_i): the stored directions, no inverse read
+    dispatch_vec(c, [&](auto vec, auto fl) {
+      constexpr int V = decltype(vec)::value;
+      constexpr int FL = decltype(fl)::value;
+      MPRK_LAUNCH_KC(c, KC_GM_FINISH, (k_gm_finish<S, C, V, 0, NDM, 0, FL>), c.ln_vec, c.ln_vec, c.y,
+                     (const S*)c.Zb, c.vstride, BJ<S>{}, c.ctl);
+    });
+    return;
+  }
+  dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
+    gm_finish_t<decltype(vec)::value, decltype(bs)::value, NDM, decltype(fl)::value>(c, dinv);
+  });
+}
+
+#define MPRK_ARNOLDI_BOUND(decl, S, C, NDM)                                                          \
+  decl template void EngineT<S, C>::gm_iter_t<NDM>(const EngineCtx&, const SolveCfg&,                \
+                                                   const Coef<double>&, const BJDesc&);              \
+  decl template void EngineT<S, C>::gm_zstep_n<NDM>(const EngineCtx&, const SolveCfg&,               \
+                                                    const Coef<double>&, const BJDesc&, int);
+// Engine (S, C): its bounds above 8, instantiated elsewhere (decl = extern) or here (empty decl)
+#define MPRK_ARNOLDI_LARGE(decl, S, C) \
+  MPRK_ARNOLDI_BOUND(decl, S, C, 16)   \
+  MPRK_ARNOLDI_BOUND(decl, S, C, MAXD)
 
 }  // namespace mprk

@@ -636,7 +636,7 @@ inline void fdm_axis_dft(int n, bool central, double nu, double b, double* Qr, d
 
 // Start of a CG pass with an external preconditioner: r = LP(res / scale), (r, r); the tolerance and the
 // inner decision are set here, (r, z) by k_cg_rz after z = P^-1 r.
-template <typename S, typename C, int VEC>
+template <typename S, typename C, int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_cg_begin_ext(Launch ln, const double* __restrict__ res,
                                                       S* __restrict__ r, SolveCfg cfg, Ctl* ctl,
                                                       Red red) {
@@ -649,7 +649,7 @@ __global__ __launch_bounds__(TPB) void k_cg_begin_ext(Launch ln, const double* _
     const int g = (L * ln.nit + it) * TPB + threadIdx.x;
     if (g >= ln.ng) break;
     double t[VEC];
-    loadv<double, double, VEC>(res + g * VEC, t);
+    loadg<double, double, VEC, FL>(res, g * VEC, ln.n, t);
     C rv[VEC];
     C s = C(0);
 #pragma unroll
@@ -676,7 +676,7 @@ __global__ __launch_bounds__(TPB) void k_cg_begin_ext(Launch ln, const double* _
 }
 
 // x += alpha p (x = alpha p first), r -= alpha q, (r, r); convergence test on ||r||.
-template <typename S, typename C, int VEC>
+template <typename S, typename C, int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_cg_upd_ext(Launch ln, S* __restrict__ x,
                                                     const S* __restrict__ p, S* __restrict__ r,
                                                     const S* __restrict__ q, SolveCfg cfg, Ctl* ctl,
@@ -701,6 +701,7 @@ __global__ __launch_bounds__(TPB) void k_cg_upd_ext(Launch ln, S* __restrict__ x
     for (int v = 0; v < VEC; ++v) {
       xv[v] = first ? alpha * pv[v] : xv[v] + alpha * pv[v];
       rv[v] = rnd<S, C>(rv[v] - alpha * qv[v]);
+      if (FL && e + v >= ln.n) rv[v] = C(0);
       s += rv[v] * rv[v];
     }
     storev<S, C, VEC>(x + e, xv);
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(TPB) void k_cg_upd_ext(Launch ln, S* __restrict__ x
 }
 
 // (r, z) after z = P^-1 r.  BEGIN: the first product of a solve; else beta = (r,z)_new/(r,z)_old.
-template <typename S, typename C, int VEC, int BEGIN>
+template <typename S, typename C, int VEC, int BEGIN, int FL>
 __global__ __launch_bounds__(TPB) void k_cg_rz(Launch ln, const S* __restrict__ r,
                                                const S* __restrict__ z, Ctl* ctl, Red red) {
   if (ctl->outer_done | ctl->inner_done) return;
@@ -737,7 +738,8 @@ __global__ __launch_bounds__(TPB) void k_cg_rz(Launch ln, const S* __restrict__ 
     loadv<C, S, VEC>(z + g * VEC, zv);
     C s = C(0);
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) s += rv[v] * zv[v];
+    for (int v = 0; v < VEC; ++v)
+      if (!FL || g * VEC + v < ln.n) s += rv[v] * zv[v];
     acc[0] += (double)s;
   }
   __shared__ double tot[1];
@@ -762,7 +764,7 @@ __global__ __launch_bounds__(TPB) void k_cg_rz(Launch ln, const S* __restrict__ 
 
 // Least-squares solution of the cycle (back substitution of the rotated Hessenberg system)
 // and t = sum_i ys_i vscale_i v_i in the compute type; counts the pass.
-template <typename S, typename C, int VEC, int NDM>
+template <typename S, typename C, int VEC, int NDM, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_combine_ext(Launch ln, C* __restrict__ t,
                                                         const S* __restrict__ V, size_t vstride,
                                                         Ctl* ctl) {
@@ -812,12 +814,12 @@ __global__ __launch_bounds__(TPB) void k_gm_combine_ext(Launch ln, C* __restrict
         for (int v = 0; v < VEC; ++v) acc[v] += cf[i] * vv[v];
       }
     }
-    storev<C, C, VEC>(t + e, acc);
+    storeg<C, C, VEC, FL>(t, e, ln.n, acc);
   }
 }
 
 // y += scale z (z = P^-1 t in the compute type) when the cycle produced a correction.
-template <typename C, int VEC>
+template <typename C, int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_update_ext(Launch ln, double* __restrict__ y,
                                                        const C* __restrict__ z, Ctl* ctl) {
   if (ctl->outer_done || ctl->J == 0 || ctl->nonfinite) return;  // no correction, or J beyond the bound
@@ -829,11 +831,11 @@ __global__ __launch_bounds__(TPB) void k_gm_update_ext(Launch ln, double* __rest
     if (g >= ln.ng) break;
     double yv[VEC];
     C zv[VEC];
-    loadv<double, double, VEC>(y + g * VEC, yv);
-    loadv<C, C, VEC>(z + g * VEC, zv);
+    loadg<double, double, VEC, FL>(y, g * VEC, ln.n, yv);
+    loadg<C, C, VEC, FL>(z, g * VEC, ln.n, zv);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) yv[v] += sc * (double)zv[v];
-    storev<double, double, VEC>(y + g * VEC, yv);
+    storeg<double, double, VEC, FL>(y, g * VEC, ln.n, yv);
   }
 }
 

@@ -55,7 +55,7 @@ struct CombArgs {
 // clears the stage record, RESET_STEP also the step's gating flags, RESET_CALL the strict halt of
 // an earlier call.  A halted call opens every later stage finished, so its solve kernels return
 // at once.
-template <int VEC>
+template <int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_stage_rhs(Launch ln, const double* __restrict__ u,
                                                    CombArgs a, double* __restrict__ rhs,
                                                    double* __restrict__ y, Ctl* ctl, int reset) {
@@ -84,27 +84,27 @@ __global__ __launch_bounds__(TPB) void k_stage_rhs(Launch ln, const double* __re
     if (g >= ln.ng) break;
     const int e = g * VEC;
     double acc[VEC];
-    loadv<double, double, VEC>(u + e, acc);
+    loadg<double, double, VEC, FL>(u, e, ln.n, acc);
     for (int j = 0; j < a.nv; ++j) {
       double t[VEC];
-      loadv<double, double, VEC>(a.v[j] + e, t);
+      loadg<double, double, VEC, FL>(a.v[j], e, ln.n, t);
       const double c = a.c[j];
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
     }
-    storev<double, double, VEC>(rhs + e, acc);
+    storeg<double, double, VEC, FL>(rhs, e, ln.n, acc);
     if (a.pv) {
       double t[VEC];
-      loadv<double, double, VEC>(a.pv + e, t);
+      loadg<double, double, VEC, FL>(a.pv, e, ln.n, t);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] += a.pc * t[v];
       if (a.pv2) {
-        loadv<double, double, VEC>(a.pv2 + e, t);
+        loadg<double, double, VEC, FL>(a.pv2, e, ln.n, t);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += a.pc2 * t[v];
       }
     }
-    storev<double, double, VEC>(y + e, acc);
+    storeg<double, double, VEC, FL>(y, e, ln.n, acc);
   }
 }
 
@@ -177,13 +177,13 @@ __device__ __forceinline__ C csr_wave_row(const Csr& m, const SV* __restrict__ v
 
 // FMT 0: matrix-free stencil (VEC values per thread); FMT 1: CSR (one row per group, VEC = 1)
 // with the row product csum from csr_wave_row.
-template <int VEC, int FMT, typename P = NoPre>
+template <int VEC, int FMT, int FL, typename P = NoPre>
 __device__ __forceinline__ void k64_group(const Geo& geo, const Coef<double>& K,
                                           const double* __restrict__ y, int g, double csum,
                                           double (&yc)[VEC], double (&ky)[VEC], const P& pre = P()) {
   if constexpr (FMT == 0) {
     In1<double, double, VEC> f{y};
-    stencil_group<double, VEC>(geo, K, g * VEC, f, yc, ky, pre);
+    stencil_group<double, VEC, FL>(geo, K, g * VEC, f, yc, ky, pre);
   } else {
     static_assert(VEC == 1, "CSR kernels use one row per group");
     pre();
@@ -231,7 +231,7 @@ __device__ __forceinline__ void residual_decision(const double* tot, const Solve
 // FP64 explicit evaluation and stage residual: k = K y ; res = rhs - y + sigma k ; ||res||^2,
 // ||rhs||^2, non-finite count.
 // The last block decides whether the stage is finished (outer residual loop).
-template <int VEC, int FMT>
+template <int VEC, int FMT, int FL>
 __global__ __launch_bounds__(TPB) void k_residual(Launch ln, Geo geo, Coef<double> K, Csr csr,
                                                   const double* __restrict__ kval,
                                                   const double* __restrict__ y,
@@ -253,8 +253,8 @@ __global__ __launch_bounds__(TPB) void k_residual(Launch ln, Geo geo, Coef<doubl
     // end load row ng - 1 unused)
     const int e = FMT == 1 ? min(g, ln.ng - 1) : g * VEC;
     double yc[VEC], ky[VEC], b[VEC], rr[VEC], fv[VEC];
-    loadv<double, double, VEC>(rhs + e, b);
-    if (force) loadv<double, double, VEC>(force + e, fv);
+    loadg<double, double, VEC, FL>(rhs, e, ln.n, b);
+    if (force) loadg<double, double, VEC, FL>(force, e, ln.n, fv);
     double csum = 0.0;
     if constexpr (FMT == 1) {
       csum = csr_wave_row<double, double>(csr, kval, gw, ln.ng, In1<double, double, 1>{y});
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(TPB) void k_residual(Launch ln, Geo geo, Coef<doubl
     }
     // the stencil's seven loads are kept in flight together (an empty loader selects the
     // scheduling barrier; moving rhs into the group measured slower)
-    k64_group<VEC, FMT>(geo, K, y, g, csum, yc, ky, [] {});
+    k64_group<VEC, FMT, FL>(geo, K, y, g, csum, yc, ky, [] {});
     if (force) {  // constant forcing: f(y) = K y + g, so the stage solves y - sigma f(y) = rhs
 #pragma unroll
       for (int v = 0; v < VEC; ++v) ky[v] += fv[v];
@@ -278,8 +278,8 @@ __global__ __launch_bounds__(TPB) void k_residual(Launch ln, Geo geo, Coef<doubl
       acc[1] += b[v] * b[v];
       acc[2] += (__builtin_isfinite(rr[v]) && __builtin_isfinite(ky[v])) ? 0.0 : 1.0;
     }
-    storev<double, double, VEC>(kout + e, ky);
-    storev<double, double, VEC>(res + e, rr);
+    storeg<double, double, VEC, FL>(kout, e, ln.n, ky);
+    storeg<double, double, VEC, FL>(res, e, ln.n, rr);
   }
   __shared__ double tot[3];
   if (!reduce_to_last<3>(acc, 3, red, L, ln.G, tot)) return;
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(TPB) void k_residual_zm(ZLaunch zl, Geo geo, Coef<d
 
 // y = K x (mode 0) or y = x - sigma K x (mode 1), FP64, no reduction (verification access);
 // mode 0 adds the terms fx (an explicit stage's slope f(x) = K x + g + R(x)).
-template <int VEC, int FMT>
+template <int VEC, int FMT, int FL>
 __global__ __launch_bounds__(TPB) void k_apply64(Launch ln, Geo geo, Coef<double> K, Csr csr,
                                                  const double* __restrict__ kval,
                                                  const double* __restrict__ x,
@@ -366,10 +366,10 @@ __global__ __launch_bounds__(TPB) void k_apply64(Launch ln, Geo geo, Coef<double
     }
     if (g >= ln.ng) break;
     double xc[VEC], kx[VEC];
-    k64_group<VEC, FMT>(geo, K, x, g, csum, xc, kx);
+    k64_group<VEC, FMT, FL>(geo, K, x, g, csum, xc, kx);
     if (force) {  // mode 0 with forcing: y = K x + g (an explicit stage's slope)
       double fv[VEC];
-      loadv<double, double, VEC>(force + g * VEC, fv);
+      loadg<double, double, VEC, FL>(force, g * VEC, ln.n, fv);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) kx[v] += fv[v];
     }
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(TPB) void k_apply64(Launch ln, Geo geo, Coef<double
 #pragma unroll
       for (int v = 0; v < VEC; ++v) kx[v] = xc[v] - sigma * kx[v];
     }
-    storev<double, double, VEC>(y + g * VEC, kx);
+    storeg<double, double, VEC, FL>(y, g * VEC, ln.n, kx);
   }
 }
 
@@ -399,7 +399,7 @@ static __global__ void k_release_halt(Ctl* ctl) {
 }
 
 // k^eps = (y - rhs) / sigma : the low-precision slope of an implicit stage.
-template <int VEC>
+template <int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_keps(Launch ln, const double* __restrict__ y,
                                               const double* __restrict__ rhs, double inv_sigma,
                                               double* __restrict__ keps) {
@@ -408,16 +408,16 @@ __global__ __launch_bounds__(TPB) void k_keps(Launch ln, const double* __restric
     const int g = (L * ln.nit + it) * TPB + threadIdx.x;
     if (g >= ln.ng) break;
     double a[VEC], b[VEC];
-    loadv<double, double, VEC>(y + g * VEC, a);
-    loadv<double, double, VEC>(rhs + g * VEC, b);
+    loadg<double, double, VEC, FL>(y, g * VEC, ln.n, a);
+    loadg<double, double, VEC, FL>(rhs, g * VEC, ln.n, b);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) a[v] = (a[v] - b[v]) * inv_sigma;
-    storev<double, double, VEC>(keps + g * VEC, a);
+    storeg<double, double, VEC, FL>(keps, g * VEC, ln.n, a);
   }
 }
 
 // u += sum_j c_j v_j (step combination), skipped when the step hit a non-finite residual.
-template <int VEC>
+template <int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_combine(Launch ln, double* __restrict__ u, CombArgs a,
                                                  Ctl* ctl) {
   const int nonfin = ctl->step_nonfinite, held = ctl->step_held;
@@ -435,15 +435,15 @@ __global__ __launch_bounds__(TPB) void k_combine(Launch ln, double* __restrict__
     if (g >= ln.ng) break;
     const int e = g * VEC;
     double acc[VEC];
-    loadv<double, double, VEC>(u + e, acc);
+    loadg<double, double, VEC, FL>(u, e, ln.n, acc);
     for (int j = 0; j < a.nv; ++j) {
       double t[VEC];
-      loadv<double, double, VEC>(a.v[j] + e, t);
+      loadg<double, double, VEC, FL>(a.v[j], e, ln.n, t);
       const double c = a.c[j];
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
     }
-    storev<double, double, VEC>(u + e, acc);
+    storeg<double, double, VEC, FL>(u, e, ln.n, acc);
   }
 }
 
@@ -453,12 +453,12 @@ __global__ __launch_bounds__(TPB) void k_combine(Launch ln, double* __restrict__
 
 // w = M v for one group; for CSR M v = v - msig * (Kt v) with Kt the scaled LP values, the row
 // product csum = (Kt v)_g coming from csr_wave_row.
-template <typename S, typename C, int VEC, int FMT, typename F, typename P = NoPre>
+template <typename S, typename C, int VEC, int FMT, int FL, typename F, typename P = NoPre>
 __device__ __forceinline__ void mlp_group(const Geo& geo, const Coef<C>& M, C msig, int g, C csum,
                                           const F& f, C (&ctr)[VEC], C (&w)[VEC],
                                           const P& pre = P()) {
   if constexpr (FMT == 0) {
-    stencil_group<C, VEC>(geo, M, g * VEC, f, ctr, w, pre);
+    stencil_group<C, VEC, FL, S>(geo, M, g * VEC, f, ctr, w, pre);
   } else {
     static_assert(VEC == 1, "CSR kernels use one row per group");
     ctr[0] = f.one(g);
@@ -466,7 +466,7 @@ __device__ __forceinline__ void mlp_group(const Geo& geo, const Coef<C>& M, C ms
   }
 }
 
-template <typename S, typename C, int VEC, int FMT>
+template <typename S, typename C, int VEC, int FMT, int FL>
 __global__ __launch_bounds__(TPB) void k_apply_lp(Launch ln, Geo geo, Coef<C> M, Csr csr,
                                                   const S* __restrict__ mval, C msig,
                                                   const S* __restrict__ x, S* __restrict__ y) {
@@ -483,12 +483,12 @@ __global__ __launch_bounds__(TPB) void k_apply_lp(Launch ln, Geo geo, Coef<C> M,
     }
     if (g >= ln.ng) break;
     C ctr[VEC], w[VEC];
-    mlp_group<S, C, VEC, FMT>(geo, M, msig, g, csum, f, ctr, w);
-    storev<S, C, VEC>(y + g * VEC, w);
+    mlp_group<S, C, VEC, FMT, FL>(geo, M, msig, g, csum, f, ctr, w);
+    storeg<S, C, VEC, FL>(y, g * VEC, ln.n, w);
   }
 }
 
-template <typename S, typename C, int VEC, int BS, int AD = 0>
+template <typename S, typename C, int VEC, int BS, int AD, int FL>
 __global__ __launch_bounds__(TPB) void k_bj_apply(Launch ln, const S* __restrict__ r,
                                                   S* __restrict__ z, BJ<S> dinv) {
   const int L = xcd_block(ln.G);
@@ -496,13 +496,13 @@ __global__ __launch_bounds__(TPB) void k_bj_apply(Launch ln, const S* __restrict
     const int g = (L * ln.nit + it) * TPB + threadIdx.x;
     const bool valid = g < ln.ng;
     C rv[VEC], zv[VEC];
-    if (valid) loadv<C, S, VEC>(r + g * VEC, rv);
+    if (valid) loadg<C, S, VEC, FL>(r, g * VEC, ln.n, rv);
     else {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) rv[v] = C(0);
     }
     bj_apply_lane<C, S, VEC, BS, AD>(dinv, g * VEC, valid, rv, zv);
-    if (valid) storev<S, C, VEC>(z + g * VEC, zv);
+    if (valid) storeg<S, C, VEC, FL>(z, g * VEC, ln.n, zv);
   }
 }
 
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(TPB) void k_bj_apply(Launch ln, const S* __restrict
 // ------------------------------------------------------------------------------------------
 
 // Start of a CG pass: r = LP(res / scale), z = BJ(r), rz = (r, z), rr = (r, r)
-template <typename S, typename C, int VEC, int BS, int AD = 0>
+template <typename S, typename C, int VEC, int BS, int AD, int FL>
 __global__ __launch_bounds__(TPB) void k_cg_begin(Launch ln, const double* __restrict__ res,
                                                   S* __restrict__ r, S* __restrict__ z,
                                                   BJ<S> dinv, SolveCfg cfg,
@@ -526,16 +526,17 @@ __global__ __launch_bounds__(TPB) void k_cg_begin(Launch ln, const double* __res
     const bool valid = g < ln.ng;
     const int e = valid ? g * VEC : 0;  // an invalid lane reads group 0 and discards it
     double t[VEC];
-    loadv<double, double, VEC>(res + e, t);
+    loadg<double, double, VEC, FL>(res, e, ln.n, t);
     BJRows<S, VEC, bj_early<S, VEC, BS>() ? BS : 1> R;
     if constexpr (bj_early<S, VEC, BS>()) bj_load<S, VEC, BS, AD>(dinv, e, valid, R);
     C rv[VEC], zv[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) rv[v] = valid ? rnd<S, C>((C)(t[v] * inv)) : C(0);
+    constexpr int ZR = FL ? 1 : AD == 2 ? (BS >= 4 ? 2 : 1) : 0;
     C prz = C(0), prr = C(0);
     if constexpr (BS > 0) {
-      if constexpr (bj_early<S, VEC, BS>()) bj_mul<C, S, VEC, BS, AD>(dinv, e, R, valid, rv, zv);
-      else bj_apply_lane<C, S, VEC, BS, AD>(dinv, e, valid, rv, zv);
+      if constexpr (bj_early<S, VEC, BS>()) bj_mul<C, S, VEC, BS, AD, ZR>(dinv, e, R, valid, rv, zv);
+      else bj_apply_lane<C, S, VEC, BS, AD, ZR>(dinv, e, valid, rv, zv);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) zv[v] = rnd<S, C>(zv[v]);
     }
@@ -544,12 +545,19 @@ __global__ __launch_bounds__(TPB) void k_cg_begin(Launch ln, const double* __res
       if constexpr (BS > 0) storev<S, C, VEC>(z + e, zv);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
-        prr += rv[v] * rv[v];
-        if constexpr (BS > 0) prz += rv[v] * zv[v];
+        if constexpr (FL) {
+          acc[1] += (double)(rv[v] * rv[v]);
+          if constexpr (BS > 0) acc[0] += (double)(rv[v] * zv[v]);
+        } else {
+          prr += rv[v] * rv[v];
+          if constexpr (BS > 0) prz += rv[v] * zv[v];
+        }
       }
     }
-    acc[0] += (double)prz;
-    acc[1] += (double)prr;
+    if constexpr (!FL) {
+      acc[0] += (double)prz;
+      acc[1] += (double)prr;
+    }
   }
   __shared__ double tot[2];
   if (!reduce_to_last<2>(acc, 2, red, L, ln.G, tot)) return;
@@ -570,7 +578,7 @@ __global__ __launch_bounds__(TPB) void k_cg_begin(Launch ln, const double* __res
 
 // p_new = z + beta p_old (p_new = z in the first iteration), q = M p_new, pq = (p_new, q).
 // p is double-buffered because neighbours read p_old at the halo while p_new is written.
-template <typename S, typename C, int VEC, int FMT>
+template <typename S, typename C, int VEC, int FMT, int FL>
 __global__ __launch_bounds__(TPB) void k_cg_dir(Launch ln, Geo geo, Coef<C> M, Csr csr,
                                                 const S* __restrict__ mval, C msig,
                                                 const S* __restrict__ z,
@@ -579,7 +587,7 @@ __global__ __launch_bounds__(TPB) void k_cg_dir(Launch ln, Geo geo, Coef<C> M, C
   if (ctl->outer_done | ctl->inner_done) return;
   count_work(ctl, KC_CG_DIR);
   const int first = ctl->iters == 0;
-  InAxpy<C, S, VEC> f{z, pold, (C)ctl->beta, !first};
+  const InAxpy<C, S, VEC> f{z, first ? z : pold, first ? C(0) : (C)ctl->beta};
   const int L = xcd_block(ln.G);
   double acc[1] = {0.0};
   for (int it = 0; it < ln.nit; ++it) {
@@ -593,16 +601,24 @@ __global__ __launch_bounds__(TPB) void k_cg_dir(Launch ln, Geo geo, Coef<C> M, C
     }
     if (g >= ln.ng) break;
     C p[VEC], w[VEC];
-    mlp_group<S, C, VEC, FMT>(geo, M, msig, g, csum, f, p, w);
-    C s = C(0);
+    mlp_group<S, C, VEC, FMT, FL>(geo, M, msig, g, csum, f, p, w);
+    if constexpr (FL) {  // (zero past the end: the vectors are padded)
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-      w[v] = rnd<S, C>(w[v]);
-      s += p[v] * w[v];
+      for (int v = 0; v < VEC; ++v) {
+        w[v] = rnd<S, C>(w[v]);
+        acc[0] += (double)(p[v] * w[v]);
+      }
+    } else {
+      C s = C(0);
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        w[v] = rnd<S, C>(w[v]);
+        s += as_fp32<S, C>(p[v]) * w[v];
+      }
+      acc[0] += (double)s;
     }
     storev<S, C, VEC>(pnew + g * VEC, p);
     storev<S, C, VEC>(q + g * VEC, w);
-    acc[0] += (double)s;
   }
   __shared__ double tot[1];
   if (!reduce_to_last<1>(acc, 1, red, L, ln.G, tot)) return;
@@ -620,7 +636,7 @@ __global__ __launch_bounds__(TPB) void k_cg_dir(Launch ln, Geo geo, Coef<C> M, C
 }
 
 // x += alpha p (x = alpha p first), r -= alpha q, z = BJ(r), rz, rr; convergence test.
-template <typename S, typename C, int VEC, int BS, int AD = 0>
+template <typename S, typename C, int VEC, int BS, int AD, int FL>
 __global__ __launch_bounds__(TPB) void k_cg_upd(Launch ln, S* __restrict__ x,
                                                 const S* __restrict__ p, S* __restrict__ r,
                                                 const S* __restrict__ q, S* __restrict__ z,
@@ -647,16 +663,23 @@ __global__ __launch_bounds__(TPB) void k_cg_upd(Launch ln, S* __restrict__ x,
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
       xv[v] = first ? alpha * pv[v] : xv[v] + alpha * pv[v];
-      rv[v] = valid ? rnd<S, C>(rv[v] - alpha * qv[v]) : C(0);
+      if constexpr (FL || AD == 2) {
+        xv[v] = rnd2<S, C>(xv[v]);
+        rv[v] = rnd_fma<S, C>(-alpha, qv[v], rv[v]);
+        if (!valid || (FL && e + v >= ln.n)) rv[v] = C(0);
+      } else {
+        rv[v] = valid ? rnd<S, C>(rv[v] - alpha * qv[v]) : C(0);
+      }
     }
     if (valid) {
       storev<S, C, VEC>(x + e, xv);
       storev<S, C, VEC>(r + e, rv);
     }
+    constexpr int ZR = FL || AD == 2 ? 1 : 0;
     C prz = C(0), prr = C(0);
     if constexpr (BS > 0) {
-      if constexpr (bj_early<S, VEC, BS>()) bj_mul<C, S, VEC, BS, AD>(dinv, e, R, valid, rv, zv);
-      else bj_apply_lane<C, S, VEC, BS, AD>(dinv, e, valid, rv, zv);
+      if constexpr (bj_early<S, VEC, BS>()) bj_mul<C, S, VEC, BS, AD, ZR>(dinv, e, R, valid, rv, zv);
+      else bj_apply_lane<C, S, VEC, BS, AD, ZR>(dinv, e, valid, rv, zv);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) zv[v] = rnd<S, C>(zv[v]);
       if (valid) storev<S, C, VEC>(z + e, zv);
@@ -664,12 +687,19 @@ __global__ __launch_bounds__(TPB) void k_cg_upd(Launch ln, S* __restrict__ x,
     if (valid) {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
-        prr += rv[v] * rv[v];
-        if constexpr (BS > 0) prz += rv[v] * zv[v];
+        if constexpr (FL) {
+          acc[1] += (double)(rv[v] * rv[v]);
+          if constexpr (BS > 0) acc[0] += (double)(rv[v] * zv[v]);
+        } else {
+          prr += rv[v] * rv[v];
+          if constexpr (BS > 0) prz += rv[v] * zv[v];
+        }
       }
     }
-    acc[0] += (double)prz;
-    acc[1] += (double)prr;
+    if constexpr (!FL) {
+      acc[0] += (double)prz;
+      acc[1] += (double)prr;
+    }
   }
   __shared__ double tot[2];
   if (!reduce_to_last<2>(acc, 2, red, L, ln.G, tot)) return;
@@ -690,7 +720,7 @@ __global__ __launch_bounds__(TPB) void k_cg_upd(Launch ln, S* __restrict__ x,
 }
 
 // End of a CG pass: y += scale * x ; one LP pass done.
-template <typename S, typename C, int VEC>
+template <typename S, typename C, int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_promote(Launch ln, double* __restrict__ y,
                                                  const S* __restrict__ x, Ctl* ctl) {
   if (ctl->outer_done) return;
@@ -709,11 +739,11 @@ __global__ __launch_bounds__(TPB) void k_promote(Launch ln, double* __restrict__
     if (g >= ln.ng) break;
     double yv[VEC];
     C xv[VEC];
-    loadv<double, double, VEC>(y + g * VEC, yv);
+    loadg<double, double, VEC, FL>(y, g * VEC, ln.n, yv);
     loadv<C, S, VEC>(x + g * VEC, xv);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) yv[v] += s * (double)xv[v];
-    storev<double, double, VEC>(y + g * VEC, yv);
+    storeg<double, double, VEC, FL>(y, g * VEC, ln.n, yv);
   }
 }
 
@@ -726,7 +756,7 @@ __global__ __launch_bounds__(TPB) void k_promote(Launch ln, double* __restrict__
 
 // Start of a GMRES cycle: V_0 = LP(res / scale) ; zt = BJ(V_0) (the preconditioned direction of the first
 // Arnoldi step, before normalisation; BJ is linear) ; beta = ||V_0||_rms.
-template <typename S, typename C, int VEC, int BS, int AD = 0>
+template <typename S, typename C, int VEC, int BS, int AD, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_begin(Launch ln, const double* __restrict__ res,
                                                   S* __restrict__ v0, S* __restrict__ zt,
                                                   BJ<S> dinv, SolveCfg cfg,
@@ -741,7 +771,7 @@ __global__ __launch_bounds__(TPB) void k_gm_begin(Launch ln, const double* __res
     const bool valid = g < ln.ng;
     const int e = valid ? g * VEC : 0;  // an invalid lane reads group 0 and discards it
     double t[VEC];
-    loadv<double, double, VEC>(res + e, t);
+    loadg<double, double, VEC, FL>(res, e, ln.n, t);
     BJRows<S, VEC, bj_early<S, VEC, BS>() ? BS : 1> R;
     if constexpr (bj_early<S, VEC, BS>()) bj_load<S, VEC, BS, AD>(dinv, e, valid, R);
     __builtin_amdgcn_sched_barrier(0);  // res and the rows in flight together
@@ -750,16 +780,17 @@ __global__ __launch_bounds__(TPB) void k_gm_begin(Launch ln, const double* __res
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
       rv[v] = valid ? rnd<S, C>((C)(t[v] * inv)) : C(0);
-      s += rv[v] * rv[v];
+      if constexpr (FL) acc[0] += (double)(rv[v] * rv[v]);
+      else s += rv[v] * rv[v];
     }
     if (valid) storev<S, C, VEC>(v0 + e, rv);
     if constexpr (BS > 0) {
       C zv[VEC];
-      if constexpr (bj_early<S, VEC, BS>()) bj_mul<C, S, VEC, BS, AD>(dinv, e, R, valid, rv, zv);
-      else bj_apply_lane<C, S, VEC, BS, AD>(dinv, e, valid, rv, zv);
+      if constexpr (bj_early<S, VEC, BS>()) bj_mul<C, S, VEC, BS, AD, (FL || AD == 2 ? 1 : 0)>(dinv, e, R, valid, rv, zv);
+      else bj_apply_lane<C, S, VEC, BS, AD, (FL || AD == 2 ? 1 : 0)>(dinv, e, valid, rv, zv);
       if (valid) storev<S, C, VEC>(zt + e, zv);
     }
-    acc[0] += (double)s;
+    if constexpr (!FL) acc[0] += (double)s;
   }
   __shared__ double tot[1];
   if (!reduce_to_last<1>(acc, 1, red, L, ln.G, tot)) return;
@@ -834,7 +865,7 @@ __device__ __forceinline__ bool gm_bound_exceeded(Ctl* ctl, int nd, int ndm) {
 // w = M BJ(v_j) (PREC: z + j zstride holds BJ of the stored vector j, scaled here by vscale[j];
 // zstride = 0 for a single preconditioned-direction buffer) or w = M v_j ; V_{j+1} := LP(w) ;
 // d_i = (V_i, LP(w)) for i <= j.
-template <typename S, typename C, int VEC, int FMT, int PREC, int NDM>
+template <typename S, typename C, int VEC, int FMT, int PREC, int NDM, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_matvec(Launch ln, Geo geo, Coef<C> M, Csr csr,
                                                    const S* __restrict__ mval, C msig,
                                                    const S* __restrict__ z, size_t zstride,
@@ -847,9 +878,11 @@ __global__ __launch_bounds__(TPB) void k_gm_matvec(Launch ln, Geo geo, Coef<C> M
   count_work(ctl, KC_GM_MATVEC, nd);
   S* wout = V + (size_t)(j + 1) * vstride;
   const int L = xcd_block(ln.G);
-  C dacc[NDM];
+  // flat groups add every product in FP64 (a group of one did), else a group's are added in C
+  using D = std::conditional_t<FL == 1, double, C>;
+  D dacc[NDM];
 #pragma unroll
-  for (int i = 0; i < NDM; ++i) dacc[i] = C(0);
+  for (int i = 0; i < NDM; ++i) dacc[i] = D(0);
   constexpr int CH = basis_chunk<S, VEC>() < NDM ? basis_chunk<S, VEC>() : NDM;
   const InScaled<C, S, VEC> f{PREC ? z + (size_t)j * zstride : V + (size_t)j * vstride,
                               (C)ctl->vscale[j]};
@@ -872,16 +905,19 @@ __global__ __launch_bounds__(TPB) void k_gm_matvec(Launch ln, Geo geo, Coef<C> M
       if (g >= ln.ng) break;
     }
     C ctr[VEC], w[VEC];
-    mlp_group<S, C, VEC, FMT>(geo, M, msig, g, csum, f, ctr, w);
+    mlp_group<S, C, VEC, FMT, FL>(geo, M, msig, g, csum, f, ctr, w);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) w[v] = rnd<S, C>(w[v]);
     storev<S, C, VEC>(wout + e, w);
 #pragma unroll
     for (int k = 0; k < CH; ++k) {
-      C s = C(0);
+      D s = D(0);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) s += (C)v0[k].v[v] * w[v];
-      dacc[k] += (k < nd) ? s : C(0);
+      for (int v = 0; v < VEC; ++v) {
+        if constexpr (FL) s += (double)((C)v0[k].v[v] * w[v]);
+        else s += (C)v0[k].v[v] * w[v];
+      }
+      dacc[k] += (k < nd) ? s : D(0);
     }
     // remaining basis vectors in chunks of CH whose loads are issued together (indices past
     // nd are clamped to a valid vector and their contribution discarded)
@@ -895,10 +931,13 @@ __global__ __launch_bounds__(TPB) void k_gm_matvec(Launch ln, Geo geo, Coef<C> M
 #pragma unroll
         for (int k = 0; k < CH; ++k) {
           if (c + k < NDM) {
-            C s = C(0);
+            D s = D(0);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) s += vv[k][v] * w[v];
-            dacc[c + k] += (c + k < nd) ? s : C(0);
+            for (int v = 0; v < VEC; ++v) {
+              if constexpr (FL) s += (double)(vv[k][v] * w[v]);
+              else s += vv[k][v] * w[v];
+            }
+            dacc[c + k] += (c + k < nd) ? s : D(0);
           }
         }
       }
@@ -920,7 +959,7 @@ __global__ __launch_bounds__(TPB) void k_gm_matvec(Launch ln, Geo geo, Coef<C> M
 // products d_i = (V_i, w') are taken in the same launch (the basis chunks are read again,
 // normally from cache).  The first pass's h moves to hacc and d becomes the coefficient set
 // that k_gm_orth subtracts; the Hessenberg column is h + d.
-template <typename S, typename C, int VEC, int NDM>
+template <typename S, typename C, int VEC, int NDM, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_reorth(Launch ln, S* __restrict__ V, size_t vstride,
                                                    SolveCfg cfg, Ctl* ctl, Red red) {
   if (ctl->outer_done | ctl->inner_done) return;
@@ -934,9 +973,10 @@ __global__ __launch_bounds__(TPB) void k_gm_reorth(Launch ln, S* __restrict__ V,
   S* w = V + (size_t)(j + 1) * vstride;
   const int L = xcd_block(ln.G);
   constexpr int CH = basis_chunk<S, VEC>() < NDM ? basis_chunk<S, VEC>() : NDM;
-  C dacc[NDM];
+  using D = std::conditional_t<FL == 1, double, C>;  // (as k_gm_matvec)
+  D dacc[NDM];
 #pragma unroll
-  for (int i = 0; i < NDM; ++i) dacc[i] = C(0);
+  for (int i = 0; i < NDM; ++i) dacc[i] = D(0);
   for (int it = 0; it < ln.nit; ++it) {
     const int g = (L * ln.nit + it) * TPB + threadIdx.x;
     if (g >= ln.ng) break;
@@ -962,7 +1002,7 @@ __global__ __launch_bounds__(TPB) void k_gm_reorth(Launch ln, S* __restrict__ V,
       }
     }
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) wv[v] = rnd<S, C>(wv[v]);
+    for (int v = 0; v < VEC; ++v) wv[v] = FL && e + v >= ln.n ? C(0) : rnd<S, C>(wv[v]);
     storev<S, C, VEC>(w + e, wv);
     // d = V^T w' (the stored, rounded w')
 #pragma unroll
@@ -975,10 +1015,13 @@ __global__ __launch_bounds__(TPB) void k_gm_reorth(Launch ln, S* __restrict__ V,
 #pragma unroll
         for (int k = 0; k < CH; ++k) {
           if (c + k < NDM) {
-            C s = C(0);
+            D s = D(0);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) s += vv[k][v] * wv[v];
-            dacc[c + k] += (c + k < nd) ? s : C(0);
+            for (int v = 0; v < VEC; ++v) {
+              if constexpr (FL) s += (double)(vv[k][v] * wv[v]);
+              else s += vv[k][v] * wv[v];
+            }
+            dacc[c + k] += (c + k < nd) ? s : D(0);
           }
         }
       }
@@ -999,7 +1042,7 @@ __global__ __launch_bounds__(TPB) void k_gm_reorth(Launch ln, S* __restrict__ V,
 // k_gm_reorth in the second pass of CGS2); h_{j+1,j} = ||w||; Givens update of the Hessenberg column; residual estimate |g_{j+1}|.
 // With a preconditioner (BS > 0) also BJ(w), the next step's preconditioned direction before
 // normalisation, stored at zt + (j + 1) zstride (zstride = 0: the single buffer zt).
-template <typename S, typename C, int VEC, int BS, int NDM, int AD = 0>
+template <typename S, typename C, int VEC, int BS, int NDM, int AD, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_orth(Launch ln, S* __restrict__ V, size_t vstride,
                                                  S* __restrict__ zt, size_t zstride, BJ<S> dinv,
                                                  SolveCfg cfg, Ctl* ctl, Red red) {
@@ -1036,10 +1079,21 @@ __global__ __launch_bounds__(TPB) void k_gm_orth(Launch ln, S* __restrict__ V, s
     C wv[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) wv[v] = (C)wr.v[v];
+    // flat groups with a small basis round w - V h with its last product (the groups of one that
+    // they replace did); every other form rounds the finished sum
+    constexpr bool LAST = FL == 1 && NDM <= 8;
 #pragma unroll
     for (int k = 0; k < CH; ++k) {  // cf is zero past nd
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) wv[v] -= cf[k] * (C)v0[k].v[v];
+      for (int v = 0; v < VEC; ++v) {
+        if constexpr (LAST && CH == NDM) {
+          if (k == NDM - 1) {
+            wv[v] = rnd_fma<S, C>(-cf[k], (C)v0[k].v[v], wv[v]);
+            continue;
+          }
+        }
+        wv[v] -= cf[k] * (C)v0[k].v[v];
+      }
     }
 #pragma unroll
     for (int c = CH; c < NDM; c += CH) {
@@ -1052,7 +1106,15 @@ __global__ __launch_bounds__(TPB) void k_gm_orth(Launch ln, S* __restrict__ V, s
         for (int k = 0; k < CH; ++k) {
           if (c + k < NDM) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) wv[v] -= cf[c + k] * vv[k][v];
+            for (int v = 0; v < VEC; ++v) {
+              if constexpr (LAST) {
+                if (c + k == NDM - 1) {
+                  wv[v] = rnd_fma<S, C>(-cf[c + k], vv[k][v], wv[v]);
+                  continue;
+                }
+              }
+              wv[v] -= cf[c + k] * vv[k][v];
+            }
           }
         }
       }
@@ -1060,17 +1122,22 @@ __global__ __launch_bounds__(TPB) void k_gm_orth(Launch ln, S* __restrict__ V, s
     C s = C(0);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
-      wv[v] = valid ? rnd<S, C>(wv[v]) : C(0);
-      s += wv[v] * wv[v];
+      if constexpr (FL || AD == 2) {
+        wv[v] = valid && !(FL && e + v >= ln.n) ? rnd2<S, C>(wv[v]) : C(0);
+      } else {
+        wv[v] = valid ? rnd<S, C>(wv[v]) : C(0);
+      }
+      if constexpr (FL) acc[0] += (double)(wv[v] * wv[v]);
+      else s += wv[v] * wv[v];
     }
     if (valid) storev<S, C, VEC>(w + e, wv);
     if constexpr (BS > 0) {
       C zv[VEC];
-      if constexpr (EARLY) bj_mul<C, S, VEC, BS, AD>(dinv, e, R, valid, wv, zv);
-      else bj_apply_lane<C, S, VEC, BS, AD>(dinv, e, valid, wv, zv);
+      if constexpr (EARLY) bj_mul<C, S, VEC, BS, AD, (FL || AD == 2 ? 1 : 0)>(dinv, e, R, valid, wv, zv);
+      else bj_apply_lane<C, S, VEC, BS, AD, (FL || AD == 2 ? 1 : 0)>(dinv, e, valid, wv, zv);
       if (valid) storev<S, C, VEC>(zw + e, zv);
     }
-    acc[0] += (double)s;
+    if constexpr (!FL) acc[0] += (double)s;
   }
   __shared__ double tot[1];
   if (!reduce_to_last<1>(acc, 1, red, L, ln.G, tot)) return;
@@ -1446,7 +1513,7 @@ __global__ __launch_bounds__(TPB) void k_gm_zclose(Launch ln, const S* __restric
 // triangular least-squares system is solved here by every block (J <= 32), so a cycle the
 // host ends early (fewer iterations enqueued than the device would run) is still promoted.
 // NDM bounds J: the host passes the number of Arnoldi steps it enqueued in this cycle.
-template <typename S, typename C, int VEC, int BS, int NDM, int AD = 0>
+template <typename S, typename C, int VEC, int BS, int NDM, int AD, int FL>
 __global__ __launch_bounds__(TPB) void k_gm_finish(Launch ln, double* __restrict__ y,
                                                    const S* __restrict__ V, size_t vstride,
                                                    BJ<S> dinv, Ctl* ctl) {
@@ -1495,7 +1562,7 @@ __global__ __launch_bounds__(TPB) void k_gm_finish(Launch ln, double* __restrict
     BJRows<S, VEC, bj_early<S, VEC, BS>() ? BS : 1> R;
     if constexpr (bj_early<S, VEC, BS>()) bj_load<S, VEC, BS, AD>(dinv, e, valid, R);
     double yv[VEC];
-    loadv<double, double, VEC>(y + e, yv);
+    loadg<double, double, VEC, FL>(y, e, ln.n, yv);
     C t[VEC], zv[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) t[v] = C(0);
@@ -1532,7 +1599,7 @@ __global__ __launch_bounds__(TPB) void k_gm_finish(Launch ln, double* __restrict
     if (valid) {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) yv[v] += sc * (double)zv[v];
-      storev<double, double, VEC>(y + e, yv);
+      storeg<double, double, VEC, FL>(y, e, ln.n, yv);
     }
   }
 }

@@ -54,19 +54,19 @@ int set_error(int code, const std::string& msg) {
   return code;
 }
 
-Launch make_launch_nit(long ng, int nit) {
+// n unknowns in groups of vec, nit groups per thread
+Launch make_launch_nit(long n, int vec, int nit) {
+  const long ng = (n + vec - 1) / vec;
   long G = (ng + (long)nit * TPB - 1) / ((long)nit * TPB);
   G = std::max(8L, (G + 7) / 8 * 8);
-  return Launch{(int)ng, nit, (int)G};
+  return Launch{(int)ng, nit, (int)G, (int)n};
 }
 
-Launch make_launch(long ng) {
+Launch make_launch(long n, int vec) {
   const long target_blocks = 2048;  // 8 resident 256-thread blocks on each of 256 CUs
-  long nit = (ng + (long)TPB * target_blocks - 1) / ((long)TPB * target_blocks);
-  nit = std::max(1L, std::min(nit, 8L));
-  long G = (ng + nit * TPB - 1) / (nit * TPB);
-  G = std::max(8L, (G + 7) / 8 * 8);
-  return Launch{(int)ng, (int)nit, (int)G};
+  const long ng = (n + vec - 1) / vec;
+  const long nit = (ng + (long)TPB * target_blocks - 1) / ((long)TPB * target_blocks);
+  return make_launch_nit(n, vec, (int)std::max(1L, std::min(nit, 8L)));
 }
 
 // 7-point coefficients of K (FP64): K u = kc u + sum_d (km_d u[-e_d] + kp_d u[+e_d]).
@@ -214,6 +214,19 @@ static void bj_dedup(const Geo& geo, const Coef<double>& K, double sigma, int bs
     last = slot;
     last_key = key;
   }
+}
+
+// Representative block of each slot of the table of modes 5 and 6 (device.hpp); a slot that no
+// block of this grid uses gets block 0.
+static void bj_table_reps(const Geo& geo, int bs, int mode, std::vector<int>& reps) {
+  const int nblk = (geo.N + bs - 1) / bs;
+  reps.assign(mode == 6 ? 1 : (size_t)bs + 1, 0);
+  if (mode == 6) return;
+  for (int b = 0; b < std::min(nblk, geo.nx); ++b) {  // the places repeat every nx blocks
+    const int k = geo.nx - (int)((long)b * bs % geo.nx);
+    if ((long)(b + 1) * bs <= geo.N) reps[(size_t)(k < bs ? k : 0)] = b;
+  }
+  reps[(size_t)bs] = nblk - 1;
 }
 
 // Adaptive-precision block-Jacobi layout (Ginkgo's adaptive block-Jacobi, cited in the
@@ -543,10 +556,13 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   prec = p;
   dt = dt_;
   stream = s;
-  geo = Geo{g.nx, g.ny, g.nz, g.bc, g.nx * g.ny * g.nz, g.nx * g.ny};
+  geo = make_geo(g.nx, g.ny, g.nz, g.bc);
   N = geo.N;
-  vec = (g.nx % 4 == 0) ? 4 : 1;
-  vec_lp = (p.storage == MPRK_FP16 && g.nx % 8 == 0) ? 8 : vec;
+  vec = 4;
+  flat = g.nx % 4 != 0;
+  vec_lp = (p.storage == MPRK_FP16 && g.nx % 8 != 4) ? 8 : 4;
+  flat_lp = g.nx % vec_lp != 0;
+  vec_ad = flat_lp ? 1 : vec_lp;
   Kc = operator_coef(g, o);
   // FP64 arithmetic over FP32 / FP16 storage: the compressed-basis variants
   const bool cb = p.compute == MPRK_FP64 && p.storage != MPRK_FP64;
@@ -579,14 +595,14 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
         need_keps = true;
   }
   // launches
-  ln_vec = make_launch(N / vec);
-  ln_row = make_launch(N);
+  ln_vec = make_launch(N, vec);
+  ln_row = make_launch(N, 1);
   // kernels with a grid reduction: one group per thread by default (the two-level reduction
   // keeps its cost independent of the number of blocks)
-  ln_vec_red = make_launch_nit(N / vec, 1);
-  ln_row_red = make_launch_nit(N, 1);
-  ln_lp = make_launch(N / vec_lp);
-  ln_lp_red = make_launch_nit(N / vec_lp, 1);
+  ln_vec_red = make_launch_nit(N, vec, 1);
+  ln_row_red = make_launch_nit(N, 1, 1);
+  ln_lp = make_launch(N, vec_lp);
+  ln_lp_red = make_launch_nit(N, vec_lp, 1);
   // z-marching residual: about four workgroups per CU (planes per tile a power of two in
   // [ZM_LZ_MIN, 32]); the autotuner may switch to another tile depth or the gather kernel
   long zm_g_max = 0;
@@ -641,8 +657,9 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   o_rhs = take(v64);
   o_y = take(v64);
   o_res = take(v64);
-  o_k = take(v64 * nstages);
-  o_keps = need_keps ? take(v64 * nstages) : 0;
+  kstride = flat ? align256(v64) : v64;  // (flat groups: every vector starts on a group)
+  o_k = take(kstride * nstages);
+  o_keps = need_keps ? take(kstride * nstages) : 0;
   o_scr = take(v64);  // scratch FP64 vector (solve output of k, verification)
   fdm = p.precond == MPRK_PRECOND_FDM;
   // the fast-diagonalisation inverse is exact for the operators it accepts: one Krylov iteration
@@ -689,7 +706,17 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   bjsets.assign(bs ? sigmas.size() : 0, BJSet());
   for (size_t q = 0; q < bjsets.size(); ++q) {
     BJSet& B = bjsets[q];
-    if (p.bj_shared) {
+    // the matrix-free operator's blocks come from a table of its distinct ones, whose slots
+    // follow from the row number (no pass over the blocks): every block alike when bs | nx, else
+    // one slot per place where an x-row can end inside a block (nx > bs, so that at most one does)
+    // (FP16 CG on groups of 4 keeps one inverse per block: the rounding of its update is the
+    // compiler's choice there and would move with the kernel)
+    const bool own = p.storage == MPRK_FP16 && p.compute == MPRK_FP32 && p.krylov == MPRK_CG && vec_lp == 4;
+    if (o.format == MPRK_FMT_STENCIL && !(p.bj_adapt_tol > 0.0) && !own && (g.nx % bs == 0 || g.nx > bs)) {
+      B.mode = g.nx % bs == 0 ? 6 : 5;
+      bj_table_reps(geo, bs, B.mode, B.reps);
+      B.nslot = (int)B.reps.size();
+    } else if (p.bj_shared) {
       bj_dedup(geo, Kc, sigmas[q], bs, B.reps, B.idx);
       B.nslot = (int)B.reps.size();
       B.mode = B.nslot == 1 ? 2 : 1;
@@ -699,15 +726,18 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
       B.mode = p.bj_adapt_tol > 0.0 ? 4 : 3;  // rows interleaved for lanes of vec_lp rows
     }
     if (B.mode == 4) {
-      bj_adaptive_layout(geo, Kc, sigmas[q], bs, vec_lp, p.bj_adapt_tol, B.tag, B.aoff);
+      bj_adaptive_layout(geo, Kc, sigmas[q], bs, vec_ad, p.bj_adapt_tol, B.tag, B.aoff);
       B.o_inv = take((size_t)B.aoff.back());
       B.aoff.pop_back();
       B.o_tag = take(B.tag.size() * 4);
       B.o_aoff = take(B.aoff.size() * 8);
       continue;
     }
-    const size_t rows = B.mode == 3 ? std::max((size_t)nblk * bs, bj_chunks((long)nblk * bs, vec_lp))
-                                    : (size_t)B.nslot * bs;
+    // (bj_shared = 0 keeps its documented footprint, one inverse per block, in every format)
+    const size_t rows = B.mode == 3 || !p.bj_shared
+                            ? std::max({(size_t)nblk * bs, bj_chunks((long)nblk * bs, vec_lp),
+                                        (size_t)B.nslot * bs})
+                            : (size_t)B.nslot * bs;
     B.o_inv = take(rows * bs * lp_bytes);
     if (B.table()) B.o_reps = take((size_t)B.nslot * 4);
     if (B.mode == 1) B.o_idx = take((size_t)nblk * 4);
@@ -808,6 +838,7 @@ EngineCtx mprk_handle::ctx() const {
   c.geo = geo;
   c.fmt = op.format;
   c.vec = vec_lp;
+  c.flat = flat_lp;
   c.ln_vec = ln_lp;
   c.ln_row = ln_row;
   c.ln_mv = op.format == MPRK_FMT_CSR ? ln_row : ln_lp;
@@ -902,7 +933,7 @@ static int bind_impl(mprk_handle* h, double* u_dev, void* workspace_dev) {
       atag = (const int*)(h->ws + B.o_tag);
       aoff = (const long long*)(h->ws + B.o_aoff);
     }
-    const int lay = (B.mode == 3 || B.mode == 4) ? h->vec_lp : 0;
+    const int lay = B.mode == 3 ? h->vec_lp : B.mode == 4 ? h->vec_ad : 0;
     if (h->op.format == MPRK_FMT_CSR)
       HIPCHK(h->eng->bj_setup_csr(c, (const double*)(h->ws + h->o_kval), h->sigmas[q], dinv, fail,
                                   B.nslot, reps, lay, atag, aoff));
@@ -1113,7 +1144,7 @@ BJDesc mprk_handle::bj_desc(int si) const {
   const BJSet& B = bjsets[si];
   return BJDesc{ws + B.o_inv, B.mode == 1 ? (const int*)(ws + B.o_idx) : nullptr, B.mode,
                 B.mode == 4 ? (const int*)(ws + B.o_tag) : nullptr,
-                B.mode == 4 ? (const long long*)(ws + B.o_aoff) : nullptr};
+                B.mode == 4 ? (const long long*)(ws + B.o_aoff) : nullptr, geo.nx, geo.N, geo.dx, vec_ad};
 }
 
 int mprk_handle::launch_residual(const SolveCfg& cfg, const double* rhs, double* y, double* kout,
@@ -1124,16 +1155,16 @@ int mprk_handle::launch_residual(const SolveCfg& cfg, const double* rhs, double*
   const Csr csr{(const int*)(ws + o_rowptr), (const int*)(ws + o_col)};
   const double* kval = (const double*)(ws + o_kval);
   if (op.format == MPRK_FMT_CSR)
-    PLAUNCH(KC_RESIDUAL, (k_residual<1, 1>), dim3(ln_row_red.G), dim3(TPB), 0, stream, ln_row_red, geo, Kc, csr,
+    PLAUNCH(KC_RESIDUAL, (k_residual<1, 1, 0>), dim3(ln_row_red.G), dim3(TPB), 0, stream, ln_row_red, geo, Kc, csr,
                        kval, y, rhs, kout, res, fx, cfg, ctl, rd);
-  else if (zm_lz > 0)  // (zm_lz > 0 implies vec == 4)
+  else if (zm_lz > 0)  // (zm_lz > 0 implies groups within x-rows)
     PLAUNCH(KC_RESIDUAL, (k_residual_zm<4>), dim3(zl_res.G), dim3(TPB), zmarch_lds(geo, zl_res, 8), stream,
             zl_res, geo, Kc, y, rhs, kout, res, fx, cfg, ctl, rd);
-  else if (vec == 4)
-    PLAUNCH(KC_RESIDUAL, (k_residual<4, 0>), dim3(ln_vec_red.G), dim3(TPB), 0, stream, ln_vec_red, geo, Kc, csr,
+  else if (!flat)
+    PLAUNCH(KC_RESIDUAL, (k_residual<4, 0, 0>), dim3(ln_vec_red.G), dim3(TPB), 0, stream, ln_vec_red, geo, Kc, csr,
                        kval, y, rhs, kout, res, fx, cfg, ctl, rd);
   else
-    PLAUNCH(KC_RESIDUAL, (k_residual<1, 0>), dim3(ln_vec_red.G), dim3(TPB), 0, stream, ln_vec_red, geo, Kc, csr,
+    PLAUNCH(KC_RESIDUAL, (k_residual<4, 0, 1>), dim3(ln_vec_red.G), dim3(TPB), 0, stream, ln_vec_red, geo, Kc, csr,
                        kval, y, rhs, kout, res, fx, cfg, ctl, rd);
   HIPCHK(hipGetLastError());
   return MPRK_OK;
@@ -1266,8 +1297,8 @@ int mprk_handle::enqueue_step(bool first_of_call) {
   Ctl* ctl = (Ctl*)(ws + o_ctl);
   double* rhs = (double*)(ws + o_rhs);
   double* y = (double*)(ws + o_y);
-  auto kvec = [&](int j) { return (double*)(ws + o_k + (size_t)j * N * 8); };
-  auto evec = [&](int j) { return (double*)(ws + o_keps + (size_t)j * N * 8); };
+  auto kvec = [&](int j) { return (double*)(ws + o_k + (size_t)j * kstride); };
+  auto evec = [&](int j) { return (double*)(ws + o_keps + (size_t)j * kstride); };
   const int s = nstages;
   // f(u), the slope at the step's start, for the start values (an explicit first stage
   // computes it as k_0)
@@ -1324,10 +1355,10 @@ int mprk_handle::enqueue_step(bool first_of_call) {
     }
     const int reset = i > 0 ? RESET_STAGE
                             : RESET_STAGE | RESET_STEP | (first_of_call ? RESET_CALL : 0);
-    if (vec == 4)
-      PLAUNCH(KC_STAGE_RHS, (k_stage_rhs<4>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, rhs, y, ctl, reset);
+    if (!flat)
+      PLAUNCH(KC_STAGE_RHS, (k_stage_rhs<4, 0>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, rhs, y, ctl, reset);
     else
-      PLAUNCH(KC_STAGE_RHS, (k_stage_rhs<1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, rhs, y, ctl, reset);
+      PLAUNCH(KC_STAGE_RHS, (k_stage_rhs<4, 1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, rhs, y, ctl, reset);
     HIPCHK(hipGetLastError());
     if (!implicit_[i]) {
       int rc = launch_apply64(y, kvec(i), 0.0, 0, fterms());
@@ -1338,10 +1369,10 @@ int mprk_handle::enqueue_step(bool first_of_call) {
     if (rc) return rc;
     if (need_keps) {
       const double inv = 1.0 / cfgs[sig_idx[i]].sigma;
-      if (vec == 4)
-        PLAUNCH(KC_KEPS, (k_keps<4>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, y, rhs, inv, evec(i));
+      if (!flat)
+        PLAUNCH(KC_KEPS, (k_keps<4, 0>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, y, rhs, inv, evec(i));
       else
-        PLAUNCH(KC_KEPS, (k_keps<1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, y, rhs, inv, evec(i));
+        PLAUNCH(KC_KEPS, (k_keps<4, 1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, y, rhs, inv, evec(i));
       HIPCHK(hipGetLastError());
     }
   }
@@ -1352,10 +1383,10 @@ int mprk_handle::enqueue_step(bool first_of_call) {
       a.v[a.nv] = kvec(i);
       a.c[a.nv++] = dt * tab.b[i];
     }
-  if (vec == 4)
-    PLAUNCH(KC_COMBINE, (k_combine<4>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, ctl);
+  if (!flat)
+    PLAUNCH(KC_COMBINE, (k_combine<4, 0>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, ctl);
   else
-    PLAUNCH(KC_COMBINE, (k_combine<1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, ctl);
+    PLAUNCH(KC_COMBINE, (k_combine<4, 1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, u, a, ctl);
   HIPCHK(hipGetLastError());
   return MPRK_OK;
 }
@@ -1365,13 +1396,13 @@ int mprk_handle::launch_apply64(const double* x, double* y, double sigma, int mo
   const Csr csr{(const int*)(ws + o_rowptr), (const int*)(ws + o_col)};
   const double* kval = (const double*)(ws + o_kval);
   if (op.format == MPRK_FMT_CSR)
-    PLAUNCH(KC_APPLY64, (k_apply64<1, 1>), dim3(ln_row.G), dim3(TPB), 0, stream, ln_row, geo, Kc, csr, kval,
+    PLAUNCH(KC_APPLY64, (k_apply64<1, 1, 0>), dim3(ln_row.G), dim3(TPB), 0, stream, ln_row, geo, Kc, csr, kval,
                        x, y, sigma, mode, fx);
-  else if (vec == 4)
-    PLAUNCH(KC_APPLY64, (k_apply64<4, 0>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, geo, Kc, csr, kval,
+  else if (!flat)
+    PLAUNCH(KC_APPLY64, (k_apply64<4, 0, 0>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, geo, Kc, csr, kval,
                        x, y, sigma, mode, fx);
   else
-    PLAUNCH(KC_APPLY64, (k_apply64<1, 0>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, geo, Kc, csr, kval,
+    PLAUNCH(KC_APPLY64, (k_apply64<4, 0, 1>), dim3(ln_vec.G), dim3(TPB), 0, stream, ln_vec, geo, Kc, csr, kval,
                        x, y, sigma, mode, fx);
   HIPCHK(hipGetLastError());
   return MPRK_OK;
@@ -1599,11 +1630,11 @@ extern "C" int32_t mprk_solve(mprk_handle* h, int32_t stage, const double* rhs_d
   a.nv = 0;
   // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
   double* rhs = (double*)(h->ws + h->o_rhs);
-  if (h->vec == 4)
-    hipLaunchKernelGGL((k_stage_rhs<4>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, rhs_dev, a, rhs,
+  if (!h->flat)
+    hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, rhs_dev, a, rhs,
                        x_dev, ctl, RESET_STAGE | RESET_CALL);
   else
-    hipLaunchKernelGGL((k_stage_rhs<1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, rhs_dev, a, rhs,
+    hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, rhs_dev, a, rhs,
                        x_dev, ctl, RESET_STAGE | RESET_CALL);
   HIPCHK(hipGetLastError());
   int rc = h->run_solve(h->sig_idx[stage], MPRK_MAX_STAGES, rhs, x_dev, (double*)(h->ws + h->o_scr),
@@ -1805,7 +1836,6 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
   if (int rcw = h->check_ws()) return rcw;
   h->graph_epoch += 1;  // launch shapes may change
   const bool csr = h->op.format == MPRK_FMT_CSR;
-  const long ngv = h->N / h->vec, ngr = h->N, ngl = h->N / h->vec_lp;
   const TuneKey key{h->grid.nx, h->grid.ny, h->grid.nz, h->grid.bc, h->op.kind, h->op.format, h->prec.storage,
                     h->prec.compute};
   {
@@ -1813,12 +1843,12 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
     auto it = g_tuned.find(key);
     if (it != g_tuned.end()) {
       const TuneVal& v = it->second;
-      h->ln_vec = make_launch_nit(ngv, v.nv);
-      h->ln_row = make_launch_nit(ngr, v.nr);
-      h->ln_vec_red = make_launch_nit(ngv, v.nvr);
-      h->ln_row_red = make_launch_nit(ngr, v.nrr);
-      h->ln_lp = make_launch_nit(ngl, v.nl);
-      h->ln_lp_red = make_launch_nit(ngl, v.nlr);
+      h->ln_vec = make_launch_nit(h->N, h->vec, v.nv);
+      h->ln_row = make_launch_nit(h->N, 1, v.nr);
+      h->ln_vec_red = make_launch_nit(h->N, h->vec, v.nvr);
+      h->ln_row_red = make_launch_nit(h->N, 1, v.nrr);
+      h->ln_lp = make_launch_nit(h->N, h->vec_lp, v.nl);
+      h->ln_lp_red = make_launch_nit(h->N, h->vec_lp, v.nlr);
       h->set_residual_tiles(v.zlz);
       if (h->prec.krylov == MPRK_GMRES && h->prec.gm_form == MPRK_GMFORM_AUTO) h->set_gm_form(v.gform, v.glz);
       if (nit_vec) *nit_vec = v.nv;
@@ -1861,9 +1891,9 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
   float bv = 1e30f;
   for (int nit : {1, 2, 4, 8, 16}) {
     const Launch sv = h->ln_vec, sr = h->ln_row, sl = h->ln_lp;
-    h->ln_vec = make_launch_nit(ngv, nit);
-    h->ln_lp = make_launch_nit(ngl, nit);
-    if (csr) h->ln_row = make_launch_nit(ngr, nit);
+    h->ln_vec = make_launch_nit(h->N, h->vec, nit);
+    h->ln_lp = make_launch_nit(h->N, h->vec_lp, nit);
+    if (csr) h->ln_row = make_launch_nit(h->N, 1, nit);
     EngineCtx c = h->ctx();
     float ms;
     time_it([&]() {
@@ -1887,9 +1917,9 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
   for (int nit : {1, 2, 4, 8}) {
     if (rc || h->cfgs.empty()) break;
     const Launch sv = h->ln_vec_red, sr = h->ln_row_red, sl = h->ln_lp_red;
-    h->ln_vec_red = make_launch_nit(ngv, nit);
-    h->ln_row_red = make_launch_nit(ngr, nit);
-    h->ln_lp_red = make_launch_nit(ngl, nit);
+    h->ln_vec_red = make_launch_nit(h->N, h->vec, nit);
+    h->ln_row_red = make_launch_nit(h->N, 1, nit);
+    h->ln_lp_red = make_launch_nit(h->N, h->vec_lp, nit);
     if (h->ln_vec_red.G > h->pstride || h->ln_row_red.G > h->pstride || h->ln_lp_red.G > h->pstride) {
       h->ln_vec_red = sv;
       h->ln_row_red = sr;
@@ -1909,11 +1939,11 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
       ca.nv = 0;
       const unsigned nb = (unsigned)((h->N + 255) / 256);
       hipLaunchKernelGGL(k_fill_pattern, dim3(nb), dim3(256), 0, h->stream, (long)h->N, 0.37, 0.011, y64);
-      if (h->vec == 4)
-        hipLaunchKernelGGL((k_stage_rhs<4>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca, rhs, x64, ctl,
+      if (!h->flat)
+        hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca, rhs, x64, ctl,
                            RESET_STAGE | RESET_CALL);
       else
-        hipLaunchKernelGGL((k_stage_rhs<1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca, rhs, x64, ctl,
+        hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca, rhs, x64, ctl,
                            RESET_STAGE | RESET_CALL);
       hipLaunchKernelGGL(k_fill_pattern, dim3(nb), dim3(256), 0, h->stream, (long)h->N, 0.23, 0.017, x64);
       if (hipGetLastError() != hipSuccess) { rc = MPRK_EDEVICE; break; }
@@ -1944,7 +1974,7 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
   if (rc == MPRK_OK && h->op.format == MPRK_FMT_STENCIL && zmarch_fits(h->geo, h->vec) &&
       !h->cfgs.empty()) {
     const Launch sv = h->ln_vec_red;
-    h->ln_vec_red = make_launch_nit(ngv, best.nvr);
+    h->ln_vec_red = make_launch_nit(h->N, h->vec, best.nvr);
     const int keep = h->zm_lz;
     float bz = 1e30f;
     for (int lz : {0, 2, 4, 8, 16, 32}) {
@@ -1954,7 +1984,7 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
       ca.nv = 0;
       const unsigned nb = (unsigned)((h->N + 255) / 256);
       hipLaunchKernelGGL(k_fill_pattern, dim3(nb), dim3(256), 0, h->stream, (long)h->N, 0.37, 0.011, y64);
-      hipLaunchKernelGGL((k_stage_rhs<4>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca, rhs,
+      hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca, rhs,
                          x64, ctl, RESET_STAGE | RESET_CALL);
       hipLaunchKernelGGL(k_fill_pattern, dim3(nb), dim3(256), 0, h->stream, (long)h->N, 0.23, 0.017, x64);
       if (hipGetLastError() != hipSuccess) { rc = MPRK_EDEVICE; break; }
@@ -1977,8 +2007,8 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
       (h->gform_ok & 6) && !h->cfgs.empty()) {
     const int keep_f = h->gform, keep_lz = h->zl_lp.LZ;
     const Launch sv = h->ln_vec_red, sl = h->ln_lp_red;
-    h->ln_vec_red = make_launch_nit(ngv, best.nvr);
-    h->ln_lp_red = make_launch_nit(ngl, best.nlr);
+    h->ln_vec_red = make_launch_nit(h->N, h->vec, best.nvr);
+    h->ln_lp_red = make_launch_nit(h->N, h->vec_lp, best.nlr);
     SolveCfg cfg = h->cfgs[si];
     cfg.rtol = 0.0;
     cfg.atol = 0.0;
@@ -2000,11 +2030,11 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
           ca.nv = 0;
           const unsigned nb = (unsigned)((h->N + 255) / 256);
           hipLaunchKernelGGL(k_fill_pattern, dim3(nb), dim3(256), 0, h->stream, (long)h->N, 0.37, 0.011, y64);
-          if (h->vec == 4)
-            hipLaunchKernelGGL((k_stage_rhs<4>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca,
+          if (!h->flat)
+            hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca,
                                rhs, x64, ctl, RESET_STAGE | RESET_CALL);
           else
-            hipLaunchKernelGGL((k_stage_rhs<1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca,
+            hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, y64, ca,
                                rhs, x64, ctl, RESET_STAGE | RESET_CALL);
           hipLaunchKernelGGL(k_fill_pattern, dim3(nb), dim3(256), 0, h->stream, (long)h->N, 0.23, 0.017, x64);
           if (hipGetLastError() != hipSuccess) { rc = MPRK_EDEVICE; break; }
@@ -2036,12 +2066,12 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return set_error(MPRK_EDEVICE, "autotune launch failed");
-  h->ln_vec = make_launch_nit(ngv, best.nv);
-  h->ln_row = make_launch_nit(ngr, best.nr);
-  h->ln_vec_red = make_launch_nit(ngv, best.nvr);
-  h->ln_row_red = make_launch_nit(ngr, best.nrr);
-  h->ln_lp = make_launch_nit(ngl, best.nl);
-  h->ln_lp_red = make_launch_nit(ngl, best.nlr);
+  h->ln_vec = make_launch_nit(h->N, h->vec, best.nv);
+  h->ln_row = make_launch_nit(h->N, 1, best.nr);
+  h->ln_vec_red = make_launch_nit(h->N, h->vec, best.nvr);
+  h->ln_row_red = make_launch_nit(h->N, 1, best.nrr);
+  h->ln_lp = make_launch_nit(h->N, h->vec_lp, best.nl);
+  h->ln_lp_red = make_launch_nit(h->N, h->vec_lp, best.nlr);
   // the timing residuals may have counted stages as missed; they are no step's stages
   if (h->rebase_missed()) return set_error(MPRK_EDEVICE, "autotune: counter read failed");
   {

@@ -13,8 +13,8 @@
 namespace mprk {
 
 int set_error(int code, const std::string& msg);
-Launch make_launch(long ng);
-Launch make_launch_nit(long ng, int nit);
+Launch make_launch(long n, int vec);
+Launch make_launch_nit(long n, int vec, int nit);
 Coef<double> operator_coef(const mprk_grid& g, const mprk_operator& op);
 Coef<double> stage_coef(const Coef<double>& K, double sigma);
 long csr_count(const Geo& geo, const Coef<double>& K, double* maxabs);
@@ -35,8 +35,11 @@ struct mprk_handle {
   hipStream_t stream = nullptr;
   mprk::Geo geo{};
   int N = 0;
-  int vec = 1;      // values per group of the FP64 kernels (4 when nx % 4 == 0)
-  int vec_lp = 1;   // values per group of the LP kernels (8 for FP16 storage when nx % 8 == 0)
+  // values per group of the FP64 kernels (4) and of the LP kernels (8 for FP16 storage unless
+  // nx % 8 == 4, else 4), and whether those groups are flat (the width does not divide nx)
+  int vec = 4, vec_lp = 4;
+  int flat = 0, flat_lp = 0;
+  int vec_ad = 1;   // rows per lane of the adaptive block-Jacobi layout (8, 4, or 1 if flat)
   mprk::Coef<double> Kc{};
   std::unique_ptr<mprk::Engine> eng;
   int lp_bytes = 8;
@@ -71,15 +74,17 @@ struct mprk_handle {
   size_t o_rhs = 0, o_y = 0, o_res = 0, o_k = 0, o_keps = 0, o_scr = 0;
   size_t o_r = 0, o_z = 0, o_p0 = 0, o_p1 = 0, o_q = 0, o_x = 0, o_V = 0, o_Zb = 0;
   size_t vstride = 0;
+  size_t kstride = 0;  // bytes between the stage slope vectors
   // block-Jacobi inverse sets, one per distinct sigma
   struct BJSet {
     int mode = 0;          // 0 per-block (row-major), 1 distinct table + index, 2 one shared
-                           // inverse, 3 per-block with rows interleaved for lanes of vec_lp rows,
+                           // inverse, 5 a table indexed by the block's place in its x-row, 6
+                           // that table with one slot, 3 per-block with rows interleaved for lanes of vec_lp rows,
                            // 4 as 3 with a storage type per chunk of 64 lane groups
     int nslot = 0;         // inverses stored
-    bool table() const { return mode == 1 || mode == 2; }  // slots hold distinct inverses
+    bool table() const { return mode == 1 || mode == 2 || mode == 5 || mode == 6; }  // slots hold distinct inverses
     size_t o_inv = 0, o_reps = 0, o_idx = 0, o_tag = 0, o_aoff = 0;
-    std::vector<int> reps; // representative block of each slot (modes 1, 2)
+    std::vector<int> reps; // representative block of each slot (modes 1, 2, 5, 6)
     std::vector<int> idx;  // slot of each block (mode 1)
     std::vector<int> tag;  // mode 4: storage type of each chunk (0 FP8 E4M3, 1 FP16, 2 FP32, 3 FP64)
     std::vector<long long> aoff;  // mode 4: byte offset of each chunk in the inverse area
