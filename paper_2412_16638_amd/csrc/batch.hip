@@ -46,7 +46,8 @@ struct BProb {
   double dt;
   double *u, *rhs, *y, *res, *k; // FP64; k holds s vectors of stride N
   void *r, *z, *p0, *p1, *q, *x; // LP vectors
-  void* dinv;                    // block-Jacobi inverses (LP)
+  void* dinv;                    // block-Jacobi inverses (LP): slots of distinct blocks
+  int bjmode;                    // their layout (modes 0, 5, 6 of device.hpp)
   double* part;                  // 2 * BND * nwg partials
   BCtl* ctl;
   int wg0, nwg, chunk;           // workgroup range and rows per workgroup (multiple of 64)
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
   const double sigma = P.sigma;
   const double sqrtN = sqrt((double)N);
   double* kout = P.k + (size_t)stage * N;
-  const BJ<S> dinv{(const S*)P.dinv, nullptr, 0};
+  const BJ<S> dinv{(const S*)P.dinv, nullptr, P.bjmode, nullptr, nullptr, P.geo.nx, N, P.geo.dx, 1};
   S* r = (S*)P.r;
   S* z = BS > 0 ? (S*)P.z : (S*)P.r;
   S* q = (S*)P.q;
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
       C rv[1], zv[1];
       rv[0] = valid ? rnd<S, C>((C)(P.res[row] * inv)) : C(0);
       if constexpr (BS > 0) {
-        bj_apply_lane<C, S, 1, BS>(dinv, row, valid, rv, zv);
+        bj_apply_lane<C, S, 1, BS, 2, 1>(dinv, row, valid, rv, zv);
         zv[0] = rnd<S, C>(zv[0]);
       } else {
         zv[0] = rv[0];
@@ -369,20 +370,20 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
           xo[k] = (C)x[row[k]];
           ro[k] = (C)r[row[k]];
           qo[k] = (C)q[row[k]];
-          if constexpr (BS > 0) bj_load<S, 1, BS>(dinv, row[k], val[k], R[k]);
+          if constexpr (BS > 0) bj_load<S, 1, BS, 2>(dinv, row[k], val[k], R[k]);
         }
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
           C rv[1], zv[1];
-          const C xv = its == 0 ? alpha * pv[k] : xo[k] + alpha * pv[k];
-          rv[0] = val[k] ? rnd<S, C>(ro[k] - alpha * qo[k]) : C(0);
+          const C xv = rnd2<S, C>(its == 0 ? alpha * pv[k] : xo[k] + alpha * pv[k]);
+          rv[0] = val[k] ? rnd_fma<S, C>(-alpha, qo[k], ro[k]) : C(0);
           if (val[k]) {
             x[row[k]] = (S)xv;
             if constexpr (BS > 0) r[row[k]] = (S)rv[0];
             else store_shared(r + row[k], (S)rv[0]);  // z aliases r
           }
           if constexpr (BS > 0) {
-            bj_mul<C, S, 1, BS>(R[k], val[k], rv, zv);
+            bj_mul<C, S, 1, BS, 2, 1>(dinv, row[k], R[k], val[k], rv, zv);
             zv[0] = rnd<S, C>(zv[0]);
             if (val[k]) store_shared(z + row[k], (S)zv[0]);
           } else {
@@ -461,7 +462,8 @@ struct mprk_batch {
   int bs = 0;
   std::vector<size_t> off_r, off_dinv, off_part, off_k, off_rhs;
   std::vector<int> N, nwg, chunk;
-  size_t o_probs = 0, o_map = 0, o_ctl = 0, o_flag = 0, ws_bytes = 0;
+  std::vector<int> bjmode;    // per problem: layout of the block-Jacobi inverses (0, 5, 6)
+  size_t o_probs = 0, o_map = 0, o_ctl = 0, o_flag = 0, o_reps = 0, ws_bytes = 0;
   size_t lp_vec_bytes_total = 0;
   int G = 0;
   char* ws = nullptr;
@@ -655,6 +657,7 @@ static int batch_layout(mprk_batch* b) {
   b->off_k.resize(b->count);
   b->off_r.resize(b->count);
   b->off_dinv.resize(b->count);
+  b->bjmode.resize(b->count);
   b->off_part.resize(b->count);
   for (int p = 0; p < b->count; ++p) {
     const size_t N = (size_t)b->N[p];
@@ -662,7 +665,12 @@ static int batch_layout(mprk_batch* b) {
     b->off_k[p] = take((size_t)s * N * 8);
     const size_t vlp = (N * b->lp_bytes + 255) & ~(size_t)255;
     b->off_r[p] = take(6 * vlp);              // r, z, p0, p1, q, x
-    b->off_dinv[p] = b->bs ? take(((N + b->bs - 1) / b->bs) * (size_t)b->bs * b->bs * b->lp_bytes) : 0;
+    // the table of distinct blocks (device.hpp, modes 5 and 6); every block for x-rows no longer
+    // than a block
+    const int nx = b->probs[p].grid.nx, bs = b->bs;
+    b->bjmode[p] = !bs || nx % bs == 0 ? 6 : nx > bs ? 5 : 0;
+    const size_t nslot = !bs ? 0 : b->bjmode[p] == 6 ? 1 : b->bjmode[p] == 5 ? (size_t)bs + 1 : (N + bs - 1) / bs;
+    b->off_dinv[p] = bs ? take(nslot * bs * bs * b->lp_bytes) : 0;
     // partials for the largest group the problem can get (one workgroup per 64 rows), so that
     // the autotuner may change the schedule after binding
     b->off_part[p] = take(2 * BND * (size_t)std::max(1, (b->N[p] + 63) / 64) * 8);
@@ -671,6 +679,7 @@ static int batch_layout(mprk_batch* b) {
   b->o_map = take(sizeof(int) * (size_t)std::max(b->G, b->max_capacity));
   b->o_ctl = take(sizeof(BCtl) * b->count);
   b->o_flag = take(256);
+  b->o_reps = b->bs ? take(sizeof(int) * (size_t)b->count * (b->bs + 1)) : 0;
   b->ws_bytes = off;
   return MPRK_OK;
 }
@@ -809,6 +818,7 @@ static void batch_problems(mprk_batch* b, std::vector<BProb>& hp, std::vector<in
     P.q = lp + 4 * vlp;
     P.x = lp + 5 * vlp;
     P.dinv = b->bs ? (void*)(b->ws + b->off_dinv[p]) : nullptr;
+    P.bjmode = b->bjmode[p];
     P.part = (double*)(b->ws + b->off_part[p]);
     P.ctl = (BCtl*)(b->ws + b->o_ctl) + p;
     P.wg0 = wg;
@@ -875,13 +885,24 @@ extern "C" int32_t mprk_batch_bind(mprk_batch* b, double* const* u_dev, void* wo
                   : b->prec.storage == MPRK_FP32 ? make_engine_fp32() : make_engine_fp16();
     std::unique_ptr<Engine> guard(eng);
     fail = (int*)(b->ws + b->o_flag);
+    std::vector<int> reps((size_t)b->count * (b->bs + 1), 0), r;
+    for (int p = 0; p < b->count; ++p) {
+      if (b->bjmode[p] == 0) continue;
+      bj_table_reps(hp[p].geo, b->bs, b->bjmode[p], r);
+      std::copy(r.begin(), r.end(), reps.begin() + (size_t)p * (b->bs + 1));
+    }
+    int* dreps = (int*)(b->ws + b->o_reps);
+    BHIP(hipMemcpyAsync(dreps, reps.data(), reps.size() * sizeof(int), hipMemcpyHostToDevice, b->stream));
+    BHIP(hipStreamSynchronize(b->stream));  // the host list goes out of scope
     for (int p = 0; p < b->count; ++p) {
       EngineCtx c{};
       c.stream = b->stream;
       c.geo = hp[p].geo;
       c.bs = b->bs;
-      const int nblk = (c.geo.N + b->bs - 1) / b->bs;
-      BHIP(eng->bj_setup_stencil(c, stage_coef(hp[p].K, hp[p].sigma), hp[p].dinv, fail, nblk, nullptr, 0));
+      const int mode = b->bjmode[p];
+      const int nslot = mode == 6 ? 1 : mode == 5 ? b->bs + 1 : (c.geo.N + b->bs - 1) / b->bs;
+      BHIP(eng->bj_setup_stencil(c, stage_coef(hp[p].K, hp[p].sigma), hp[p].dinv, fail, nslot,
+                                 mode == 0 ? nullptr : dreps + (size_t)p * (b->bs + 1), 0));
     }
   }
   int hfail = 0;

@@ -776,10 +776,11 @@ __host__ __device__ inline BJ<S> bj_typed(const BJDesc& d) {
   return BJ<S>{(const S*)d.inv, d.idx, d.mode, d.tag, d.aoff, d.nx, d.N, d.dx, d.lay};
 }
 
-// Slot of the block that starts at row b0 (modes 5 and 6).
+// Slot of the block that starts at row b0 (modes 5 and 6; mode 0 has a slot per block).
 template <int BS>
 __host__ __device__ __forceinline__ int bj_slot_of(int mode, int b0, int nx, int N, const FastDiv& dx) {
   if (mode == 6) return 0;
+  if (mode == 0) return b0 / BS;
   const int k = nx - (b0 - dx.div(b0) * nx);  // rows left in the x-row
   if (b0 + BS > N) return BS;
   return k < BS ? k : 0;

@@ -218,7 +218,7 @@ static void bj_dedup(const Geo& geo, const Coef<double>& K, double sigma, int bs
 
 // Representative block of each slot of the table of modes 5 and 6 (device.hpp); a slot that no
 // block of this grid uses gets block 0.
-static void bj_table_reps(const Geo& geo, int bs, int mode, std::vector<int>& reps) {
+void bj_table_reps(const Geo& geo, int bs, int mode, std::vector<int>& reps) {
   const int nblk = (geo.N + bs - 1) / bs;
   reps.assign(mode == 6 ? 1 : (size_t)bs + 1, 0);
   if (mode == 6) return;

@@ -17,6 +17,7 @@ Launch make_launch(long n, int vec);
 Launch make_launch_nit(long n, int vec, int nit);
 Coef<double> operator_coef(const mprk_grid& g, const mprk_operator& op);
 Coef<double> stage_coef(const Coef<double>& K, double sigma);
+void bj_table_reps(const Geo& geo, int bs, int mode, std::vector<int>& reps);
 long csr_count(const Geo& geo, const Coef<double>& K, double* maxabs);
 void assemble_csr(const Geo& geo, const Coef<double>& K, std::vector<int>& rowptr,
                   std::vector<int>& col, std::vector<double>& val);
