@@ -44,7 +44,8 @@ struct BProb {
   Coef<double> K;                // FP64 operator
   double sigma;                  // dt * a_ii (single distinct diagonal)
   double dt;
-  double *u, *rhs, *y, *res, *k; // FP64; k holds s vectors of stride N
+  double *u, *rhs, *y, *res, *k; // FP64 (padded to whole groups, but for u); k holds s vectors
+  size_t kstride;                // of this stride
   void *r, *z, *p0, *p1, *q, *x; // LP vectors
   void* dinv;                    // block-Jacobi inverses (LP): slots of distinct blocks
   int bjmode;                    // their layout (modes 0, 5, 6 of device.hpp)
@@ -86,6 +87,34 @@ __device__ __forceinline__ void store_shared(T* p, T v) {
                        __HIP_MEMORY_SCOPE_AGENT);
   } else {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// The group at element e of a workgroup's chunk, which starts at `base` (uniform over the wave) and
+// holds `chunk` elements: device-scope stores of 16 bytes where a group has them (8-byte atomic
+// stores would each write half of every 16 bytes through to memory).
+template <typename S, typename C, int VEC>
+__device__ __forceinline__ void store_shared_group(S* base, int e, int chunk, const C (&o)[VEC]) {
+  constexpr int B = sizeof(S) * VEC;
+  Vec<S, VEC> t;
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) t.v[v] = (S)o[v];
+  if constexpr (B % 16 == 0) {
+    typedef unsigned quad __attribute__((ext_vector_type(4)));
+    constexpr int SC1 = 16;  // cache policy: device scope
+    quad w[B / 16];
+    __builtin_memcpy(w, &t, B);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, chunk * (int)sizeof(S), 0x00020000);
+#pragma unroll
+    for (int i = 0; i < B / 16; ++i)
+      __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, e * (int)sizeof(S) + 16 * i, 0, SC1);
+  } else if constexpr (B == 8) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(base + e),
+                       __builtin_bit_cast(unsigned long long, t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) store_shared(base + e + v, (S)o[v]);
   }
 }
 
@@ -186,77 +215,102 @@ __device__ void group_reduce(const double (&v)[ND], int nd, const BProb& P, int 
   parity ^= 1;
 }
 
-// one FP64 stencil row of K
-__device__ __forceinline__ double k64_row(const Geo& geo, const Coef<double>& K,
-                                          const double* __restrict__ y, int r, double& yc) {
-  In1<double, double, 1> f{y};
-  double c[1], o[1];
-  stencil_group<double, 1>(geo, K, r, f, c, o);
-  yc = c[0];
-  return o[0];
-}
-
-// Rows it0 .. it0+RU-1 of this thread in [r0, r1) (nit rows per thread); a row past the end is
-// replaced by r0 (a valid row) and flagged invalid.  RU rows are handled together by a thread
-// in the CG phases, their loads issued together (RU = 1, 2 or 4, picked by the autotuner).
-template <int RU>
-__device__ __forceinline__ void rows_of(int r0, int r1, int nit, int it0, int (&row)[RU],
-                                        bool (&val)[RU]) {
-#pragma unroll
-  for (int k = 0; k < RU; ++k) {
-    const int rr = r0 + (it0 + k) * TPB + (int)threadIdx.x;
-    val[k] = it0 + k < nit && rr < r1;
-    row[k] = val[k] ? rr : r0;
-  }
-}
-
-// Minimum waves per SIMD the compiler must allow (register budget) for each row unroll.
-template <typename S, int RU>
+// Minimum waves per SIMD the compiler must allow (register budget) for each group width.  Groups
+// of 4 get room to keep a whole stencil group's loads in flight (at 96 registers the compiler
+// waits for them one by one: 64 FP32 heat problems 34 ms a step against 29 with 168); the
+// narrower ones keep the co-residency that schedules of many workgroups need.
+template <typename S, int VEC>
 constexpr int kb_min_waves() {
-  return sizeof(S) == 8 ? (RU == 1 ? 4 : RU == 2 ? 3 : 2) : (RU == 1 ? 6 : RU == 2 ? 5 : 3);
+  return VEC == 4 ? 3 : sizeof(S) == 8 ? (VEC == 1 ? 4 : 3) : 5;
 }
 
-template <typename S, typename C, int BS, int RU>
-__global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a, int stage) {
+// Every vector phase of the stage works on flat groups of VEC consecutive unknowns per thread
+// (stencil_group, FL = 1), whose products are added in FP64 one by one, so results do not depend
+// on VEC.  The library's vectors are padded to whole groups and hold zero past the end.
+// A CG iteration moves 44 bytes per unknown in FP32 (16 in the direction, 28 in the update), and
+// the 64-problem mix (20.5 M unknowns, 1.7 G unknown-iterations a step) does not fit the Infinity
+// Cache: 15 ms a step at a copy's rate.  Measured 41.7 ms with one value per lane, 26.9 ms with
+// groups of 4: what is left is the two group reductions of an iteration and the latency of a
+// workgroup's few dozen groups between them.
+template <typename S, typename C, int BS, int VEC>
+__global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs a, int stage) {
   const int pid = a.wg2prob[blockIdx.x];
-  const BProb P = a.probs[pid];
+  BProb P = a.probs[pid];
+  {
+    // the vectors' addresses through the constant address space: the compiler then knows them for
+    // global memory (flat loads would also occupy, and wait for, the LDS path)
+    typedef const __attribute__((address_space(4))) BProb* cprob;
+    const cprob c = (cprob)(unsigned long long)(a.probs + pid);
+    P.u = c->u;
+    P.rhs = c->rhs;
+    P.y = c->y;
+    P.res = c->res;
+    P.k = c->k;
+    P.r = c->r;
+    P.z = c->z;
+    P.p0 = c->p0;
+    P.p1 = c->p1;
+    P.q = c->q;
+    P.x = c->x;
+    P.dinv = c->dinv;
+    P.part = c->part;
+    P.ctl = c->ctl;
+  }
   BCtl* ctl = P.ctl;
   const int wl = blockIdx.x - P.wg0;
   const int N = P.geo.N;
   const int r0 = wl * P.chunk;
   const int r1 = min(N, r0 + P.chunk);
-  const int nit = (P.chunk + TPB - 1) / TPB;
+  const int nit = (P.chunk + TPB * VEC - 1) / (TPB * VEC);
   int parity = 0;
   const double sigma = P.sigma;
   const double sqrtN = sqrt((double)N);
-  double* kout = P.k + (size_t)stage * N;
+  const size_t ks = P.kstride;
+  double* kout = P.k + (size_t)stage * ks;
   const BJ<S> dinv{(const S*)P.dinv, nullptr, P.bjmode, nullptr, nullptr, P.geo.nx, N, P.geo.dx, 1};
   S* r = (S*)P.r;
   S* z = BS > 0 ? (S*)P.z : (S*)P.r;
   S* q = (S*)P.q;
   S* x = (S*)P.x;
   const Coef<C> M = coef_cast<C>(coef_stage(P.K, sigma));
+  const int e0 = r0 + (int)threadIdx.x * VEC;  // this thread's first group; then every TPB-th
 
   if (stage == 0 && wl == 0 && threadIdx.x == 0)
     __hip_atomic_store(&ctl->step_nonfinite, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // ---- stage right-hand side: rhs = u + dt sum_{j<stage} a_ij k_j ; y = its start value ----
   for (int it = 0; it < nit; ++it) {
-    const int row = r0 + it * TPB + threadIdx.x;
-    if (row >= r1) break;
-    double acc = P.u[row];
-    for (int j = 0; j < stage; ++j) acc += P.dt * a.A[stage][j] * P.k[(size_t)j * N + row];
-    P.rhs[row] = acc;
-    double yv = acc;
-    if (stage == 0 && a.feval) {
-      double uc;
-      const double fu = k64_row(P.geo, P.K, P.u, row, uc);
-      yv += sigma * a.y0f * fu;
-      if (a.fkeep) P.k[(size_t)(a.s - 1) * N + row] = fu;
-    } else if (stage > 0) {
-      yv += sigma * a.ya[stage] * P.k[(size_t)(stage - 1) * N + row];
-      if (a.yb[stage] != 0.0) yv += sigma * a.yb[stage] * P.k[(size_t)a.yj[stage] * N + row];
+    const int e = e0 + it * TPB * VEC;
+    if (e >= r1) break;
+    double acc[VEC], t[VEC];
+    loadg<double, double, VEC, 1>(P.u, e, N, acc);
+    for (int j = 0; j < stage; ++j) {
+      loadv<double, double, VEC>(P.k + (size_t)j * ks + e, t);
+      const double c = P.dt * a.A[stage][j];
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
     }
-    store_shared(P.y + row, yv);
+    storev<double, double, VEC>(P.rhs + e, acc);
+    if (stage == 0 && a.feval) {
+      const In1<double, double, VEC> f{P.u};
+      double uc[VEC];
+      stencil_group<double, VEC, 1>(P.geo, P.K, e, f, uc, t);
+      const double c = sigma * a.y0f;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
+      if (a.fkeep) storev<double, double, VEC>(P.k + (size_t)(a.s - 1) * ks + e, t);
+    } else if (stage > 0) {
+      loadv<double, double, VEC>(P.k + (size_t)(stage - 1) * ks + e, t);
+      const double c = sigma * a.ya[stage];
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
+      if (a.yb[stage] != 0.0) {
+        loadv<double, double, VEC>(P.k + (size_t)a.yj[stage] * ks + e, t);
+        const double c2 = sigma * a.yb[stage];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] += c2 * t[v];
+      }
+    }
+    store_shared_group<double, double, VEC>(P.y + r0, e - r0, P.chunk, acc);
   }
   group_barrier(ctl, P.nwg);
 
@@ -268,17 +322,21 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
     // ---- FP64 stage residual: k = K y ; res = rhs - y + sigma k ----
     double acc[BND] = {0.0, 0.0, 0.0, 0.0};
     for (int it = 0; it < nit; ++it) {
-      const int row = r0 + it * TPB + threadIdx.x;
-      if (row >= r1) break;
-      double yc;
-      const double ky = k64_row(P.geo, P.K, P.y, row, yc);
-      const double b = P.rhs[row];
-      const double rr = b - yc + sigma * ky;
-      kout[row] = ky;
-      P.res[row] = rr;
-      acc[0] += rr * rr;
-      acc[1] += b * b;
-      acc[2] += (__builtin_isfinite(rr) && __builtin_isfinite(ky)) ? 0.0 : 1.0;
+      const int e = e0 + it * TPB * VEC;
+      if (e >= r1) break;
+      double yc[VEC], ky[VEC], b[VEC], rr[VEC];
+      loadv<double, double, VEC>(P.rhs + e, b);
+      const In1<double, double, VEC> f{P.y};
+      stencil_group<double, VEC, 1>(P.geo, P.K, e, f, yc, ky);
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        rr[v] = b[v] - yc[v] + sigma * ky[v];
+        acc[0] += rr[v] * rr[v];
+        acc[1] += b[v] * b[v];
+        acc[2] += (__builtin_isfinite(rr[v]) && __builtin_isfinite(ky[v])) ? 0.0 : 1.0;
+      }
+      storev<double, double, VEC>(kout + e, ky);
+      storev<double, double, VEC>(P.res + e, rr);
     }
     double t[BND];
     group_reduce<BND>(acc, 3, P, wl, parity, t);
@@ -295,25 +353,33 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
     // ---- CG begin: r = LP(res / scale), z = BJ(r) ----
     double acc2[BND] = {0.0, 0.0, 0.0, 0.0};
     for (int it = 0; it < nit; ++it) {
-      const int row = r0 + it * TPB + threadIdx.x;
-      const bool valid = row < r1;
-      C rv[1], zv[1];
-      rv[0] = valid ? rnd<S, C>((C)(P.res[row] * inv)) : C(0);
+      const int e = e0 + it * TPB * VEC;
+      const bool valid = e < r1;
+      double rs[VEC];
+      C rv[VEC], zv[VEC];
+      loadv<double, double, VEC>(P.res + (valid ? e : r0), rs);
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) rv[v] = valid ? rnd<S, C>((C)(rs[v] * inv)) : C(0);
       if constexpr (BS > 0) {
-        bj_apply_lane<C, S, 1, BS, 2, 1>(dinv, row, valid, rv, zv);
-        zv[0] = rnd<S, C>(zv[0]);
+        bj_apply_lane<C, S, VEC, BS, 2, 1>(dinv, e, valid, rv, zv);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) zv[v] = rnd<S, C>(zv[v]);
       } else {
-        zv[0] = rv[0];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) zv[v] = rv[v];
       }
       if (valid) {
         if constexpr (BS > 0) {
-          r[row] = (S)rv[0];
-          store_shared(z + row, (S)zv[0]);
+          storev<S, C, VEC>(r + e, rv);
+          store_shared_group<S, C, VEC>(z + r0, e - r0, P.chunk, zv);
         } else {
-          store_shared(r + row, (S)rv[0]);  // z aliases r
+          store_shared_group<S, C, VEC>(r + r0, e - r0, P.chunk, rv);  // z aliases r
         }
-        acc2[0] += (double)(rv[0] * zv[0]);
-        acc2[1] += (double)(rv[0] * rv[0]);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+          acc2[0] += (double)(rv[v] * zv[v]);
+          acc2[1] += (double)(rv[v] * rv[v]);
+        }
       }
     }
     group_reduce<BND>(acc2, 2, P, wl, parity, t);
@@ -329,24 +395,20 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
       // ---- C1: p_new = z + beta p_old ; q = M p_new ; (p, q) ----
       const S* pold = (its & 1) ? (const S*)P.p1 : (const S*)P.p0;
       S* pnew = (its & 1) ? (S*)P.p0 : (S*)P.p1;
-      const InAxpy<C, S, 1> f{z, its > 0 ? pold : z, its > 0 ? (C)beta : C(0)};
+      const InAxpy<C, S, VEC> f{z, its > 0 ? pold : z, its > 0 ? (C)beta : C(0)};
       double acc3[BND] = {0.0, 0.0, 0.0, 0.0};
-      for (int it0 = 0; it0 < nit; it0 += RU) {
-        int row[RU];
-        bool val[RU];
-        rows_of<RU>(r0, r1, nit, it0, row, val);
-        C pc[RU][1], w[RU][1];
+      for (int it = 0; it < nit; ++it) {
+        const int e = e0 + it * TPB * VEC;
+        if (e >= r1) break;
+        C pc[VEC], w[VEC];
+        stencil_group<C, VEC, 1, S>(P.geo, M, e, f, pc, w);
 #pragma unroll
-        for (int k = 0; k < RU; ++k) stencil_group<C, 1, 0, S>(P.geo, M, row[k], f, pc[k], w[k]);
-#pragma unroll
-        for (int k = 0; k < RU; ++k) {
-          if (val[k]) {
-            w[k][0] = rnd<S, C>(w[k][0]);
-            store_shared(pnew + row[k], (S)pc[k][0]);
-            q[row[k]] = (S)w[k][0];
-            acc3[0] += (double)(pc[k][0] * w[k][0]);
-          }
+        for (int v = 0; v < VEC; ++v) {
+          w[v] = rnd<S, C>(w[v]);
+          acc3[0] += (double)(pc[v] * w[v]);
         }
+        store_shared_group<S, C, VEC>(pnew + r0, e - r0, P.chunk, pc);
+        storev<S, C, VEC>(q + e, w);
       }
       group_reduce<BND>(acc3, 1, P, wl, parity, t);
       const double pq = t[0];
@@ -357,42 +419,41 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
       const C alpha = (C)(rz / pq);
       // ---- C2: x += alpha p ; r -= alpha q ; z = BJ(r) ; (r, z), (r, r) ----
       double acc4[BND] = {0.0, 0.0, 0.0, 0.0};
-      for (int it0 = 0; it0 < nit; it0 += RU) {
-        int row[RU];
-        bool val[RU];
-        rows_of<RU>(r0, r1, nit, it0, row, val);
-        // every load of the RU rows first (x is read but unused in the first iteration)
-        C pv[RU], xo[RU], ro[RU], qo[RU];
-        BJRows<S, 1, BS == 0 ? 1 : BS> R[RU];
+      for (int it = 0; it < nit; ++it) {
+        const int e = e0 + it * TPB * VEC;
+        const bool valid = e < r1;
+        const int el = valid ? e : r0;  // an invalid lane reads a valid group and discards it
+        // all loads first (x is read but unused in the first iteration)
+        C pv[VEC], xv[VEC], rv[VEC], qv[VEC], zv[VEC];
+        loadv<C, S, VEC>(pnew + el, pv);
+        loadv<C, S, VEC>(q + el, qv);
+        loadv<C, S, VEC>(r + el, rv);
+        loadv<C, S, VEC>(x + el, xv);
+        BJRows<S, VEC, BS == 0 ? 1 : BS> R;
+        if constexpr (BS > 0) bj_load<S, VEC, BS, 2>(dinv, e, valid, R);
 #pragma unroll
-        for (int k = 0; k < RU; ++k) {
-          pv[k] = (C)pnew[row[k]];
-          xo[k] = (C)x[row[k]];
-          ro[k] = (C)r[row[k]];
-          qo[k] = (C)q[row[k]];
-          if constexpr (BS > 0) bj_load<S, 1, BS, 2>(dinv, row[k], val[k], R[k]);
+        for (int v = 0; v < VEC; ++v) {
+          xv[v] = rnd2<S, C>(its == 0 ? alpha * pv[v] : xv[v] + alpha * pv[v]);
+          rv[v] = valid && e + v < N ? rnd_fma<S, C>(-alpha, qv[v], rv[v]) : C(0);
+        }
+        if (valid) {
+          storev<S, C, VEC>(x + e, xv);
+          if constexpr (BS > 0) storev<S, C, VEC>(r + e, rv);
+          else store_shared_group<S, C, VEC>(r + r0, e - r0, P.chunk, rv);  // z aliases r
+        }
+        if constexpr (BS > 0) {
+          bj_mul<C, S, VEC, BS, 2, 1>(dinv, e, R, valid, rv, zv);
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) zv[v] = rnd<S, C>(zv[v]);
+          if (valid) store_shared_group<S, C, VEC>(z + r0, e - r0, P.chunk, zv);
+        } else {
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) zv[v] = rv[v];
         }
 #pragma unroll
-        for (int k = 0; k < RU; ++k) {
-          C rv[1], zv[1];
-          const C xv = rnd2<S, C>(its == 0 ? alpha * pv[k] : xo[k] + alpha * pv[k]);
-          rv[0] = val[k] ? rnd_fma<S, C>(-alpha, qo[k], ro[k]) : C(0);
-          if (val[k]) {
-            x[row[k]] = (S)xv;
-            if constexpr (BS > 0) r[row[k]] = (S)rv[0];
-            else store_shared(r + row[k], (S)rv[0]);  // z aliases r
-          }
-          if constexpr (BS > 0) {
-            bj_mul<C, S, 1, BS, 2, 1>(dinv, row[k], R[k], val[k], rv, zv);
-            zv[0] = rnd<S, C>(zv[0]);
-            if (val[k]) store_shared(z + row[k], (S)zv[0]);
-          } else {
-            zv[0] = rv[0];
-          }
-          if (val[k]) {
-            acc4[0] += (double)(rv[0] * zv[0]);
-            acc4[1] += (double)(rv[0] * rv[0]);
-          }
+        for (int v = 0; v < VEC; ++v) {
+          acc4[0] += (double)(rv[v] * zv[v]);
+          acc4[1] += (double)(rv[v] * rv[v]);
         }
       }
       group_reduce<BND>(acc4, 2, P, wl, parity, t);
@@ -408,9 +469,16 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
     // ---- promote: y += scale * x ----
     if (its > 0) {
       for (int it = 0; it < nit; ++it) {
-        const int row = r0 + it * TPB + threadIdx.x;
-        if (row >= r1) break;
-        store_shared(P.y + row, P.y[row] + scale * (double)(C)x[row]);
+        const int e = e0 + it * TPB * VEC;
+        if (e >= r1) break;
+        double yv[VEC];
+        C xv[VEC];
+        loadv<double, double, VEC>(P.y + e, yv);
+        loadv<C, S, VEC>(x + e, xv);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v)
+          yv[v] = e + v < N ? yv[v] + scale * (double)xv[v] : 0.0;
+        store_shared_group<double, double, VEC>(P.y + r0, e - r0, P.chunk, yv);
       }
     }
     ++passes;
@@ -432,11 +500,17 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, RU>())) void kb_stage(BArgs a
     const int bad = __hip_atomic_load(&ctl->step_nonfinite, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!bad) {
       for (int it = 0; it < nit; ++it) {
-        const int row = r0 + it * TPB + threadIdx.x;
-        if (row >= r1) break;
-        double acc = P.u[row];
-        for (int i = 0; i < a.s; ++i) acc += P.dt * a.b[i] * P.k[(size_t)i * N + row];
-        P.u[row] = acc;
+        const int e = e0 + it * TPB * VEC;
+        if (e >= r1) break;
+        double acc[VEC], t[VEC];
+        loadg<double, double, VEC, 1>(P.u, e, N, acc);
+        for (int i = 0; i < a.s; ++i) {
+          loadv<double, double, VEC>(P.k + (size_t)i * ks + e, t);
+          const double c = P.dt * a.b[i];
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
+        }
+        storeg<double, double, VEC, 1>(P.u, e, N, acc);
       }
     }
     if (wl == 0 && threadIdx.x == 0) {
@@ -479,8 +553,9 @@ struct mprk_batch {
   // of the last step; used by plan_groups while use_measured is set
   std::vector<double> measured_w;
   bool use_measured = false;
-  int ru = 2;                 // rows a thread handles together in the CG phases (1, 2, 4)
+  int ru = 4;                 // consecutive rows a thread handles together (1, 2, 4)
   int capacity = 0;           // co-resident workgroups of the device for the kernel in use
+  int cus = 0;                // compute units of the device
   int max_capacity = 0;       // largest capacity over the kernel variants (sizes the map)
   ~mprk_batch() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
@@ -615,8 +690,11 @@ static int plan_groups(mprk_batch* b, int capacity) {
   b->nwg.assign(b->count, 1);
   b->chunk.assign(b->count, 0);
   b->N.assign(b->count, 0);
-  int avail = capacity - b->count;
-  if (avail < 0) return set_error(MPRK_EUNSUPPORTED, "more problems than co-resident workgroups");
+  // two workgroups per CU at most, unless the caller's schedule or the problem count asks for more:
+  // the 64-problem mix takes 27.2 ms a step with 484 workgroups, 29.0 with 739, 33.6 with 233
+  // (fewer groups of unknowns per barrier, more partials to add)
+  int avail = std::min(capacity, std::max(b->count, 2 * b->cus)) - b->count;
+  if (capacity < b->count) return set_error(MPRK_EUNSUPPORTED, "more problems than co-resident workgroups");
   int fixed_total = 0;
   for (int p = 0; p < b->count; ++p) {
     const mprk_grid& g = b->probs[p].grid;
@@ -645,6 +723,9 @@ static int plan_groups(mprk_batch* b, int capacity) {
   return MPRK_OK;
 }
 
+// FP64 vectors are padded to a multiple of 32 values (whole groups, 256-byte aligned).
+static size_t batch_pad(size_t n) { return (n + 31) & ~(size_t)31; }
+
 static int batch_layout(mprk_batch* b) {
   const int s = b->tab.s;
   size_t off = 0;
@@ -661,8 +742,8 @@ static int batch_layout(mprk_batch* b) {
   b->off_part.resize(b->count);
   for (int p = 0; p < b->count; ++p) {
     const size_t N = (size_t)b->N[p];
-    b->off_rhs[p] = take(3 * N * 8);          // rhs, y, res
-    b->off_k[p] = take((size_t)s * N * 8);
+    b->off_rhs[p] = take(3 * batch_pad(N) * 8);  // rhs, y, res
+    b->off_k[p] = take((size_t)s * batch_pad(N) * 8);
     const size_t vlp = (N * b->lp_bytes + 255) & ~(size_t)255;
     b->off_r[p] = take(6 * vlp);              // r, z, p0, p1, q, x
     // the table of distinct blocks (device.hpp, modes 5 and 6); every block for x-rows no longer
@@ -694,6 +775,7 @@ static int batch_capacity(mprk_batch* b, int ru, int* cap) {
     return set_error(MPRK_EDEVICE, "occupancy query failed");
   // stay one workgroup per CU below the occupancy bound
   *cap = std::max(1, cus * std::max(1, per - 1));
+  b->cus = cus;
   return MPRK_OK;
 }
 
@@ -726,7 +808,21 @@ extern "C" int64_t mprk_batch_workspace_bytes(const mprk_batch* cb) {
       mx = std::max(mx, cap);
     }
     b->max_capacity = mx;
+    // the widest groups whose kernel can hold the schedule asked for
+    long need = b->count;
+    if (!b->fixed_wg.empty()) {
+      need = 0;
+      for (int p = 0; p < b->count; ++p) {
+        const mprk_grid& g = b->probs[p].grid;
+        const int maxwg = std::max(1, (g.nx * g.ny * g.nz + 63) / 64);
+        need += std::min(maxwg, std::max(1, b->fixed_wg[p]));
+      }
+    }
     int rc = batch_capacity(b, b->ru, &cap);
+    for (; !rc && cap < need && b->ru > 1;) {
+      b->ru /= 2;
+      rc = batch_capacity(b, b->ru, &cap);
+    }
     if (rc) return rc;
     b->capacity = cap;
     rc = plan_groups(b, cap);
@@ -806,8 +902,9 @@ static void batch_problems(mprk_batch* b, std::vector<BProb>& hp, std::vector<in
     P.dt = q.dt;
     P.u = b->u[p];
     P.rhs = (double*)(b->ws + b->off_rhs[p]);
-    P.y = P.rhs + N;
-    P.res = P.y + N;
+    P.kstride = batch_pad((size_t)N);
+    P.y = P.rhs + P.kstride;
+    P.res = P.y + P.kstride;
     P.k = (double*)(b->ws + b->off_k[p]);
     const size_t vlp = ((size_t)N * b->lp_bytes + 255) & ~(size_t)255;
     char* lp = b->ws + b->off_r[p];
@@ -971,6 +1068,10 @@ extern "C" int32_t mprk_batch_autotune(mprk_batch* b, double* exponent_out, int3
   int best_ru = b->ru;
   float best_ms = 1e30f;
   for (int ru : {1, 2, 4}) {
+    int cap = 0;
+    rc = batch_capacity(b, ru, &cap);
+    if (rc) break;
+    if (cap < b->count) continue;  // this width cannot hold every problem at once
     b->ru = ru;
     float ms = 0.f;
     rc = trial(&ms);
