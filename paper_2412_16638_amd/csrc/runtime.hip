@@ -739,7 +739,10 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
                                         (size_t)B.nslot * bs})
                             : (size_t)B.nslot * bs;
     B.o_inv = take(rows * bs * lp_bytes);
-    if (B.table()) B.o_reps = take((size_t)B.nslot * 4);
+    // (the slots' rows go behind the table where that footprint has room)
+    const size_t used = align256((size_t)B.nslot * bs * bs * lp_bytes);
+    if (B.table())
+      B.o_reps = used + (size_t)B.nslot * 4 <= rows * bs * lp_bytes ? B.o_inv + used : take((size_t)B.nslot * 4);
     if (B.mode == 1) B.o_idx = take((size_t)nblk * 4);
   }
   if (o.format == MPRK_FMT_CSR) {
