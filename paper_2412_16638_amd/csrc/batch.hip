@@ -20,19 +20,15 @@
 #include <vector>
 
 #include "../../include/mprk.h"
+#include "group.hpp"
 #include "runtime_internal.hpp"
 
 using namespace mprk;
 
 namespace mprk {
 
-constexpr int BND = 4;            // values per group reduction
-constexpr long BAR_SPIN_LIMIT = 1L << 22;
-
 struct BCtl {
-  unsigned int bar_count;
-  unsigned int bar_gen;
-  int error;                     // a group barrier timed out
+  GroupBar bar;
   int step_nonfinite;
   long long good_steps, bad_steps, life_iters, life_passes;
   int iters[MAXS], passes[MAXS], converged[MAXS], nonfinite[MAXS];
@@ -49,7 +45,7 @@ struct BProb {
   void *r, *z, *p0, *p1, *q, *x; // LP vectors
   void* dinv;                    // block-Jacobi inverses (LP): slots of distinct blocks
   int bjmode;                    // their layout (modes 0, 5, 6 of device.hpp)
-  double* part;                  // 2 * BND * nwg partials
+  double* part;                  // 2 * GRP_ND * nwg partials
   BCtl* ctl;
   int wg0, nwg, chunk;           // workgroup range and rows per workgroup (multiple of 64)
 };
@@ -70,150 +66,6 @@ struct BArgs {
   int yj[MAXS];
   int feval, fkeep;
 };
-
-// Data one workgroup writes and another reads inside a stage launch (the stencil inputs y, p
-// and z, and the reduction partials) are written with device-scope stores, which are coherent
-// across the XCDs once complete.  A barrier therefore needs no L2 writeback: every wave waits
-// for its own stores to complete before its workgroup arrives, and after the barrier every wave
-// invalidates its non-coherent cached lines (agent-scope acquire) before reading other
-// workgroups' rows.  Data a thread writes and only the same thread reads back (its own rows of
-// r, x, q, res, rhs, k) stay plain stores.
-template <typename T>
-__device__ __forceinline__ void store_shared(T* p, T v) {
-  if constexpr (sizeof(T) == 2) {
-    unsigned short b;
-    __builtin_memcpy(&b, &v, 2);
-    __hip_atomic_store(reinterpret_cast<unsigned short*>(p), b, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-// The group at element e of a workgroup's chunk, which starts at `base` (uniform over the wave) and
-// holds `chunk` elements: device-scope stores of 16 bytes where a group has them (8-byte atomic
-// stores would each write half of every 16 bytes through to memory).
-template <typename S, typename C, int VEC>
-__device__ __forceinline__ void store_shared_group(S* base, int e, int chunk, const C (&o)[VEC]) {
-  constexpr int B = sizeof(S) * VEC;
-  Vec<S, VEC> t;
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) t.v[v] = (S)o[v];
-  if constexpr (B % 16 == 0) {
-    typedef unsigned quad __attribute__((ext_vector_type(4)));
-    constexpr int SC1 = 16;  // cache policy: device scope
-    quad w[B / 16];
-    __builtin_memcpy(w, &t, B);
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(base, 0, chunk * (int)sizeof(S), 0x00020000);
-#pragma unroll
-    for (int i = 0; i < B / 16; ++i)
-      __builtin_amdgcn_raw_buffer_store_b128(w[i], rs, e * (int)sizeof(S) + 16 * i, 0, SC1);
-  } else if constexpr (B == 8) {
-    __hip_atomic_store(reinterpret_cast<unsigned long long*>(base + e),
-                       __builtin_bit_cast(unsigned long long, t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) store_shared(base + e + v, (S)o[v]);
-  }
-}
-
-__device__ __forceinline__ void wait_own_stores() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-__device__ __forceinline__ unsigned int load_u32_dev(const unsigned int* p) {
-  return __hip_atomic_load(const_cast<unsigned int*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Barrier over the nwg workgroups of one problem (generation counter; bounded spin).
-__device__ bool group_barrier(BCtl* c, int nwg) {
-  if (nwg > 1) wait_own_stores();
-  __syncthreads();
-  if (nwg > 1) {
-    if (threadIdx.x == 0) {
-      // the generation is read (and the read completed) before this arrival is counted
-      const unsigned gen = load_u32_dev(&c->bar_gen);
-      wait_own_stores();
-      const unsigned arrived = __hip_atomic_fetch_add(&c->bar_count, 1u, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT);
-      if (arrived == (unsigned)nwg - 1u) {
-        __hip_atomic_store(&c->bar_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_own_stores();  // the reset is visible before the next generation opens
-        __hip_atomic_fetch_add(&c->bar_gen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        long spins = 0;
-        while (load_u32_dev(&c->bar_gen) == gen) {
-          __builtin_amdgcn_s_sleep(2);
-          if (++spins > BAR_SPIN_LIMIT) {
-            __hip_atomic_store(&c->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  }
-  return true;
-}
-
-// Group reduction of nd values; every workgroup of the group returns the same totals.  Each
-// workgroup publishes its partials (device-scope stores), passes the group barrier, then sums
-// all the group's partials itself in workgroup order (every thread a strided slice, fixed
-// shuffle tree and wave order), so all workgroups take identical decisions without a second
-// round trip.  Partials are double-buffered by `parity` (a fast workgroup may publish the next
-// reduction's partials while a slow one still reads these).
-template <int ND>
-__device__ void group_reduce(const double (&v)[ND], int nd, const BProb& P, int wl, int& parity,
-                             double (&out)[ND]) {
-  __shared__ double wsum[NWAVE][BND];
-  __shared__ double tot[BND];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int d = 0; d < ND; ++d) {
-    if (d < nd) {
-      const double s = wave_sum(v[d]);
-      if (lane == 0) wsum[wave][d] = s;
-    }
-  }
-  __syncthreads();
-  const int nwg = P.nwg;
-  double* part = P.part + (size_t)parity * BND * nwg;
-  if (threadIdx.x < nd) {
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < NWAVE; ++w) s += wsum[w][threadIdx.x];
-    if (nwg > 1) store_dev(part + (size_t)threadIdx.x * nwg + wl, s);
-    else tot[threadIdx.x] = s;
-  }
-  if (nwg > 1) {
-    group_barrier(P.ctl, nwg);
-    __shared__ double wt[NWAVE][BND];
-#pragma unroll 1
-    for (int d = 0; d < nd; ++d) {
-      double s = 0.0;
-#pragma unroll 1
-      for (int w = threadIdx.x; w < nwg; w += TPB) s += load_dev(part + (size_t)d * nwg + w);
-      s = wave_sum(s);
-      if (lane == 0) wt[wave][d] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < nd) {
-      double s = 0.0;
-#pragma unroll
-      for (int w = 0; w < NWAVE; ++w) s += wt[w][threadIdx.x];
-      tot[threadIdx.x] = s;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int d = 0; d < ND; ++d) out[d] = d < nd ? tot[d] : 0.0;
-  __syncthreads();
-  parity ^= 1;
-}
 
 // Minimum waves per SIMD the compiler must allow (register budget) for each group width.  Groups
 // of 4 get room to keep a whole stencil group's loads in flight (at 96 registers the compiler
@@ -312,7 +164,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
     }
     store_shared_group<double, double, VEC>(P.y + r0, e - r0, P.chunk, acc);
   }
-  group_barrier(ctl, P.nwg);
+  group_barrier(&ctl->bar, P.nwg);
 
   int passes = 0, total_iters = 0, converged = 0, nonfinite = 0;
   bool last_conv = false;  // the last LP solve stopped on its own tolerance
@@ -320,7 +172,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
   const int P_max = a.paper_mode ? 1 : a.max_passes;
   for (int pass = 0;; ++pass) {
     // ---- FP64 stage residual: k = K y ; res = rhs - y + sigma k ----
-    double acc[BND] = {0.0, 0.0, 0.0, 0.0};
+    double acc[3] = {0.0, 0.0, 0.0};
     for (int it = 0; it < nit; ++it) {
       const int e = e0 + it * TPB * VEC;
       if (e >= r1) break;
@@ -338,8 +190,8 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
       storev<double, double, VEC>(kout + e, ky);
       storev<double, double, VEC>(P.res + e, rr);
     }
-    double t[BND];
-    group_reduce<BND>(acc, 3, P, wl, parity, t);
+    double t[3];
+    group_reduce<3, TPB>(acc, P.part, &ctl->bar, P.nwg, wl, parity, t);
     const double rn = sqrt(t[0]), bn = sqrt(t[1]);
     rel = bn > 0.0 ? rn / bn : rn;
     if (t[2] != 0.0 || !__builtin_isfinite(rn)) {
@@ -351,7 +203,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
     const double scale = rn / sqrtN;
     const double inv = 1.0 / scale;
     // ---- CG begin: r = LP(res / scale), z = BJ(r) ----
-    double acc2[BND] = {0.0, 0.0, 0.0, 0.0};
+    double acc2[2] = {0.0, 0.0};
     for (int it = 0; it < nit; ++it) {
       const int e = e0 + it * TPB * VEC;
       const bool valid = e < r1;
@@ -382,12 +234,13 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
         }
       }
     }
-    group_reduce<BND>(acc2, 2, P, wl, parity, t);
-    double rz = t[0];
+    double t2[2];
+    group_reduce<2, TPB>(acc2, P.part, &ctl->bar, P.nwg, wl, parity, t2);
+    double rz = t2[0];
     // (the outer target as for a single problem: the 2-norm of the LP residual, unit = scale)
-    const double tol = fmax(fmax(a.rtol * sqrt(t[1]), a.atol / scale),
+    const double tol = fmax(fmax(a.rtol * sqrt(t2[1]), a.atol / scale),
                             a.outer_stop ? 0.5 * a.outer_tol * bn / scale : 0.0);
-    bool inner_done = sqrt(t[1]) <= tol;
+    bool inner_done = sqrt(t2[1]) <= tol;
     bool inner_conv = inner_done;
     double beta = 0.0;
     int its = 0;
@@ -396,7 +249,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
       const S* pold = (its & 1) ? (const S*)P.p1 : (const S*)P.p0;
       S* pnew = (its & 1) ? (S*)P.p0 : (S*)P.p1;
       const InAxpy<C, S, VEC> f{z, its > 0 ? pold : z, its > 0 ? (C)beta : C(0)};
-      double acc3[BND] = {0.0, 0.0, 0.0, 0.0};
+      double acc3[1] = {0.0};
       for (int it = 0; it < nit; ++it) {
         const int e = e0 + it * TPB * VEC;
         if (e >= r1) break;
@@ -410,15 +263,16 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
         store_shared_group<S, C, VEC>(pnew + r0, e - r0, P.chunk, pc);
         storev<S, C, VEC>(q + e, w);
       }
-      group_reduce<BND>(acc3, 1, P, wl, parity, t);
-      const double pq = t[0];
+      double pq1[1];
+      group_reduce<1, TPB>(acc3, P.part, &ctl->bar, P.nwg, wl, parity, pq1);
+      const double pq = pq1[0];
       if (!(pq > 0.0) || !__builtin_isfinite(pq)) {
         inner_conv = false;
         break;
       }
       const C alpha = (C)(rz / pq);
       // ---- C2: x += alpha p ; r -= alpha q ; z = BJ(r) ; (r, z), (r, r) ----
-      double acc4[BND] = {0.0, 0.0, 0.0, 0.0};
+      double acc4[2] = {0.0, 0.0};
       for (int it = 0; it < nit; ++it) {
         const int e = e0 + it * TPB * VEC;
         const bool valid = e < r1;
@@ -456,13 +310,13 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
           acc4[1] += (double)(rv[v] * rv[v]);
         }
       }
-      group_reduce<BND>(acc4, 2, P, wl, parity, t);
+      group_reduce<2, TPB>(acc4, P.part, &ctl->bar, P.nwg, wl, parity, t2);
       ++its;
-      const double rz_new = t[0];
+      const double rz_new = t2[0];
       beta = rz_new / rz;
       rz = rz_new;
-      inner_conv = __builtin_isfinite(t[1]) && sqrt(t[1]) <= tol;
-      inner_done = !__builtin_isfinite(t[1]) || inner_conv;
+      inner_conv = __builtin_isfinite(t2[1]) && sqrt(t2[1]) <= tol;
+      inner_done = !__builtin_isfinite(t2[1]) || inner_conv;
     }
     last_conv = inner_conv;
     total_iters += its;
@@ -482,7 +336,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
       }
     }
     ++passes;
-    group_barrier(ctl, P.nwg);
+    group_barrier(&ctl->bar, P.nwg);
   }
   if (wl == 0 && threadIdx.x == 0) {
     ctl->iters[stage] = total_iters;
@@ -496,7 +350,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
   }
   if (stage == a.s - 1) {
     // ---- step combination u += dt sum_i b_i k_i (skipped after a non-finite residual) ----
-    group_barrier(ctl, P.nwg);
+    group_barrier(&ctl->bar, P.nwg);
     const int bad = __hip_atomic_load(&ctl->step_nonfinite, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!bad) {
       for (int it = 0; it < nit; ++it) {
@@ -754,7 +608,7 @@ static int batch_layout(mprk_batch* b) {
     b->off_dinv[p] = bs ? take(nslot * bs * bs * b->lp_bytes) : 0;
     // partials for the largest group the problem can get (one workgroup per 64 rows), so that
     // the autotuner may change the schedule after binding
-    b->off_part[p] = take(2 * BND * (size_t)std::max(1, (b->N[p] + 63) / 64) * 8);
+    b->off_part[p] = take(2 * GRP_ND * (size_t)std::max(1, (b->N[p] + 63) / 64) * 8);
   }
   b->o_probs = take(sizeof(BProb) * b->count);
   b->o_map = take(sizeof(int) * (size_t)std::max(b->G, b->max_capacity));
@@ -1174,7 +1028,7 @@ extern "C" int32_t mprk_batch_stats_sync(mprk_batch* b, int32_t idx, mprk_stats*
   out->total_iters = c.life_iters;
   out->total_passes = c.life_passes;
   out->nonfinite = c.bad_steps > 0;
-  if (c.error) return set_error(MPRK_EDEVICE, "a batched group barrier timed out (workgroups not co-resident)");
+  if (c.bar.error) return set_error(MPRK_EDEVICE, "a batched group barrier timed out (workgroups not co-resident)");
   return MPRK_OK;
 }
 

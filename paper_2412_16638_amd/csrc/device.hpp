@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace mprk {
@@ -114,6 +115,16 @@ enum KClass {
 
 // Device control record of one solve context (one per problem).  The first 64 bytes
 // are the head the host polls.
+// What a slot of a group exchange (group.hpp) reads as until it is published: a NaN no sum gives.
+constexpr unsigned long long GRP_EMPTY = 0x7ff4c0de00000001ULL;
+
+struct GroupBar {  // barrier of a group of workgroups (group.hpp)
+  unsigned int count;
+  unsigned int gen;
+  int error;  // a barrier timed out
+  int pad;
+};
+
 struct Ctl {
   // ---- head polled by the host (64 bytes) ----
   int outer_done;     // stage finished (converged, pass limit, or non-finite)
@@ -134,6 +145,9 @@ struct Ctl {
   long long life_passes;  // LP solves since bind
   long long missed;       // stages finished without reaching their tolerance, since bind
   long long held_steps;   // strict: steps not combined because a stage missed its tolerance
+  GroupBar bar;           // one-launch stages
+  long long srec[MAXSTG][8];  // each stage's final head (one-launch stages, replayed steps)
+  // ---- (the host reads everything above in one copy at the end of a call) ----
   int inner_conv;         // the current LP solve stopped because it reached its tolerance
   int step_held;          // strict: a stage of the current step missed (gates the combination)
   int halt;               // strict: a stage missed in this call; its remaining stages are skipped
@@ -155,7 +169,6 @@ struct Ctl {
   int pass_iters[MAXPASS];           // Krylov iterations of each pass of the current stage
   long long worked[KC_COUNT];        // launches per kernel class that did work (profiling)
   long long units[KC_COUNT];         // basis vectors touched (GMRES kernels), else launches
-  long long srec[MAXSTG][8];         // steps replayed from a graph: each stage's final head
 };
 
 __device__ __forceinline__ void count_work(Ctl* ctl, int kc, int units = 1) {
@@ -173,6 +186,17 @@ struct CtlHead {
   int bad_steps, step_nonfinite;
 };
 static_assert(sizeof(CtlHead) == 64, "poll head must be 64 bytes");
+
+// What the host reads at the end of a call: the prefix of Ctl.
+struct CtlTop {
+  CtlHead head;
+  long long life_iters, life_passes, missed, held_steps;
+  GroupBar bar;
+  CtlHead srec[MAXSTG];
+};
+static_assert(offsetof(Ctl, srec) == offsetof(CtlTop, srec) &&
+                  offsetof(Ctl, held_steps) == offsetof(CtlTop, held_steps),
+              "prefix of the control record");
 
 
 // k_stage_rhs reset flags: a new stage, a new step, a new library call (clears the halt)

@@ -7,6 +7,7 @@
 
 #include <vector>
 
+#include "cgstage.hpp"
 #include "kernels.hpp"
 #include "fdm.hpp"
 
@@ -133,6 +134,11 @@ class Engine {
   virtual hipError_t cg_iter(const EngineCtx& c, const SolveCfg& cfg, const Coef<double>& Mc,
                              const BJDesc& dinv, int it) = 0;
   virtual hipError_t cg_finish(const EngineCtx& c) = 0;
+  // a whole stage in one launch (FP64 and FP32 storage with their own arithmetic; table or no
+  // block-Jacobi); slot: the stage's record
+  virtual hipError_t cg_stage(const EngineCtx& c, const SolveCfg& cfg, const StagePlan& pl,
+                              const Coef<double>& K, const double* rhs, double* y, double* kout,
+                              const FTerms& fx, const BJDesc& dinv, int slot) = 0;
   // z = P^-1 r with the fast-diagonalisation preconditioner for stage shift sigma (S storage)
   virtual hipError_t fdm_apply(const EngineCtx& c, double sigma, const void* r, void* z) = 0;
   // GMRES
@@ -462,6 +468,33 @@ class EngineT final : public Engine {
                      c.ln_vec, c.y, (const S*)c.x, c.ctl);
     });
     return hipGetLastError();
+  }
+
+  hipError_t cg_stage(const EngineCtx& c, const SolveCfg& cfg, const StagePlan& pl,
+                      const Coef<double>& K, const double* rhs, double* y, double* kout,
+                      const FTerms& fx, const BJDesc& dinv, int slot) override {
+    if constexpr (!std::is_same<S, C>::value) {
+      return hipErrorInvalidValue;
+    } else {
+      const unsigned lds = (pl.slab + 4) * sizeof(double);
+      auto go = [&](auto bs) {
+        constexpr int BS = decltype(bs)::value;
+        auto launch = [&](auto kern) {
+          hipLaunchKernelGGL(kern, dim3(pl.nwg), dim3(TPB), lds, c.stream, pl, c.geo, K, y, rhs, kout, (S*)c.z,
+                             bj_typed<S>(dinv), fx, cfg, c.ctl, c.red.p1, slot);
+        };
+        if (pl.nwg == 1) launch(k_cg_stage<S, C, BS, false>);
+        else launch(k_cg_stage<S, C, BS, true>);
+      };
+      switch (c.bs) {
+        case 0: go(IC<0>{}); break;
+        case 1: go(IC<1>{}); break;
+        case 2: go(IC<2>{}); break;
+        case 4: go(IC<4>{}); break;
+        default: go(IC<8>{}); break;
+      }
+      return hipGetLastError();
+    }
   }
 
   // ---------------- GMRES ----------------

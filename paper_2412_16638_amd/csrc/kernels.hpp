@@ -45,6 +45,8 @@ struct CombArgs {
   double pc;
   const double* pv2;
   double pc2;
+  unsigned long long* empty;  // slots of the one-launch stage that follows, emptied here
+  int nempty;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -60,6 +62,8 @@ __global__ __launch_bounds__(TPB) void k_stage_rhs(Launch ln, const double* __re
                                                    CombArgs a, double* __restrict__ rhs,
                                                    double* __restrict__ y, Ctl* ctl, int reset) {
   count_work(ctl, KC_STAGE_RHS);
+  if (a.empty && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < a.nempty; i += TPB) a.empty[i] = GRP_EMPTY;
   if (reset && blockIdx.x == 0 && threadIdx.x == 0) {
     if (reset & RESET_CALL) ctl->halt = 0;
     ctl->outer_done = ctl->halt;

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
 #include <deque>
@@ -448,6 +449,7 @@ extern "C" int32_t mprk_precisions_default(int32_t storage, int32_t krylov, mprk
 // create / layout
 // ------------------------------------------------------------------------------------------
 
+
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 static int validate(const mprk_grid* g, const mprk_operator* op, const mprk_tableau* tab,
@@ -703,6 +705,7 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
     }
   }
   vstride = vlp / lp_bytes;
+  plan_one_launch(cb);
   bjsets.assign(bs ? sigmas.size() : 0, BJSet());
   for (size_t q = 0; q < bjsets.size(); ++q) {
     BJSet& B = bjsets[q];
@@ -801,6 +804,31 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   return MPRK_OK;
 }
 
+// Small CG problems on the matrix-free stencil run each stage as one launch (cgstage.hpp): faster
+// at every size it holds (a step of 8^3 FP32 131 us, 50^3 742 against 1056), so the line lies where
+// its workgroups or their LDS end.  Not FP16 storage: its per-kernel path adds the products of a group in FP32 on even grids, and the
+// two forms would round differently.
+void mprk_handle::plan_one_launch(bool cb) {
+  stage_plan = StagePlan{0, 0, 0};
+  if (prec.krylov != MPRK_CG || op.format != MPRK_FMT_STENCIL || fdm || cb ||
+      prec.storage == MPRK_FP16 || N > GRP_WGS * STAGE_PART)
+    return;
+  if (bs && (prec.bj_adapt_tol > 0.0 || !(grid.nx % bs == 0 || grid.nx > bs))) return;
+  long nwg = ((long)N + STAGE_PART - 1) / STAGE_PART;
+  const long chunk = ((N + nwg - 1) / nwg + 63) / 64 * 64;
+  nwg = (N + chunk - 1) / chunk;
+  const long slab = nwg == 1 ? N : std::min((long)N, chunk + 2L * grid.nx * grid.ny);
+  if (slab > STAGE_SLAB_MAX) return;
+  stage_plan = StagePlan{(int)nwg, (int)chunk, (int)slab};
+}
+
+// The exchange slots the stage's launch expects empty.
+void mprk_handle::stage_slots(CombArgs& a) const {
+  if (!one_launch() || stage_plan.nwg == 1) return;
+  a.empty = (unsigned long long*)(ws + o_part);
+  a.nempty = 3 * GRP_ND * stage_plan.nwg;
+}
+
 // Pinned poll slots and events: made on the first bind (the first call that needs a device).
 int mprk_handle::make_device_resources() {
   if (events_made) return MPRK_OK;
@@ -809,6 +837,7 @@ int mprk_handle::make_device_resources() {
     std::memset(slots, 0, sizeof(CtlHead) * (NSLOT + MPRK_MAX_STAGES + 1));
   }
   for (int i = 0; i < NSLOT; ++i) HIPCHK(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
+  HIPCHK(hipHostMalloc((void**)&top, sizeof(CtlTop)));
   HIPCHK(hipHostMalloc((void**)&rec_iters, sizeof(int) * MAXPASS * (MPRK_MAX_STAGES + 1)));
   for (int i = 0; i <= MPRK_MAX_STAGES; ++i)
     HIPCHK(hipEventCreateWithFlags(&rec_ev[i], hipEventDisableTiming));
@@ -823,6 +852,7 @@ mprk_handle::~mprk_handle() {
     for (int i = 0; i <= MPRK_MAX_STAGES; ++i) (void)hipEventDestroy(rec_ev[i]);
   }
   if (slots) (void)hipHostFree(slots);
+  if (top) (void)hipHostFree(top);
   if (rec_iters) (void)hipHostFree(rec_iters);
   graph_drop();
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
@@ -1183,6 +1213,12 @@ int mprk_handle::launch_residual(const SolveCfg& cfg, const double* rhs, double*
 int mprk_handle::run_solve(int si, int slot, const double* rhs, double* y, double* kout,
                            const FTerms& fx) {
   if (capturing) return run_solve_graph(si, slot, rhs, y, kout, fx);
+  if (one_launch()) {
+    EngineCtx c = ctx();
+    HIPCHK(eng->cg_stage(c, cfgs[si], stage_plan, Kc, rhs, y, kout, fx, bj_desc(si), slot));
+    // (the step graph captures what the last steered solves needed)
+    return graph_on && slot < MAXSTG ? stage_record(slot) : MPRK_OK;
+  }
   int rc = update_hist(slot);
   if (rc) return rc;
   const StageHist H = hist[slot];
@@ -1275,6 +1311,10 @@ int mprk_handle::run_solve_graph(int si, int slot, const double* rhs, double* y,
   const BJDesc dinv = bj_desc(si);
   const Coef<double> Mc = stage_coef(Kc, cfg.sigma);
   const bool cg = prec.krylov == MPRK_CG;
+  if (one_launch()) {  // the same launch as the steered path's, with the replay's pass limit
+    HIPCHK(eng->cg_stage(c, cfg, stage_plan, Kc, rhs, y, kout, fx, dinv, slot));
+    return MPRK_OK;
+  }
   int most = 1;
   for (int p = 0; p < H.passes; ++p) most = std::max(most, H.iters[p]);
   for (int pass = 0; pass <= P; ++pass) {
@@ -1319,6 +1359,7 @@ int mprk_handle::enqueue_step(bool first_of_call) {
   for (int i = 0; i < s; ++i) {
     CombArgs a{};
     a.nv = 0;
+    stage_slots(a);
     for (int j = 0; j < i; ++j) {
       const double ah = tab.a_hi[i * s + j], al = tab.a_lo[i * s + j];
       if (!implicit_[j]) {  // f^eps = f for an explicit stage
@@ -1544,34 +1585,29 @@ int mprk_handle::graph_steps(int nsteps, int* done) {
   hipLaunchKernelGGL(k_release_halt, dim3(1), dim3(64), 0, stream, ctl);
   HIPCHK(hipGetLastError());
   for (int n = 0; n < nsteps; ++n) HIPCHK(hipGraphLaunch(gexec, stream));
-  // the stage records of the last replayed step, for the statistics
-  HIPCHK(hipMemcpyAsync((void*)&slots[NSLOT], ctl->srec, sizeof(CtlHead) * nstages,
-                        hipMemcpyDeviceToHost, stream));
   // counters: completed steps; a miss inside the graph is not reported (its steps are re-run)
   int rc = sync_counters();
+  // the stage records of the last replayed step, for the statistics
+  if (rc == MPRK_OK || rc == MPRK_ENONFINITE) keep_records();
   *done = last_good;
   graph_steps_last = last_good;
   return rc;
 }
 
-int mprk_handle::rebase_missed() {
-  Ctl* ctl = (Ctl*)(ws + o_ctl);
-  long long m = 0;
-  HIPCHK(hipMemcpyAsync(&m, &ctl->missed, sizeof(m), hipMemcpyDeviceToHost, stream));
+// The control record's prefix (head, counters, stage records) in one copy to pinned memory; waits
+// for the stream.
+int mprk_handle::read_top() {
+  HIPCHK(hipMemcpyAsync(top, ws + o_ctl, sizeof(CtlTop), hipMemcpyDeviceToHost, stream));
   HIPCHK(hipStreamSynchronize(stream));
-  missed_base = m;
+  std::atomic_thread_fence(std::memory_order_acquire);
+  if (top->bar.error)
+    return set_error(MPRK_EDEVICE, "a one-launch stage timed out (workgroups not co-resident)");
   return MPRK_OK;
 }
 
 int mprk_handle::sync_counters() {
-  Ctl* ctl = (Ctl*)(ws + o_ctl);
-  long long lf[4];  // life_iters, life_passes, missed, held_steps (adjacent in Ctl)
-  static_assert(offsetof(Ctl, held_steps) == offsetof(Ctl, life_iters) + 3 * sizeof(long long),
-                "counters read together");
-  CtlHead hd;
-  HIPCHK(hipMemcpyAsync(&hd, ctl, sizeof(CtlHead), hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipMemcpyAsync(lf, &ctl->life_iters, sizeof(lf), hipMemcpyDeviceToHost, stream));
-  HIPCHK(hipStreamSynchronize(stream));
+  if (int rc = read_top()) return rc;
+  const CtlHead& hd = top->head;
   const long long good = hd.good_steps - good_base;
   const int bad = hd.bad_steps - bad_base;
   last_good = (int)good;
@@ -1579,21 +1615,60 @@ int mprk_handle::sync_counters() {
   bad_base = hd.bad_steps;
   step_count += good;
   t_now += dt * (double)good;
-  life_iters = lf[0];
-  life_passes = lf[1];
-  last_missed = (int)(lf[2] - missed_base);
-  missed_base = lf[2];
-  last_held = (int)(lf[3] - held_base);
-  held_base = lf[3];
+  life_iters = top->life_iters;
+  life_passes = top->life_passes;
+  last_missed = (int)(top->missed - missed_base);
+  missed_base = top->missed;
+  last_held = (int)(top->held_steps - held_base);
+  held_base = top->held_steps;
   last_nonfinite = bad > 0;
   return bad > 0 ? MPRK_ENONFINITE : MPRK_OK;
 }
+
+// The stage records in the prefix just read, for the statistics (replayed steps and one-launch
+// stages leave them on the device).
+void mprk_handle::keep_records() {
+  std::memcpy((void*)&slots[NSLOT], top->srec, sizeof(CtlHead) * nstages);
+}
+
+// Workgroups of one-launch stages in flight in this process: their workgroups wait for each other
+// inside a launch, so all launched at a time have to fit the device together, also beside a batched
+// step (two workgroups per CU).  A call waits here until the others in flight leave it room.
+namespace {
+struct StageGate {
+  std::mutex mu;
+  std::condition_variable cv;
+  int used = 0;
+};
+StageGate g_gate;
+constexpr int GATE_WGS = 192;
+
+struct GateHold {
+  int n;
+  explicit GateHold(const mprk_handle* h)
+      : n(h->one_launch() && h->stage_plan.nwg > 1 ? h->stage_plan.nwg : 0) {
+    if (!n) return;
+    std::unique_lock<std::mutex> lk(g_gate.mu);
+    g_gate.cv.wait(lk, [&] { return g_gate.used + n <= GATE_WGS; });
+    g_gate.used += n;
+  }
+  ~GateHold() {
+    if (!n) return;
+    {
+      std::lock_guard<std::mutex> lk(g_gate.mu);
+      g_gate.used -= n;
+    }
+    g_gate.cv.notify_all();
+  }
+};
+}  // namespace
 
 extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) {
   if (!h) return set_error(MPRK_EINVAL, "NULL handle");
   if (!h->bound) return set_error(MPRK_ESTATE, "mprk_step before mprk_bind");
   if (int rcw = h->check_ws()) return rcw;
   if (nsteps < 0) return set_error(MPRK_EINVAL, "nsteps must be >= 0");
+  const GateHold gate(h);
   int done = 0;
   h->graph_steps_last = 0;
   if (h->graph_on && nsteps > 0) {
@@ -1611,6 +1686,8 @@ extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) 
     if (rc) return rc;
   }
   int rc = h->sync_counters();
+  if (rc && rc != MPRK_ENONFINITE) return rc;
+  if (h->one_launch() && done < nsteps) h->keep_records();
   if (stats) h->fill_stats(stats);
   if (rc == MPRK_ENONFINITE) return set_error(rc, "non-finite residual: u left at the last completed step");
   // every stage of every step of this call counts, not only the last step's record; the
@@ -1628,9 +1705,11 @@ extern "C" int32_t mprk_solve(mprk_handle* h, int32_t stage, const double* rhs_d
   if (int rcw = h->check_ws()) return rcw;
   if (stage < 0 || stage >= h->nstages || !h->implicit_[stage])
     return set_error(MPRK_EINVAL, "stage must be an implicit stage of the tableau");
+  const GateHold gate(h);
   Ctl* ctl = (Ctl*)(h->ws + h->o_ctl);
   CombArgs a{};
   a.nv = 0;
+  h->stage_slots(a);
   // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
   double* rhs = (double*)(h->ws + h->o_rhs);
   if (!h->flat)
@@ -1643,12 +1722,9 @@ extern "C" int32_t mprk_solve(mprk_handle* h, int32_t stage, const double* rhs_d
   int rc = h->run_solve(h->sig_idx[stage], MPRK_MAX_STAGES, rhs, x_dev, (double*)(h->ws + h->o_scr),
                         FTerms{});
   if (rc) return rc;
-  CtlHead hd;
-  HIPCHK(hipMemcpyAsync(&hd, ctl, sizeof(CtlHead), hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipStreamSynchronize(h->stream));
-  // a missed solve here is reported in info, not by the next mprk_step
-  rc = h->rebase_missed();
-  if (rc) return rc;
+  if ((rc = h->read_top())) return rc;
+  const CtlHead& hd = h->top->head;
+  h->missed_base = h->top->missed;  // a missed solve here is reported in info, not by the next mprk_step
   if (info) {
     info->iters = hd.total_iters;
     info->passes = hd.passes;
@@ -2076,7 +2152,8 @@ extern "C" int32_t mprk_autotune(mprk_handle* h, int32_t* nit_vec, int32_t* nit_
   h->ln_lp = make_launch_nit(h->N, h->vec_lp, best.nl);
   h->ln_lp_red = make_launch_nit(h->N, h->vec_lp, best.nlr);
   // the timing residuals may have counted stages as missed; they are no step's stages
-  if (h->rebase_missed()) return set_error(MPRK_EDEVICE, "autotune: counter read failed");
+  if (h->read_top()) return set_error(MPRK_EDEVICE, "autotune: counter read failed");
+  h->missed_base = h->top->missed;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tuned[key] = best;

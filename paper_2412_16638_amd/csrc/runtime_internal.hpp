@@ -67,6 +67,9 @@ struct mprk_handle {
   mprk::Launch ln_lp{}, ln_lp_red{};        // LP kernels (groups of vec_lp)
   int pstride = 8;   // level-1 partials per reduced value (max blocks of a reducing launch)
   int pstride2 = 1;  // level-2 partials per reduced value
+  // small CG problems: a whole stage in one launch (nwg = 0: the per-kernel path)
+  mprk::StagePlan stage_plan{};
+  bool one_launch() const { return stage_plan.nwg > 0 && !prof_on; }
   int bs = 0;
   int nblk = 0;
   long nnz = 0;
@@ -115,6 +118,7 @@ struct mprk_handle {
   unsigned long long static_gen = 0;  // that scratch's bind count when this handle bound it
   // host steering
   mprk::CtlHead* slots = nullptr;   // pinned: NSLOT poll slots + one record per stage
+  mprk::CtlTop* top = nullptr;      // pinned: the control record's prefix at the end of a call
   hipEvent_t ev[mprk::NSLOT] = {};
   bool slot_used[mprk::NSLOT] = {};
   bool events_made = false;
@@ -168,6 +172,8 @@ struct mprk_handle {
   int init(const mprk_grid& g, const mprk_operator& o, const mprk_tableau& t,
            const mprk_precisions& p, double dt_, hipStream_t s);
   ~mprk_handle();
+  void plan_one_launch(bool cb);
+  void stage_slots(mprk::CombArgs& a) const;
   int make_device_resources();
   mprk::EngineCtx ctx() const;
   int poll_enqueue(int* slot);
@@ -188,8 +194,9 @@ struct mprk_handle {
   void graph_drop();
   int graph_steps(int nsteps, int* done);
   int enqueue_step(bool first_of_call);
+  int read_top();
+  void keep_records();
   int sync_counters();
-  int rebase_missed();
   int check_ws() const;
   void set_residual_tiles(int lz);
   void set_gm_form(int f, int lz);
