@@ -345,27 +345,31 @@ class EngineT final : public Engine {
     const FdmGeo g{n, fdm_ldq(n), 0, nc, ld, bstride, nb, 0, skip};
     fdm_go<C, C>(c, g, 0, Q, in, out, sc);
   }
-  // complex-basis contractions: V4 dispatch as for the real ones
-  template <typename TI, typename TO, int INR, int OUTR, int V4>
-  void fdm_launch_cx(const EngineCtx& c, FdmGeo g, int row, const FdmCx& cx, const TI* in_r,
-                     const TI* in_i, TO* out_r, TO* out_i, const FdmScale& sc) {
-    const int n = g.n;
-    const int ro = g.ro ? g.ro : n;
-    g.tiles = row ? ((g.nr + 63) / 64) * ((ro + FT_N - 1) / FT_N)
-                  : ((n + 63) / 64) * ((g.nc + FT_N - 1) / FT_N) * g.nb;
+  // complex-basis contractions: along x (real in, or real out) and folded along y and z; V4 dispatch
+  // as for the real ones
+  template <typename TI, typename TO, int OUTR>
+  void fdm_row_cx(const EngineCtx& c, FdmGeo g, const FdmCx& cx, const TI* in_r, const TI* in_i, TO* out_r,
+                  TO* out_i) {
+    const int ro = g.ro ? g.ro : g.n;
+    g.tiles = ((g.nr + 63) / 64) * ((ro + FT_N - 1) / FT_N);
     const dim3 grid((unsigned)((g.tiles + 7) & ~7));
-    if (row)
-      hipLaunchKernelGGL((k_fdm_contract_cx<TI, TO, C, 1, V4, INR, OUTR>), grid, dim3(256), 0,
-                         c.stream, g, cx, in_r, in_i, out_r, out_i, sc, c.ctl);
+    if (c.geo.nx % 4 == 0)
+      hipLaunchKernelGGL((k_fdm_contract_cx<TI, TO, C, 1, OUTR>), grid, dim3(256), 0, c.stream, g, cx, in_r,
+                         in_i, out_r, out_i, c.ctl);
     else
-      hipLaunchKernelGGL((k_fdm_contract_cx<TI, TO, C, 0, V4, INR, OUTR>), grid, dim3(256), 0,
-                         c.stream, g, cx, in_r, in_i, out_r, out_i, sc, c.ctl);
+      hipLaunchKernelGGL((k_fdm_contract_cx<TI, TO, C, 0, OUTR>), grid, dim3(256), 0, c.stream, g, cx, in_r,
+                         in_i, out_r, out_i, c.ctl);
   }
-  template <typename TI, typename TO, int INR, int OUTR>
-  void fdm_go_cx(const EngineCtx& c, const FdmGeo& g, int row, const FdmCx& cx, const TI* in_r,
-                 const TI* in_i, TO* out_r, TO* out_i, const FdmScale& sc) {
-    if (c.geo.nx % 4 == 0) fdm_launch_cx<TI, TO, INR, OUTR, 1>(c, g, row, cx, in_r, in_i, out_r, out_i, sc);
-    else fdm_launch_cx<TI, TO, INR, OUTR, 0>(c, g, row, cx, in_r, in_i, out_r, out_i, sc);
+  void fdm_col_cx(const EngineCtx& c, FdmGeo g, const FdmCx& cx, const C* in_r, const C* in_i, C* out_r,
+                  C* out_i, const FdmScale& sc) {
+    g.tiles = ((g.n / 2 + 1 + 63) / 64) * ((g.nc + FF_N - 1) / FF_N) * g.nb;
+    const dim3 grid((unsigned)((g.tiles + 7) & ~7));
+    if (c.geo.nx % 4 == 0)
+      hipLaunchKernelGGL((k_fdm_fold_cx<C, 1>), grid, dim3(256), 0, c.stream, g, cx, in_r, in_i, out_r, out_i,
+                         sc, c.ctl);
+    else
+      hipLaunchKernelGGL((k_fdm_fold_cx<C, 0>), grid, dim3(256), 0, c.stream, g, cx, in_r, in_i, out_r, out_i,
+                         sc, c.ctl);
   }
   // z = Re(conj(U) P_D^-1 U r), U the 3-D unitary DFT (axis by axis), for the circulant factors
   // of the periodic advection operators; planar complex scratch (t0, t0i), (t1, t1i).  The data
@@ -393,12 +397,12 @@ class EngineT final : public Engine {
     const FdmGeo gy{ny, fdm_ldq(ny), 0, nx, nx, (long)nx * ny, nz, 0, skip};
     const FdmGeo gz{nz, fdm_ldq(nz), 0, nx * ny, nx * ny, 0, 1, 0, skip};
     if (c.prof) c.prof->before(KC_FDM, 6);
-    fdm_go_cx<TI, C, 1, 0>(c, gx, 1, cxd(0, 1.0), in, nullptr, t0, t0i, none);
-    fdm_go_cx<C, C, 0, 0>(c, gy, 0, cxd(1, 1.0), t0, t0i, t1, t1i, none);
-    fdm_go_cx<C, C, 0, 0>(c, gz, 0, cxd(2, 1.0), t1, t1i, t0, t0i, sc);
-    fdm_go_cx<C, C, 0, 0>(c, gz, 0, cxd(2, -1.0), t0, t0i, t1, t1i, none);
-    fdm_go_cx<C, C, 0, 0>(c, gy, 0, cxd(1, -1.0), t1, t1i, t0, t0i, none);
-    fdm_go_cx<C, TO, 0, 1>(c, gx, 1, cxd(0, -1.0), t0, t0i, out, nullptr, none);
+    fdm_row_cx<TI, C, 0>(c, gx, cxd(0, 1.0), in, nullptr, t0, t0i);
+    fdm_col_cx(c, gy, cxd(1, 1.0), t0, t0i, t1, t1i, none);
+    fdm_col_cx(c, gz, cxd(2, 1.0), t1, t1i, t0, t0i, sc);
+    fdm_col_cx(c, gz, cxd(2, -1.0), t0, t0i, t1, t1i, none);
+    fdm_col_cx(c, gy, cxd(1, -1.0), t1, t1i, t0, t0i, none);
+    fdm_row_cx<C, TO, 1>(c, gx, cxd(0, -1.0), t0, t0i, out, nullptr);
     if (c.prof) c.prof->after();
   }
   template <typename TI, typename TO>
@@ -427,12 +431,12 @@ class EngineT final : public Engine {
     gy.cstride = (long)H * ny;
     const FdmGeo gz{nz, fdm_ldq(nz), 0, H * ny, H * ny, 0, 1, 0, skip};
     if (c.prof) c.prof->before(KC_FDM, 6);
-    fdm_go_cx<TI, C, 1, 0>(c, gxf, 1, cxd(0, 1.0), in, nullptr, t0, t0i, none);
-    fdm_go_cx<C, C, 0, 0>(c, gy, 0, cxd(1, 1.0), t0, t0i, t1, t1i, none);
-    fdm_go_cx<C, C, 0, 0>(c, gz, 0, cxd(2, 1.0), t1, t1i, t0, t0i, sc);
-    fdm_go_cx<C, C, 0, 0>(c, gz, 0, cxd(2, -1.0), t0, t0i, t1, t1i, none);
-    fdm_go_cx<C, C, 0, 0>(c, gy, 0, cxd(1, -1.0), t1, t1i, t0, t0i, none);
-    fdm_go_cx<C, TO, 0, 1>(c, gxb, 1, xw, t0, t0i, out, nullptr, none);
+    fdm_row_cx<TI, C, 0>(c, gxf, cxd(0, 1.0), in, nullptr, t0, t0i);
+    fdm_col_cx(c, gy, cxd(1, 1.0), t0, t0i, t1, t1i, none);
+    fdm_col_cx(c, gz, cxd(2, 1.0), t1, t1i, t0, t0i, sc);
+    fdm_col_cx(c, gz, cxd(2, -1.0), t0, t0i, t1, t1i, none);
+    fdm_col_cx(c, gy, cxd(1, -1.0), t1, t1i, t0, t0i, none);
+    fdm_row_cx<C, TO, 1>(c, gxb, xw, t0, t0i, out, nullptr);
     if (c.prof) c.prof->after();
   }
   // z = P^-1 r: T_R, T_M, T_L with the basis (its own inverse), P_D^-1, then back.  in and out
