@@ -67,6 +67,29 @@ struct BArgs {
   int feval, fkeep;
 };
 
+// A problem's description, the vectors' addresses through the constant address space: the compiler
+// then knows them for global memory (flat loads would also occupy, and wait for, the LDS path).
+__device__ __forceinline__ BProb load_problem(const BArgs& a, int pid) {
+  BProb P = a.probs[pid];
+  typedef const __attribute__((address_space(4))) BProb* cprob;
+  const cprob c = (cprob)(unsigned long long)(a.probs + pid);
+  P.u = c->u;
+  P.rhs = c->rhs;
+  P.y = c->y;
+  P.res = c->res;
+  P.k = c->k;
+  P.r = c->r;
+  P.z = c->z;
+  P.p0 = c->p0;
+  P.p1 = c->p1;
+  P.q = c->q;
+  P.x = c->x;
+  P.dinv = c->dinv;
+  P.part = c->part;
+  P.ctl = c->ctl;
+  return P;
+}
+
 // Minimum waves per SIMD the compiler must allow (register budget) for each group width.  Groups
 // of 4 get room to keep a whole stencil group's loads in flight (at 96 registers the compiler
 // waits for them one by one: 64 FP32 heat problems 34 ms a step against 29 with 168); the
@@ -87,27 +110,7 @@ constexpr int kb_min_waves() {
 template <typename S, typename C, int BS, int VEC>
 __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs a, int stage) {
   const int pid = a.wg2prob[blockIdx.x];
-  BProb P = a.probs[pid];
-  {
-    // the vectors' addresses through the constant address space: the compiler then knows them for
-    // global memory (flat loads would also occupy, and wait for, the LDS path)
-    typedef const __attribute__((address_space(4))) BProb* cprob;
-    const cprob c = (cprob)(unsigned long long)(a.probs + pid);
-    P.u = c->u;
-    P.rhs = c->rhs;
-    P.y = c->y;
-    P.res = c->res;
-    P.k = c->k;
-    P.r = c->r;
-    P.z = c->z;
-    P.p0 = c->p0;
-    P.p1 = c->p1;
-    P.q = c->q;
-    P.x = c->x;
-    P.dinv = c->dinv;
-    P.part = c->part;
-    P.ctl = c->ctl;
-  }
+  const BProb P = load_problem(a, pid);
   BCtl* ctl = P.ctl;
   const int wl = blockIdx.x - P.wg0;
   const int N = P.geo.N;
@@ -374,6 +377,273 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
   }
 }
 
+// one FP64 stencil row of K
+__device__ __forceinline__ double k64_row(const Geo& geo, const Coef<double>& K,
+                                          const double* __restrict__ y, int r, double& yc) {
+  In1<double, double, 1> f{y};
+  double c[1], o[1];
+  stencil_group<double, 1>(geo, K, r, f, c, o);
+  yc = c[0];
+  return o[0];
+}
+
+// Rows it0 .. it0+RU-1 of this thread in [r0, r1) (nit rows per thread); a row past the end is
+// replaced by r0 (a valid row) and flagged invalid.  RU rows are handled together by a thread
+// in the CG phases, their loads issued together (RU = 1, 2 or 4, picked by the autotuner).
+template <int RU>
+__device__ __forceinline__ void rows_of(int r0, int r1, int nit, int it0, int (&row)[RU],
+                                        bool (&val)[RU]) {
+#pragma unroll
+  for (int k = 0; k < RU; ++k) {
+    const int rr = r0 + (it0 + k) * TPB + (int)threadIdx.x;
+    val[k] = it0 + k < nit && rr < r1;
+    row[k] = val[k] ? rr : r0;
+  }
+}
+
+// Minimum waves per SIMD the compiler must allow (register budget) for each row unroll.
+template <int RU>
+constexpr int kb_rows_min_waves() {
+  return RU == 1 ? 6 : RU == 2 ? 5 : 3;
+}
+
+// FP16 storage: one row per lane, RU rows of a thread in flight together.  An FP16 solve decides
+// its roundings at 5e-4, so a sum added in another order may move a solution by 1e-7, within its
+// outer tolerance but not the same numbers; this form keeps the order results have had.  (On
+// groups of 4 values a batch of 22 FP16 problems up to 50^3 takes 4.4 ms a step, here 8.7.  Its
+// vectors' addresses stay generic: read as in kb_stage the compiler schedules more waits, 9.0.)
+
+template <typename S, typename C, int BS, int RU>
+__global__ __launch_bounds__(TPB, (kb_rows_min_waves<RU>())) void kb_stage_rows(BArgs a, int stage) {
+  const int pid = a.wg2prob[blockIdx.x];
+  const BProb P = a.probs[pid];
+  BCtl* ctl = P.ctl;
+  const int wl = blockIdx.x - P.wg0;
+  const int N = P.geo.N;
+  const int r0 = wl * P.chunk;
+  const int r1 = min(N, r0 + P.chunk);
+  const int nit = (P.chunk + TPB - 1) / TPB;
+  int parity = 0;
+  const double sigma = P.sigma;
+  const double sqrtN = sqrt((double)N);
+  const size_t ks = P.kstride;
+  double* kout = P.k + (size_t)stage * ks;
+  const BJ<S> dinv{(const S*)P.dinv, nullptr, P.bjmode, nullptr, nullptr, P.geo.nx, N, P.geo.dx, 1};
+  S* r = (S*)P.r;
+  S* z = BS > 0 ? (S*)P.z : (S*)P.r;
+  S* q = (S*)P.q;
+  S* x = (S*)P.x;
+  const Coef<C> M = coef_cast<C>(coef_stage(P.K, sigma));
+
+  if (stage == 0 && wl == 0 && threadIdx.x == 0)
+    __hip_atomic_store(&ctl->step_nonfinite, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // ---- stage right-hand side: rhs = u + dt sum_{j<stage} a_ij k_j ; y = its start value ----
+  for (int it = 0; it < nit; ++it) {
+    const int row = r0 + it * TPB + threadIdx.x;
+    if (row >= r1) break;
+    double acc = P.u[row];
+    for (int j = 0; j < stage; ++j) acc += P.dt * a.A[stage][j] * P.k[(size_t)j * ks + row];
+    P.rhs[row] = acc;
+    double yv = acc;
+    if (stage == 0 && a.feval) {
+      double uc;
+      const double fu = k64_row(P.geo, P.K, P.u, row, uc);
+      yv += sigma * a.y0f * fu;
+      if (a.fkeep) P.k[(size_t)(a.s - 1) * ks + row] = fu;
+    } else if (stage > 0) {
+      yv += sigma * a.ya[stage] * P.k[(size_t)(stage - 1) * ks + row];
+      if (a.yb[stage] != 0.0) yv += sigma * a.yb[stage] * P.k[(size_t)a.yj[stage] * ks + row];
+    }
+    store_shared(P.y + row, yv);
+  }
+  group_barrier(&ctl->bar, P.nwg);
+
+  int passes = 0, total_iters = 0, converged = 0, nonfinite = 0;
+  bool last_conv = false;  // the last LP solve stopped on its own tolerance
+  double rel = 0.0;
+  const int P_max = a.paper_mode ? 1 : a.max_passes;
+  for (int pass = 0;; ++pass) {
+    // ---- FP64 stage residual: k = K y ; res = rhs - y + sigma k ----
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (int it = 0; it < nit; ++it) {
+      const int row = r0 + it * TPB + threadIdx.x;
+      if (row >= r1) break;
+      double yc;
+      const double ky = k64_row(P.geo, P.K, P.y, row, yc);
+      const double b = P.rhs[row];
+      const double rr = b - yc + sigma * ky;
+      kout[row] = ky;
+      P.res[row] = rr;
+      acc[0] += rr * rr;
+      acc[1] += b * b;
+      acc[2] += (__builtin_isfinite(rr) && __builtin_isfinite(ky)) ? 0.0 : 1.0;
+    }
+    double t3[3], t[2], t1[1];
+    group_reduce<3, TPB>(acc, P.part, &ctl->bar, P.nwg, wl, parity, t3);
+    const double rn = sqrt(t3[0]), bn = sqrt(t3[1]);
+    rel = bn > 0.0 ? rn / bn : rn;
+    if (t3[2] != 0.0 || !__builtin_isfinite(rn)) {
+      nonfinite = 1;
+      break;
+    }
+    converged = a.paper_mode ? (passes >= 1 && last_conv) : (rel <= a.outer_tol);
+    if (converged || passes >= P_max || rn == 0.0) break;
+    const double scale = rn / sqrtN;
+    const double inv = 1.0 / scale;
+    // ---- CG begin: r = LP(res / scale), z = BJ(r) ----
+    double acc2[2] = {0.0, 0.0};
+    for (int it = 0; it < nit; ++it) {
+      const int row = r0 + it * TPB + threadIdx.x;
+      const bool valid = row < r1;
+      C rv[1], zv[1];
+      rv[0] = valid ? rnd<S, C>((C)(P.res[row] * inv)) : C(0);
+      if constexpr (BS > 0) {
+        bj_apply_lane<C, S, 1, BS, 2, 1>(dinv, row, valid, rv, zv);
+        zv[0] = rnd<S, C>(zv[0]);
+      } else {
+        zv[0] = rv[0];
+      }
+      if (valid) {
+        if constexpr (BS > 0) {
+          r[row] = (S)rv[0];
+          store_shared(z + row, (S)zv[0]);
+        } else {
+          store_shared(r + row, (S)rv[0]);  // z aliases r
+        }
+        acc2[0] += (double)(rv[0] * zv[0]);
+        acc2[1] += (double)(rv[0] * rv[0]);
+      }
+    }
+    group_reduce<2, TPB>(acc2, P.part, &ctl->bar, P.nwg, wl, parity, t);
+    double rz = t[0];
+    // (the outer target as for a single problem: the 2-norm of the LP residual, unit = scale)
+    const double tol = fmax(fmax(a.rtol * sqrt(t[1]), a.atol / scale),
+                            a.outer_stop ? 0.5 * a.outer_tol * bn / scale : 0.0);
+    bool inner_done = sqrt(t[1]) <= tol;
+    bool inner_conv = inner_done;
+    double beta = 0.0;
+    int its = 0;
+    while (!inner_done && its < a.maxit) {
+      // ---- C1: p_new = z + beta p_old ; q = M p_new ; (p, q) ----
+      const S* pold = (its & 1) ? (const S*)P.p1 : (const S*)P.p0;
+      S* pnew = (its & 1) ? (S*)P.p0 : (S*)P.p1;
+      const InAxpy<C, S, 1> f{z, its > 0 ? pold : z, its > 0 ? (C)beta : C(0)};
+      double acc3[1] = {0.0};
+      for (int it0 = 0; it0 < nit; it0 += RU) {
+        int row[RU];
+        bool val[RU];
+        rows_of<RU>(r0, r1, nit, it0, row, val);
+        C pc[RU][1], w[RU][1];
+#pragma unroll
+        for (int k = 0; k < RU; ++k) stencil_group<C, 1, 0, S>(P.geo, M, row[k], f, pc[k], w[k]);
+#pragma unroll
+        for (int k = 0; k < RU; ++k) {
+          if (val[k]) {
+            w[k][0] = rnd<S, C>(w[k][0]);
+            store_shared(pnew + row[k], (S)pc[k][0]);
+            q[row[k]] = (S)w[k][0];
+            acc3[0] += (double)(pc[k][0] * w[k][0]);
+          }
+        }
+      }
+      group_reduce<1, TPB>(acc3, P.part, &ctl->bar, P.nwg, wl, parity, t1);
+      const double pq = t1[0];
+      if (!(pq > 0.0) || !__builtin_isfinite(pq)) {
+        inner_conv = false;
+        break;
+      }
+      const C alpha = (C)(rz / pq);
+      // ---- C2: x += alpha p ; r -= alpha q ; z = BJ(r) ; (r, z), (r, r) ----
+      double acc4[2] = {0.0, 0.0};
+      for (int it0 = 0; it0 < nit; it0 += RU) {
+        int row[RU];
+        bool val[RU];
+        rows_of<RU>(r0, r1, nit, it0, row, val);
+        // every load of the RU rows first (x is read but unused in the first iteration)
+        C pv[RU], xo[RU], ro[RU], qo[RU];
+        BJRows<S, 1, BS == 0 ? 1 : BS> R[RU];
+#pragma unroll
+        for (int k = 0; k < RU; ++k) {
+          pv[k] = (C)pnew[row[k]];
+          xo[k] = (C)x[row[k]];
+          ro[k] = (C)r[row[k]];
+          qo[k] = (C)q[row[k]];
+          if constexpr (BS > 0) bj_load<S, 1, BS, 2>(dinv, row[k], val[k], R[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < RU; ++k) {
+          C rv[1], zv[1];
+          const C xv = rnd2<S, C>(its == 0 ? alpha * pv[k] : xo[k] + alpha * pv[k]);
+          rv[0] = val[k] ? rnd_fma<S, C>(-alpha, qo[k], ro[k]) : C(0);
+          if (val[k]) {
+            x[row[k]] = (S)xv;
+            if constexpr (BS > 0) r[row[k]] = (S)rv[0];
+            else store_shared(r + row[k], (S)rv[0]);  // z aliases r
+          }
+          if constexpr (BS > 0) {
+            bj_mul<C, S, 1, BS, 2, 1>(dinv, row[k], R[k], val[k], rv, zv);
+            zv[0] = rnd<S, C>(zv[0]);
+            if (val[k]) store_shared(z + row[k], (S)zv[0]);
+          } else {
+            zv[0] = rv[0];
+          }
+          if (val[k]) {
+            acc4[0] += (double)(rv[0] * zv[0]);
+            acc4[1] += (double)(rv[0] * rv[0]);
+          }
+        }
+      }
+      group_reduce<2, TPB>(acc4, P.part, &ctl->bar, P.nwg, wl, parity, t);
+      ++its;
+      const double rz_new = t[0];
+      beta = rz_new / rz;
+      rz = rz_new;
+      inner_conv = __builtin_isfinite(t[1]) && sqrt(t[1]) <= tol;
+      inner_done = !__builtin_isfinite(t[1]) || inner_conv;
+    }
+    last_conv = inner_conv;
+    total_iters += its;
+    // ---- promote: y += scale * x ----
+    if (its > 0) {
+      for (int it = 0; it < nit; ++it) {
+        const int row = r0 + it * TPB + threadIdx.x;
+        if (row >= r1) break;
+        store_shared(P.y + row, P.y[row] + scale * (double)(C)x[row]);
+      }
+    }
+    ++passes;
+    group_barrier(&ctl->bar, P.nwg);
+  }
+  if (wl == 0 && threadIdx.x == 0) {
+    ctl->iters[stage] = total_iters;
+    ctl->passes[stage] = passes;
+    ctl->resid[stage] = rel;
+    ctl->converged[stage] = converged && !nonfinite;
+    ctl->nonfinite[stage] = nonfinite;
+    ctl->life_iters += total_iters;
+    ctl->life_passes += passes;
+    if (nonfinite) __hip_atomic_store(&ctl->step_nonfinite, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (stage == a.s - 1) {
+    // ---- step combination u += dt sum_i b_i k_i (skipped after a non-finite residual) ----
+    group_barrier(&ctl->bar, P.nwg);
+    const int bad = __hip_atomic_load(&ctl->step_nonfinite, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!bad) {
+      for (int it = 0; it < nit; ++it) {
+        const int row = r0 + it * TPB + threadIdx.x;
+        if (row >= r1) break;
+        double acc = P.u[row];
+        for (int i = 0; i < a.s; ++i) acc += P.dt * a.b[i] * P.k[(size_t)i * ks + row];
+        P.u[row] = acc;
+      }
+    }
+    if (wl == 0 && threadIdx.x == 0) {
+      if (bad) ctl->bad_steps += 1;
+      else ctl->good_steps += 1;
+    }
+  }
+}
+
 }  // namespace mprk
 
 // ------------------------------------------------------------------------------------------
@@ -407,11 +677,16 @@ struct mprk_batch {
   // of the last step; used by plan_groups while use_measured is set
   std::vector<double> measured_w;
   bool use_measured = false;
-  int ru = 4;                 // consecutive rows a thread handles together (1, 2, 4)
+  int ru = 4;                 // consecutive rows a thread handles together (1, 2, 4; FP16: rows, 2)
   int capacity = 0;           // co-resident workgroups of the device for the kernel in use
   int cus = 0;                // compute units of the device
   int max_capacity = 0;       // largest capacity over the kernel variants (sizes the map)
+  hipEvent_t launched = nullptr;  // after the last step enqueued, where steps fill the device
   ~mprk_batch() {
+    if (launched) {
+      gate_forget(launched);
+      (void)hipEventDestroy(launched);
+    }
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (graph) (void)hipGraphDestroy(graph);
   }
@@ -421,14 +696,20 @@ namespace mprk {
 Coef<double> operator_coef(const mprk_grid& g, const mprk_operator& op);
 }
 
+template <typename S, typename C, int BS, int RU>
+static const void* kb_kernel_bs() {
+  if constexpr (sizeof(S) == 2) return (const void*)kb_stage_rows<S, C, BS, RU>;
+  else return (const void*)kb_stage<S, C, BS, RU>;
+}
+
 template <typename S, typename C, int RU>
 static const void* kb_kernel_ptr(int bs) {
   switch (bs) {
-    case 0: return (const void*)kb_stage<S, C, 0, RU>;
-    case 1: return (const void*)kb_stage<S, C, 1, RU>;
-    case 2: return (const void*)kb_stage<S, C, 2, RU>;
-    case 4: return (const void*)kb_stage<S, C, 4, RU>;
-    default: return (const void*)kb_stage<S, C, 8, RU>;
+    case 0: return kb_kernel_bs<S, C, 0, RU>();
+    case 1: return kb_kernel_bs<S, C, 1, RU>();
+    case 2: return kb_kernel_bs<S, C, 2, RU>();
+    case 4: return kb_kernel_bs<S, C, 4, RU>();
+    default: return kb_kernel_bs<S, C, 8, RU>();
   }
 }
 
@@ -497,6 +778,7 @@ extern "C" int32_t mprk_batch_create(int32_t count, const mprk_problem* problems
   b->probs.assign(problems, problems + count);
   b->tab = *tab;
   b->prec = *prec;
+  if (prec->storage == MPRK_FP16) b->ru = 2;
   b->stream = (hipStream_t)hip_stream;
   for (int p = 0; p < count; ++p) {
     const mprk_problem& q = problems[p];
@@ -547,7 +829,9 @@ static int plan_groups(mprk_batch* b, int capacity) {
   // two workgroups per CU at most, unless the caller's schedule or the problem count asks for more:
   // the 64-problem mix takes 27.2 ms a step with 484 workgroups, 29.0 with 739, 33.6 with 233
   // (fewer groups of unknowns per barrier, more partials to add)
-  int avail = std::min(capacity, std::max(b->count, 2 * b->cus)) - b->count;
+  // FP16 problems are divided as their results' order of sums has it: all the kernel can hold.
+  const int most = b->prec.storage == MPRK_FP16 ? capacity : std::min(capacity, std::max(b->count, 2 * b->cus));
+  int avail = most - b->count;
   if (capacity < b->count) return set_error(MPRK_EUNSUPPORTED, "more problems than co-resident workgroups");
   int fixed_total = 0;
   for (int p = 0; p < b->count; ++p) {
@@ -673,7 +957,7 @@ extern "C" int64_t mprk_batch_workspace_bytes(const mprk_batch* cb) {
       }
     }
     int rc = batch_capacity(b, b->ru, &cap);
-    for (; !rc && cap < need && b->ru > 1;) {
+    for (; !rc && cap < need && b->ru > 1 && b->prec.storage != MPRK_FP16;) {
       b->ru /= 2;
       rc = batch_capacity(b, b->ru, &cap);
     }
@@ -910,6 +1194,7 @@ extern "C" int32_t mprk_batch_autotune(mprk_batch* b, double* exponent_out, int3
     for (int rep = 0; rep < 2 && !r; ++rep) {
       r = restore();
       if (r) break;
+      const std::unique_lock<std::mutex> turn = gate_batch_turn();  // (to the replay's end)
       if (hipEventRecord(e0, b->stream) != hipSuccess || hipGraphLaunch(b->gexec, b->stream) != hipSuccess ||
           hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
         r = set_error(MPRK_EDEVICE, "autotune replay failed");
@@ -1004,7 +1289,18 @@ extern "C" int32_t mprk_batch_step(mprk_batch* b, int32_t nsteps) {
   if (!b) return set_error(MPRK_EINVAL, "NULL batch");
   if (!b->bound) return set_error(MPRK_ESTATE, "mprk_batch_step before mprk_batch_bind");
   if (nsteps < 0) return set_error(MPRK_EINVAL, "nsteps must be >= 0");
+  // more than two workgroups per CU leave one-launch stages no room: the two take turns
+  const bool fills = b->prec.storage == MPRK_FP16 || b->G > 2 * b->cus;
+  std::unique_lock<std::mutex> turn;
+  if (fills) {
+    if (!b->launched) BHIP(hipEventCreateWithFlags(&b->launched, hipEventDisableTiming));
+    turn = gate_batch_turn();
+  }
   for (int n = 0; n < nsteps; ++n) BHIP(hipGraphLaunch(b->gexec, b->stream));
+  if (fills) {
+    BHIP(hipEventRecord(b->launched, b->stream));
+    gate_remember(b->launched);
+  }
   return MPRK_OK;
 }
 

@@ -1633,12 +1633,13 @@ void mprk_handle::keep_records() {
 
 // Workgroups of one-launch stages in flight in this process: their workgroups wait for each other
 // inside a launch, so all launched at a time have to fit the device together, also beside a batched
-// step (two workgroups per CU).  A call waits here until the others in flight leave it room.
+// step of two workgroups per CU; a batch that takes more of the device takes turns with them.  A call waits here until the others in flight leave it room.
 namespace {
 struct StageGate {
   std::mutex mu;
   std::condition_variable cv;
   int used = 0;
+  std::vector<hipEvent_t> batches;  // steps of batches that leave no room, perhaps still running
 };
 StageGate g_gate;
 constexpr int GATE_WGS = 192;
@@ -1650,6 +1651,8 @@ struct GateHold {
     if (!n) return;
     std::unique_lock<std::mutex> lk(g_gate.mu);
     g_gate.cv.wait(lk, [&] { return g_gate.used + n <= GATE_WGS; });
+    for (hipEvent_t e : g_gate.batches) (void)hipEventSynchronize(e);
+    g_gate.batches.clear();
     g_gate.used += n;
   }
   ~GateHold() {
@@ -1662,6 +1665,21 @@ struct GateHold {
   }
 };
 }  // namespace
+
+// A batch's launches go out while no one-launch stage is in flight and the lock is held.
+std::unique_lock<std::mutex> gate_batch_turn() {
+  std::unique_lock<std::mutex> lk(g_gate.mu);
+  g_gate.cv.wait(lk, [] { return g_gate.used == 0; });
+  return lk;
+}
+void gate_remember(hipEvent_t e) {
+  if (std::find(g_gate.batches.begin(), g_gate.batches.end(), e) == g_gate.batches.end())
+    g_gate.batches.push_back(e);
+}
+void gate_forget(hipEvent_t e) {
+  std::lock_guard<std::mutex> lk(g_gate.mu);
+  g_gate.batches.erase(std::remove(g_gate.batches.begin(), g_gate.batches.end(), e), g_gate.batches.end());
+}
 
 extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) {
   if (!h) return set_error(MPRK_EINVAL, "NULL handle");

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -25,6 +26,11 @@ void assemble_csr(const Geo& geo, const Coef<double>& K, std::vector<int>& rowpt
 constexpr int NSLOT = 64;  // pinned poll slots
 
 }  // namespace mprk
+
+// One-launch stages and batches that fill the device take turns (runtime.hip).
+std::unique_lock<std::mutex> gate_batch_turn();
+void gate_remember(hipEvent_t e);  // (the turn is held)
+void gate_forget(hipEvent_t e);
 
 struct mprk_handle {
   // problem
