@@ -564,6 +564,12 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   flat = g.nx % 4 != 0;
   vec_lp = (p.storage == MPRK_FP16 && g.nx % 8 != 4) ? 8 : 4;
   flat_lp = g.nx % vec_lp != 0;
+  // CG on a small grid of flat groups: one value per thread.  A wave whose groups cross a plane's
+  // edge makes two trips to memory more, which few waves cannot hide: a heat step of 51^3 in FP16
+  // 873 us with groups of eight, 732 with one value, 75^3 1076 and 1067, 83^3 1216 and 1280; of
+  // 54^3 in FP32 1160 with groups of four, 1095 with one value, 75^3 1583 and 1618; in FP64 1667
+  // and 1532, 2587 and 2671.
+  if (flat_lp && p.krylov == MPRK_CG && N <= (p.storage == MPRK_FP16 ? 1 << 19 : 3 << 17)) vec_lp = 1;
   vec_ad = flat_lp ? 1 : vec_lp;
   Kc = operator_coef(g, o);
   // FP64 arithmetic over FP32 / FP16 storage: the compressed-basis variants

@@ -85,3 +85,21 @@ def test_stage_solve_on_misaligned_caller_vectors(shape, krylov_name, storage):
     # the residual test: ||M (x - ref)|| <= outer_tol ||rhs|| and ||M^-1|| <= 1
     tol = st.prec.outer_tol * np.linalg.norm(rhs.cpu().numpy())
     assert np.linalg.norm(got[1:N + 1] - ref) <= 1.01 * tol + 1e-13 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("storage", ['fp64', 'fp32', 'fp16'])
+@pytest.mark.parametrize("shape", [(66, 67, 65), (90, 66, 66), (74, 73, 73), (89, 81, 73), (7, 9, 5)])
+def test_cg_steps_on_both_sides_of_the_one_value_line(shape, storage):
+    # CG with one value per thread and with groups of values: past the one-launch stages, on both
+    # sides of 3 2^17 (FP64, FP32) and 2^19 (FP16) unknowns; the stage system's residual test
+    bc, kind, diff, b = OPS[0]
+    log_case('flat_cg_line', shape=shape, storage=storage)
+    st = M.Stepper(shape, bc, kind, diff, b, A.FMT_STENCIL, 'SDIRK3', M.precisions(storage, 'cg'), 2e-3)
+    rhs = np.random.default_rng(8).standard_normal(st.N)
+    x, info = st.solve(0, torch.from_numpy(rhs).cuda())
+    Mx = operators.stage_matrix(operators.operator(shape, bc, kind, diff, b), st.dt * st.tab.a_lo[0])
+    got = x.cpu().numpy()
+    lim = st.prec.outer_tol * np.linalg.norm(rhs) + 32 * U[A.FP64] * np.linalg.norm(abs(Mx) @ np.abs(got))
+    st.close()
+    assert info['converged'] == 1, info
+    assert np.linalg.norm(rhs - Mx @ got) <= lim
