@@ -704,7 +704,7 @@ struct In1 {
 // before it issues the second, fourteen memory round trips in a row per stencil group.
 template <typename C, typename S, int VEC>
 struct InAxpy {
-  static constexpr int pin = sizeof(S) == 2 && sizeof(C) == 4 ? 1 : 0;
+  static constexpr int pin = sizeof(C) == 4 ? 1 : 0;
   const S* __restrict__ a;
   const S* __restrict__ b;
   C beta;
