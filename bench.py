@@ -38,13 +38,14 @@ def log(*a):
 def algorithmic_bytes(kc: str, N: int, s: int, m: int, bs: int, worked: int, units: int,
                       nv_total: int = 0, fdm: bool = False, cb: int = 4,
                       csr_nnz_row: float = 0.0, zstored: bool = False,
-                      inv_entry: float = 0.0) -> float:
+                      inv_entry: float = 0.0, bj_table: bool = False) -> float:
     """Bytes each kernel class must move per its definition (each array touched once; halos
     and reduction partials not counted).  s = LP storage bytes, m = LP matrix bytes, bs = block,
     cb = bytes of the arithmetic type; csr_nnz_row > 0: CSR format with that many nonzeros per
     row (values, int32 column indices and row pointers read once per SpMV); inv_entry > 0: mean
-    bytes per block-Jacobi inverse entry (adaptive precision), else m."""
-    inv = bs * (inv_entry or m)  # block-Jacobi inverse row per unknown
+    bytes per block-Jacobi inverse entry (adaptive precision), else m; bj_table: the blocks share
+    a table of a few inverses, which stays in the caches."""
+    inv = 0 if bj_table else bs * (inv_entry or m)  # block-Jacobi inverse row per unknown
     pre = (inv + s) if bs else 0  # fused block-Jacobi: inverse row read + preconditioned write
     csr_lp = csr_nnz_row * (m + 4) + 4 if csr_nnz_row else 0.0    # LP matrix of one SpMV
     csr_64 = csr_nnz_row * (8 + 4) + 4 if csr_nnz_row else 0.0    # FP64 matrix of one SpMV
@@ -475,7 +476,8 @@ def main():
         zst = (p.krylov == 'gmres' and bs > 0 and args.precond == 'bj' and launch.get('gm_form') == 1)
         b = algorithmic_bytes(kc, N, sv, s_bytes, bs, r['worked'], r['units'], nv_total,
                               fdm=args.precond == 'fdm', cb=cbytes, csr_nnz_row=nnz_row,
-                              zstored=zst, inv_entry=inv_entry)
+                              zstored=zst, inv_entry=inv_entry,
+                              bj_table=fmt == AB.FMT_STENCIL and inv_entry == 0.0)
         rows.append((kc, r, b))
     total_ms = sum(r['ms'] for _, r, _ in rows)
     dom = max(rows, key=lambda x: x[1]['ms'])

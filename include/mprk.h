@@ -166,7 +166,9 @@ typedef struct {
  *  bj_shared: 0 = one stored inverse per block-Jacobi block (default); 1 = store each distinct
  *           diagonal block's inverse once plus a per-block index (a single shared inverse when
  *           all blocks coincide, e.g. constant coefficients with block | nx).  Both modes give
- *           bitwise-identical inverses; mode 1 removes the inverse stream from the apply.
+ *           bitwise-identical inverses.  Matrix-free operators read a table of their distinct
+ *           inverses in either mode (0 keeps the larger workspace) where block | nx or
+ *           nx > block; elsewhere mode 1 removes the inverse stream from the apply.
  *  stage_start: start value of an implicit stage's solve y_i = rhs_i + sigma k_i (the paper
  *           leaves it open), i.e. a guess of the stage slope k_i: MPRK_START_RHS = none
  *           (y = rhs_i); MPRK_START_SLOPE = the previous stage's slope k_{i-1} for the stages
