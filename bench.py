@@ -864,12 +864,12 @@ def batch_leg(K: int, Wm: int, quick: bool) -> dict:
         return time.perf_counter() - t0
 
     t_plan = timed()
-    log(f'planned schedule (2 rows per thread, work model e = 0.5): {dof * K / t_plan:.4e} DOF-steps/s')
+    log(f'planned schedule (default unknowns per thread, work model e = 0.5): {dof * K / t_plan:.4e} DOF-steps/s')
     for i, p in enumerate(probs):
         b.set_u(i, p.u0)
     expo, ru = b.autotune()
     model = 'measured work of the last step' if expo < 0 else f'work-model exponent {expo}'
-    log(f'autotuned: {ru} rows per thread per CG sweep, {model}; workgroups '
+    log(f'autotuned: {ru} unknowns per thread, {model}; workgroups '
         f'per problem {min(b.schedule)}..{max(b.schedule)}, total {sum(b.schedule)}')
     t = timed()
     st = [b.stats(i) for i in range(len(probs))]
@@ -878,14 +878,14 @@ def batch_leg(K: int, Wm: int, quick: bool) -> dict:
     b.close()
     log(f'batch: {dof * K / t:.4e} DOF-steps/s')
     # where the time goes: the step's CG work (iterations x unknowns, from each problem's last
-    # step) at the FP32 per-block BJ(8) bytes of one iteration (11 s + 8 m = 76 B), the FP64
+    # step) at the FP32 bytes of one iteration (11 s = 44 B; the inverses' table is cached), the FP64
     # outer passes (about 120 B per unknown each), stage right-hand sides and the combination
     # (about 136 B): an effective bandwidth; and the share of workgroup time that does work when
     # each problem's workgroups take N x iterations / workgroups and the stage ends with the
     # slowest (1 = every group finishes together)
     it_dofs = sum(p.N * sum(x['iters']) for p, x in zip(probs, st))
     pass_dofs = sum(p.N * sum(x['passes']) for p, x in zip(probs, st))
-    bytes_step = 76.0 * it_dofs + 120.0 * pass_dofs + 136.0 * dof
+    bytes_step = 44.0 * it_dofs + 120.0 * pass_dofs + 136.0 * dof
     span = max(p.N * sum(x['iters']) / g for p, x, g in zip(probs, st, sched))
     balance = it_dofs / (wg * span) if span > 0 else None
     log(f'batch: {it_dofs / dof:.1f} CG iterations per unknown per step, effective '
