@@ -864,7 +864,9 @@ __device__ __forceinline__ void bj_row_adaptive(const void* base, int tag, size_
 }
 
 // Offsets (in entries) of the stored inverse rows of this lane's VEC rows e .. e+VEC-1; an
-// invalid lane gets offset 0 (the first stored row) so that its loads stay in bounds.
+// invalid lane gets offset 0 (the first stored row) so that its loads stay in bounds.  The last
+// group of a flat grid may reach past the last block: idx has no entry there, and its rows (whose
+// inputs are zero) take the last block's.
 template <typename S, int VEC, int BS>
 __device__ __forceinline__ void bj_offsets(const BJ<S>& dinv, int e, bool valid, size_t (&off)[VEC]) {
   if (dinv.mode == 3) {
@@ -877,7 +879,7 @@ __device__ __forceinline__ void bj_offsets(const BJ<S>& dinv, int e, bool valid,
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       const int row = e + i;
-      const int b = (dinv.mode == 2 || !valid) ? 0 : dinv.idx[row / BS];
+      const int b = (dinv.mode == 2 || !valid) ? 0 : dinv.idx[min(row, dinv.N - 1) / BS];
       off[i] = ((size_t)b * BS + (row & (BS - 1))) * BS;
     }
   }
