@@ -1697,6 +1697,28 @@ __device__ inline void bj_store_adaptive(void* base, const int* tag, const long 
   }
 }
 
+// The rows past the last block that the last lane's group of `lay` rows still covers (blocks smaller
+// than a group) are stored as zero: such a lane multiplies them by zero inputs, which whatever lay
+// in the workspace could turn into NaN.  tag == nullptr: the layouts of bj_store.
+template <typename S>
+__device__ inline void bj_store_tail(S* dinv, const int* tag, const long long* aoff, int nblk, int BS,
+                                     int lay) {
+  const int per = tag && lay == 1 ? 64 : lay;  // (mode 4 with lay = 1 serves groups of any width)
+  if (per < 1) return;
+  for (int r = nblk * BS; r % per != 0; ++r) {
+    if (tag) {
+      const int g = r / lay, q = r % lay;
+      const int ch = g >> 6;
+      const int eb = 1 << tag[ch];  // bytes per entry
+      char* p = (char*)dinv + aoff[ch] + ((size_t)q * 64 + (g & 63)) * BS * eb;
+      for (int k = 0; k < BS * eb; ++k) p[k] = 0;
+    } else {
+      const size_t chunk = lay == 8 ? bj_chunk<8>(r) : lay == 4 ? bj_chunk<4>(r) : bj_chunk<1>(r);
+      for (int k = 0; k < BS; ++k) dinv[chunk * BS + k] = (S)0;
+    }
+  }
+}
+
 // Diagonal blocks of M = I - sigma K for the stencil operator (Mc = stencil of M in FP64).
 // Slot i receives the inverse of block reps[i] (reps == nullptr: block i, stored in the
 // layout `lay`), so the per-block table and the table of distinct blocks come from the same
@@ -1727,6 +1749,7 @@ __global__ void k_bj_setup_stencil(int nslot, int BS, Geo geo, Coef<double> Mc, 
   if (gj_invert(a, inv, n)) atomicOr(fail, 1);
   if (atag) bj_store_adaptive(dinv, atag, aoff, slot, BS, n, inv, lay);
   else bj_store<S>(dinv, slot, BS, n, inv, reps ? 0 : lay);
+  if (!reps && slot == nslot - 1) bj_store_tail<S>(dinv, atag, aoff, nslot, BS, lay);
 }
 
 // Diagonal blocks of M = I - sigma K from the FP64 CSR values of K (slots as above).
@@ -1752,6 +1775,7 @@ __global__ void k_bj_setup_csr(int nslot, int BS, int N, Csr csr, const double* 
   if (gj_invert(a, inv, n)) atomicOr(fail, 1);
   if (atag) bj_store_adaptive(dinv, atag, aoff, slot, BS, n, inv, lay);
   else bj_store<S>(dinv, slot, BS, n, inv, reps ? 0 : lay);
+  if (!reps && slot == nslot - 1) bj_store_tail<S>(dinv, atag, aoff, nslot, BS, lay);
 }
 
 // LP copy of the CSR values of K, scaled by a power of two into [-1, 1].
