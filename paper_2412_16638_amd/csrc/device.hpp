@@ -996,7 +996,9 @@ __device__ __forceinline__ void bj_decode_narrow(const Vec<S, BS>& row, int tag,
 // z = D^{-1} r from the table of modes 5 and 6 when a lane holds whole blocks (BS <= VEC).  The
 // inverse of the blocks inside an x-row is the same for every lane, so its entries are read
 // through the scalar cache into scalar registers and cost the vector memory path nothing; only
-// lanes whose block an x-row ends in read their own rows.  RND: as bj_row_dot.
+// lanes whose block an x-row ends in read their own rows.  Mode 0 (the batched form's grids of
+// x-rows shorter than a block) has a slot per block, which all but the first block read so.
+// RND: as bj_row_dot.
 template <typename C, typename S, int VEC, int BS, int RND>
 __device__ __forceinline__ void bj_table_mul(const BJ<S>& dinv, int e, bool valid, const C (&r)[VEC],
                                              C (&z)[VEC]) {
@@ -1017,10 +1019,11 @@ __device__ __forceinline__ void bj_table_mul(const BJ<S>& dinv, int e, bool vali
   __builtin_memcpy(T, &raw, sizeof(T));
 #pragma unroll
   for (int q = 0; q < VEC; ++q) z[q] = bj_row_dot<C, S, VEC, BS, RND>(T[q % BS], q, r, nullptr);
-  if (dinv.mode == 5 && BS > 1) {
+  if (dinv.mode != 6 && BS > 1) {
 #pragma unroll
     for (int b = 0; b < VEC / BS; ++b) {
-      const int slot = valid ? bj_slot_of<BS>(5, e + b * BS, dinv.nx, dinv.N, dinv.dx) : 0;
+      const int b0 = e + b * BS;  // (past the end in the grid's last group: its inputs are zero)
+      const int slot = valid && b0 < dinv.N ? bj_slot_of<BS>(dinv.mode, b0, dinv.nx, dinv.N, dinv.dx) : 0;
       if (slot > 0) {
         const S* rows = dinv.inv + (size_t)slot * BS * BS;
 #pragma unroll
