@@ -90,7 +90,16 @@ template <typename S, typename C, int BS, bool many>
 __global__ __launch_bounds__(TPB, 3) void k_cg_stage(
     StagePlan pl, Geo geo, Coef<double> K, double* y, const double* __restrict__ rhs, double* kout, S* z,
     BJ<S> dinv, FTerms fx, SolveCfg cfg, Ctl* ctl, double* part, int slot) {
-  if (ctl->outer_done) return;  // (a halted call: uniform over the grid, written before the launch)
+  // the stage's record for the host (one thread)
+  auto keep_record = [&]() {
+    const long long* head = reinterpret_cast<const long long*>(ctl);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ctl->srec[slot][i] = head[i];
+  };
+  if (ctl->outer_done) {  // (a halted call: uniform over the grid, written before the launch)
+    if (blockIdx.x == 0 && threadIdx.x == 0 && slot < MAXSTG) keep_record();
+    return;
+  }
   constexpr int VEC = 4, T = TPB;
   extern __shared__ double stage_lds[];
   double* yl = stage_lds;
@@ -290,11 +299,7 @@ __global__ __launch_bounds__(TPB, 3) void k_cg_stage(
       __syncthreads();
     }
   }
-  if (lead && slot < MAXSTG) {
-    const long long* head = reinterpret_cast<const long long*>(ctl);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ctl->srec[slot][i] = head[i];
-  }
+  if (lead && slot < MAXSTG) keep_record();
 }
 
 }  // namespace mprk
