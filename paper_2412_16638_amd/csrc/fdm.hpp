@@ -700,10 +700,11 @@ __global__ __launch_bounds__(TPB) void k_cg_begin_ext(Launch ln, const double* _
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
       rv[v] = rnd<S, C>((C)(t[v] * inv));
-      s += rv[v] * rv[v];
+      if constexpr (FL) acc[0] += (double)(rv[v] * rv[v]);  // (as k_cg_begin)
+      else s += rv[v] * rv[v];
     }
     storev<S, C, VEC>(r + g * VEC, rv);
-    acc[0] += (double)s;
+    if constexpr (!FL) acc[0] += (double)s;
   }
   __shared__ double tot[1];
   if (!reduce_to_last<1>(acc, 1, red, L, ln.G, tot)) return;
@@ -747,11 +748,12 @@ __global__ __launch_bounds__(TPB) void k_cg_upd_ext(Launch ln, S* __restrict__ x
       xv[v] = first ? alpha * pv[v] : xv[v] + alpha * pv[v];
       rv[v] = rnd<S, C>(rv[v] - alpha * qv[v]);
       if (FL && e + v >= ln.n) rv[v] = C(0);
-      s += rv[v] * rv[v];
+      if constexpr (FL) acc[0] += (double)(rv[v] * rv[v]);
+      else s += rv[v] * rv[v];
     }
     storev<S, C, VEC>(x + e, xv);
     storev<S, C, VEC>(r + e, rv);
-    acc[0] += (double)s;
+    if constexpr (!FL) acc[0] += (double)s;
   }
   __shared__ double tot[1];
   if (!reduce_to_last<1>(acc, 1, red, L, ln.G, tot)) return;
@@ -783,9 +785,11 @@ __global__ __launch_bounds__(TPB) void k_cg_rz(Launch ln, const S* __restrict__ 
     loadv<C, S, VEC>(z + g * VEC, zv);
     C s = C(0);
 #pragma unroll
-    for (int v = 0; v < VEC; ++v)
-      if (!FL || g * VEC + v < ln.n) s += rv[v] * zv[v];
-    acc[0] += (double)s;
+    for (int v = 0; v < VEC; ++v) {
+      if constexpr (FL) acc[0] += g * VEC + v < ln.n ? (double)(rv[v] * zv[v]) : 0.0;
+      else s += rv[v] * zv[v];
+    }
+    if constexpr (!FL) acc[0] += (double)s;
   }
   __shared__ double tot[1];
   if (!reduce_to_last<1>(acc, 1, red, L, ln.G, tot)) return;
