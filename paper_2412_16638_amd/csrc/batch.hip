@@ -92,11 +92,15 @@ __device__ __forceinline__ BProb load_problem(const BArgs& a, int pid) {
 
 // Minimum waves per SIMD the compiler must allow (register budget) for each group width.  Groups
 // of 4 get room to keep a whole stencil group's loads in flight (at 96 registers the compiler
-// waits for them one by one: 64 FP32 heat problems 34 ms a step against 29 with 168); the
-// narrower ones keep the co-residency that schedules of many workgroups need.
-template <typename S, int VEC>
+// waits for them one by one: 64 FP32 heat problems 34 ms a step against 29 with 168); groups of
+// one, taken where a batch or a schedule of more workgroups leaves no other choice, hold as many as
+// a batch has been allowed: 5 a CU in FP32 (4 with blocks of 4 and 8), 4 in FP64 (3 with blocks),
+// one below what their registers allow.
+template <typename S, int BS, int VEC>
 constexpr int kb_min_waves() {
-  return VEC == 4 ? 3 : sizeof(S) == 8 ? (VEC == 1 ? 4 : 3) : 5;
+  if (VEC == 4) return 3;
+  if (VEC == 2) return sizeof(S) == 8 ? 3 : 5;
+  return sizeof(S) == 8 ? (BS > 1 ? 4 : 5) : (BS > 2 ? 5 : 6);
 }
 
 // Every vector phase of the stage works on flat groups of VEC consecutive unknowns per thread
@@ -108,7 +112,9 @@ constexpr int kb_min_waves() {
 // groups of 4: what is left is the two group reductions of an iteration and the latency of a
 // workgroup's few dozen groups between them.
 template <typename S, typename C, int BS, int VEC>
-__global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs a, int stage) {
+__global__ __launch_bounds__(TPB, (kb_min_waves<S, BS, VEC>())) void kb_stage(BArgs a, int stage) {
+  // one value never crosses a row end (the sums are added alike; FP64's own order is the flat form's)
+  constexpr int FS = VEC == 1 && sizeof(S) == 4 ? 0 : 1;
   const int pid = a.wg2prob[blockIdx.x];
   const BProb P = load_problem(a, pid);
   BCtl* ctl = P.ctl;
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
     if (stage == 0 && a.feval) {
       const In1<double, double, VEC> f{P.u};
       double uc[VEC];
-      stencil_group<double, VEC, 1>(P.geo, P.K, e, f, uc, t);
+      stencil_group<double, VEC, FS>(P.geo, P.K, e, f, uc, t);
       const double c = sigma * a.y0f;
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] += c * t[v];
@@ -182,7 +188,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
       double yc[VEC], ky[VEC], b[VEC], rr[VEC];
       loadv<double, double, VEC>(P.rhs + e, b);
       const In1<double, double, VEC> f{P.y};
-      stencil_group<double, VEC, 1>(P.geo, P.K, e, f, yc, ky);
+      stencil_group<double, VEC, FS>(P.geo, P.K, e, f, yc, ky);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
         rr[v] = b[v] - yc[v] + sigma * ky[v];
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, VEC>())) void kb_stage(BArgs 
         const int e = e0 + it * TPB * VEC;
         if (e >= r1) break;
         C pc[VEC], w[VEC];
-        stencil_group<C, VEC, 1, S>(P.geo, M, e, f, pc, w);
+        stencil_group<C, VEC, FS, S>(P.geo, M, e, f, pc, w);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
           w[v] = rnd<S, C>(w[v]);
