@@ -665,7 +665,7 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   o_rhs = take(v64);
   o_y = take(v64);
   o_res = take(v64);
-  kstride = flat ? align256(v64) : v64;  // (flat groups: every vector starts on a group)
+  kstride = flat ? (v64 + 127) & ~(size_t)127 : v64;  // (flat groups: every vector starts on a cache line)
   o_k = take(kstride * nstages);
   o_keps = need_keps ? take(kstride * nstages) : 0;
   o_scr = take(v64);  // scratch FP64 vector (solve output of k, verification)
@@ -701,7 +701,8 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
     o_V = 0;
   } else {
     o_V = take(vlp * (size_t)(p.restart + 1));
-    o_z = (bs || fdm) ? take(vlp) : 0;
+    // (with the stored directions below, the tiled forms alone read z)
+    o_z = fdm || (bs && gform_ok != 1) ? take(vlp) : 0;
     // the stored preconditioned directions BJ(V_0) .. BJ(V_m) of the gather form
     o_Zb = (bs && !fdm) ? take(vlp * (size_t)(p.restart + 1)) : 0;
     o_r = o_p0 = o_p1 = o_q = o_x = 0;
@@ -743,8 +744,9 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
       continue;
     }
     // (bj_shared = 0 keeps its documented footprint, one inverse per block, in every format)
+    const int lanes = B.mode == 3 || !flat_lp ? vec_lp : 1;
     const size_t rows = B.mode == 3 || !p.bj_shared
-                            ? std::max({(size_t)nblk * bs, bj_chunks((long)nblk * bs, vec_lp),
+                            ? std::max({(size_t)nblk * bs, bj_chunks((long)nblk * bs, lanes),
                                         (size_t)B.nslot * bs})
                             : (size_t)B.nslot * bs;
     B.o_inv = take(rows * bs * lp_bytes);
@@ -784,8 +786,11 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   }
   o_ctl = take(sizeof(Ctl));
   o_flag = take(256);
-  o_part = take((size_t)MAXRED * pstride * 8);
-  o_part2 = take((size_t)MAXRED * pstride2 * 8);
+  // values of one reduction: the residual's three; in GMRES one per basis vector, with the tiled forms'
+  // two norms; the exchange slots of a one-launch stage (12 a workgroup of up to 1024 unknowns) fit too
+  const size_t nred = p.krylov == MPRK_CG ? 4 : std::max(4, p.restart + (gform_ok == 1 ? 1 : 2));
+  o_part = take(nred * pstride * 8);
+  o_part2 = take(nred * pstride2 * 8);
   o_tick = take(red_ticks(pstride) * 4);
   ws_bytes = off;
   // per-sigma solve configurations
