@@ -1227,8 +1227,7 @@ int mprk_handle::run_solve(int si, int slot, const double* rhs, double* y, doubl
   if (one_launch()) {
     EngineCtx c = ctx();
     HIPCHK(eng->cg_stage(c, cfgs[si], stage_plan, Kc, rhs, y, kout, fx, bj_desc(si), slot));
-    // (the step graph captures what the last steered solves needed)
-    return graph_on && slot < MAXSTG ? stage_record(slot) : MPRK_OK;
+    return MPRK_OK;  // (its record stays on the device: keep_records)
   }
   int rc = update_hist(slot);
   if (rc) return rc;
@@ -1585,7 +1584,7 @@ int mprk_handle::graph_steps(int nsteps, int* done) {
   for (int i = 0; i < nstages && same; ++i) {
     if (!implicit_[i]) continue;
     if (hist[i].passes > ghist[i].passes) same = false;
-    for (int p = 0; p < hist[i].passes && same; ++p)
+    for (int p = 0; p < hist[i].passes && same && !one_launch(); ++p)
       if (hist[i].iters[p] > ghist[i].iters[p]) same = false;
   }
   if (!same) {
@@ -1640,6 +1639,21 @@ int mprk_handle::sync_counters() {
 // stages leave them on the device).
 void mprk_handle::keep_records() {
   std::memcpy((void*)&slots[NSLOT], top->srec, sizeof(CtlHead) * nstages);
+}
+
+// The histories of steered one-launch stages, from those records: what the step graph captures.  A
+// pass's iterations are bounded by the stage's.
+void mprk_handle::keep_history() {
+  for (int i = 0; i < nstages; ++i) {
+    if (!implicit_[i]) continue;
+    const CtlHead& r = top->srec[i];
+    StageHist& H = hist[i];
+    rec_pending[i] = false;
+    H.valid = !r.nonfinite && r.converged && r.passes > 0 && r.passes <= MAXPASS;
+    if (!H.valid) continue;
+    H.passes = r.passes;
+    for (int p = 0; p < r.passes; ++p) H.iters[p] = r.total_iters;
+  }
 }
 
 // Workgroups of one-launch stages in flight in this process: their workgroups wait for each other
@@ -1716,7 +1730,10 @@ extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) 
   }
   int rc = h->sync_counters();
   if (rc && rc != MPRK_ENONFINITE) return rc;
-  if (h->one_launch() && done < nsteps) h->keep_records();
+  if (h->one_launch() && done < nsteps) {
+    h->keep_records();
+    h->keep_history();
+  }
   if (stats) h->fill_stats(stats);
   if (rc == MPRK_ENONFINITE) return set_error(rc, "non-finite residual: u left at the last completed step");
   // every stage of every step of this call counts, not only the last step's record; the

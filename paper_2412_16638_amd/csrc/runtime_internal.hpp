@@ -202,6 +202,7 @@ struct mprk_handle {
   int enqueue_step(bool first_of_call);
   int read_top();
   void keep_records();
+  void keep_history();
   int sync_counters();
   int check_ws() const;
   void set_residual_tiles(int lz);

@@ -1,5 +1,6 @@
-"""Statistics of the most recent step when a small CG problem's stages run as one launch each: stages
-that a strict miss skipped report nothing of an earlier step."""
+"""Records of the most recent step when a small CG problem's stages run as one launch each: stages that a
+strict miss skipped report nothing of an earlier step, and steered steps leave the step graph the
+histories that it needs."""
 import numpy as np
 import pytest
 
@@ -38,3 +39,21 @@ def test_skipped_stages_report_nothing(n, storage, graph):
     for s, skipped in ((one, (1, 2)), (three, (0, 1, 2))):
         for i in skipped:
             assert (s['iters'][i], s['passes'][i], s['resid'][i], s['converged'][i]) == (0, 0, 0.0, 0), s
+
+
+@pytest.mark.parametrize("n", [8, 24])
+@pytest.mark.parametrize("storage", ['fp64', 'fp32'])
+def test_graph_enabled_after_steered_steps_replays(n, storage):
+    log_case('graph_after_steps', n=n, storage=storage)
+    p = W.heat_modes(n=n, nsteps=1)
+    p.precision = storage
+    a, b = M.from_problem(p), M.from_problem(p)
+    a.step(1)
+    a.set_step_graph(True)
+    s = a.step(3)
+    t = b.step(4)
+    ua, ub = a.get_u(), b.get_u()
+    a.close()
+    b.close()
+    assert s['graph_steps'] == 3
+    assert s['iters'] == t['iters'] and np.array_equal(ua, ub)
