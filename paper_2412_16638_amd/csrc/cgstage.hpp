@@ -27,6 +27,7 @@ struct StagePlan {
   int slab;   // most unknowns of a workgroup's part and the planes beside it
 };
 
+constexpr int STAGE_WGS_PER_CU = 3;   // by registers and LDS
 constexpr int STAGE_PART = 4 * TPB;   // a workgroup's part: one group of four unknowns per thread
 constexpr int STAGE_SLAB_MAX = 6500;  // FP64 values, so that three workgroups' slabs fit a CU's LDS
 
@@ -87,7 +88,7 @@ __device__ __forceinline__ void read_slab(const S* src, int N, int o, int L, con
 // (srec), or >= MAXSTG for none.  part: nwg > 1: 3 GRP_ND nwg slots, EMPTY before the launch.
 // Dynamic LDS: slab + 4 FP64 values.
 template <typename S, typename C, int BS, bool many>
-__global__ __launch_bounds__(TPB, 3) void k_cg_stage(
+__global__ __launch_bounds__(TPB, STAGE_WGS_PER_CU) void k_cg_stage(
     StagePlan pl, Geo geo, Coef<double> K, double* y, const double* __restrict__ rhs, double* kout, S* z,
     BJ<S> dinv, FTerms fx, SolveCfg cfg, Ctl* ctl, double* part, int slot) {
   // the stage's record for the host (one thread)
@@ -96,6 +97,7 @@ __global__ __launch_bounds__(TPB, 3) void k_cg_stage(
 #pragma unroll
     for (int i = 0; i < 8; ++i) ctl->srec[slot][i] = head[i];
   };
+  if (many && ctl->bar.error) return;  // a stage of this call timed out (the host starts it again)
   if (ctl->outer_done) {  // (a halted call: uniform over the grid, written before the launch)
     if (blockIdx.x == 0 && threadIdx.x == 0 && slot < MAXSTG) keep_record();
     return;

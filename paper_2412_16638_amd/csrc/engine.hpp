@@ -139,6 +139,8 @@ class Engine {
   virtual hipError_t cg_stage(const EngineCtx& c, const SolveCfg& cfg, const StagePlan& pl,
                               const Coef<double>& K, const double* rhs, double* y, double* kout,
                               const FTerms& fx, const BJDesc& dinv, int slot) = 0;
+  // workgroups of that launch a compute unit holds at once (0: not known)
+  virtual int cg_stage_per_cu(const EngineCtx& c, const StagePlan& pl) = 0;
   // z = P^-1 r with the fast-diagonalisation preconditioner for stage shift sigma (S storage)
   virtual hipError_t fdm_apply(const EngineCtx& c, double sigma, const void* r, void* z) = 0;
   // GMRES
@@ -474,21 +476,14 @@ class EngineT final : public Engine {
     return hipGetLastError();
   }
 
-  hipError_t cg_stage(const EngineCtx& c, const SolveCfg& cfg, const StagePlan& pl,
-                      const Coef<double>& K, const double* rhs, double* y, double* kout,
-                      const FTerms& fx, const BJDesc& dinv, int slot) override {
-    if constexpr (!std::is_same<S, C>::value) {
-      return hipErrorInvalidValue;
-    } else {
-      const unsigned lds = (pl.slab + 4) * sizeof(double);
+  // f(the one-launch stage's kernel for this problem)
+  template <typename F>
+  static void with_stage_kernel(const EngineCtx& c, const StagePlan& pl, F&& f) {
+    if constexpr (std::is_same<S, C>::value) {
       auto go = [&](auto bs) {
         constexpr int BS = decltype(bs)::value;
-        auto launch = [&](auto kern) {
-          hipLaunchKernelGGL(kern, dim3(pl.nwg), dim3(TPB), lds, c.stream, pl, c.geo, K, y, rhs, kout, (S*)c.z,
-                             bj_typed<S>(dinv), fx, cfg, c.ctl, c.red.p1, slot);
-        };
-        if (pl.nwg == 1) launch(k_cg_stage<S, C, BS, false>);
-        else launch(k_cg_stage<S, C, BS, true>);
+        if (pl.nwg == 1) f(k_cg_stage<S, C, BS, false>);
+        else f(k_cg_stage<S, C, BS, true>);
       };
       switch (c.bs) {
         case 0: go(IC<0>{}); break;
@@ -497,8 +492,25 @@ class EngineT final : public Engine {
         case 4: go(IC<4>{}); break;
         default: go(IC<8>{}); break;
       }
-      return hipGetLastError();
     }
+  }
+  static unsigned stage_lds(const StagePlan& pl) { return (pl.slab + 4) * sizeof(double); }
+  hipError_t cg_stage(const EngineCtx& c, const SolveCfg& cfg, const StagePlan& pl,
+                      const Coef<double>& K, const double* rhs, double* y, double* kout,
+                      const FTerms& fx, const BJDesc& dinv, int slot) override {
+    if (!std::is_same<S, C>::value) return hipErrorInvalidValue;
+    with_stage_kernel(c, pl, [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(pl.nwg), dim3(TPB), stage_lds(pl), c.stream, pl, c.geo, K, y, rhs, kout,
+                         (S*)c.z, bj_typed<S>(dinv), fx, cfg, c.ctl, c.red.p1, slot);
+    });
+    return hipGetLastError();
+  }
+  int cg_stage_per_cu(const EngineCtx& c, const StagePlan& pl) override {
+    int per = 0;
+    with_stage_kernel(c, pl, [&](auto kern) {
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, TPB, stage_lds(pl)) != hipSuccess) per = 0;
+    });
+    return per;
   }
 
   // ---------------- GMRES ----------------

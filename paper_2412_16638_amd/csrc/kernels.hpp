@@ -420,14 +420,16 @@ __global__ __launch_bounds__(TPB) void k_keps(Launch ln, const double* __restric
   }
 }
 
-// u += sum_j c_j v_j (step combination), skipped when the step hit a non-finite residual.
+// u += sum_j c_j v_j (step combination), skipped when the step hit a non-finite residual, was held or
+// timed out.
 template <int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_combine(Launch ln, double* __restrict__ u, CombArgs a,
                                                  Ctl* ctl) {
   const int nonfin = ctl->step_nonfinite, held = ctl->step_held;
-  const int bad = nonfin | held;
+  const int late = ctl->bar.error;  // a one-launch stage timed out: the host runs the step again
+  const int bad = nonfin | held | late;
   count_work(ctl, KC_COMBINE);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && !late) {
     if (nonfin) ctl->bad_steps += 1;
     else if (held) ctl->held_steps += 1;
     else ctl->good_steps += 1;

@@ -833,6 +833,35 @@ void mprk_handle::plan_one_launch(bool cb) {
   stage_plan = StagePlan{(int)nwg, (int)chunk, (int)slab};
 }
 
+// The workgroups of a one-launch stage wait for each other, so the device has to hold them at once:
+// three to a compute unit (cgstage.hpp), on a stream that reaches every unit.
+bool mprk_handle::stage_fits_device() {
+  if (stage_plan.nwg <= 1) return stage_plan.nwg == 1;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return false;
+  uint32_t mask[32] = {};
+  if (hipExtStreamGetCUMask(stream, 32, mask) == hipSuccess) {
+    int set = 0;
+    for (uint32_t m : mask) set += __builtin_popcount(m);
+    if (set > 0 && set < cus) return false;
+  } else {
+    (void)hipGetLastError();
+  }
+  return stage_plan.nwg <= STAGE_WGS_PER_CU * cus && eng->cg_stage_per_cu(ctx(), stage_plan) >= STAGE_WGS_PER_CU;
+}
+
+// After a one-launch stage has timed out (its workgroups found no room beside another process's, or a
+// kernel held the device for seconds): the handle goes on on the per-kernel path until the next bind.
+int mprk_handle::drop_one_launch() {
+  stage_fits = false;
+  graph_epoch += 1;  // the captured step holds one-launch stages
+  Ctl* ctl = (Ctl*)(ws + o_ctl);
+  HIPCHK(hipMemsetAsync(&ctl->bar, 0, sizeof(ctl->bar), stream));
+  return MPRK_OK;
+}
+
 // The exchange slots the stage's launch expects empty.
 void mprk_handle::stage_slots(CombArgs& a) const {
   if (!one_launch() || stage_plan.nwg == 1) return;
@@ -1044,6 +1073,7 @@ static int bind_impl(mprk_handle* h, double* u_dev, void* workspace_dev) {
   HIPCHK(hipMemcpyAsync(&hfail, fail, sizeof(int), hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
   if (hfail) return set_error(MPRK_EINVAL, "singular block-Jacobi block");
+  h->stage_fits = h->stage_fits_device();
   h->bound = true;
   return MPRK_OK;
 }
@@ -1610,8 +1640,6 @@ int mprk_handle::read_top() {
   HIPCHK(hipMemcpyAsync(top, ws + o_ctl, sizeof(CtlTop), hipMemcpyDeviceToHost, stream));
   HIPCHK(hipStreamSynchronize(stream));
   std::atomic_thread_fence(std::memory_order_acquire);
-  if (top->bar.error)
-    return set_error(MPRK_EDEVICE, "a one-launch stage timed out (workgroups not co-resident)");
   return MPRK_OK;
 }
 
@@ -1712,7 +1740,7 @@ extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) 
   if (int rcw = h->check_ws()) return rcw;
   if (nsteps < 0) return set_error(MPRK_EINVAL, "nsteps must be >= 0");
   const GateHold gate(h);
-  int done = 0;
+  int done = 0, missed = 0, held = 0;
   h->graph_steps_last = 0;
   if (h->graph_on && nsteps > 0) {
     int rc = h->graph_steps(nsteps, &done);
@@ -1721,15 +1749,27 @@ extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) 
       return set_error(rc, "non-finite residual: u left at the last completed step");
     }
     if (rc) return rc;
+    if (h->top->bar.error && (rc = h->drop_one_launch())) return rc;
   }
   // steered steps (all of them, or those after a step the graph held); the first releases the
   // halt of an earlier call or of the replays
-  for (int n = done; n < nsteps; ++n) {
-    int rc = h->enqueue_step(n == done);
-    if (rc) return rc;
+  int rc = MPRK_OK;
+  for (;;) {
+    for (int n = done; n < nsteps; ++n) {
+      rc = h->enqueue_step(n == done);
+      if (rc) return rc;
+    }
+    rc = h->sync_counters();
+    if (rc && rc != MPRK_ENONFINITE) return rc;
+    if (!h->top->bar.error) break;
+    // the steps from the one that timed out on are run again, without one-launch stages
+    done += h->last_good;
+    missed += h->last_missed;
+    held += h->last_held;
+    if ((rc = h->drop_one_launch())) return rc;
   }
-  int rc = h->sync_counters();
-  if (rc && rc != MPRK_ENONFINITE) return rc;
+  h->last_missed += missed;
+  h->last_held += held;
   if (h->one_launch() && done < nsteps) {
     h->keep_records();
     h->keep_history();
@@ -1753,22 +1793,27 @@ extern "C" int32_t mprk_solve(mprk_handle* h, int32_t stage, const double* rhs_d
     return set_error(MPRK_EINVAL, "stage must be an implicit stage of the tableau");
   const GateHold gate(h);
   Ctl* ctl = (Ctl*)(h->ws + h->o_ctl);
-  CombArgs a{};
-  a.nv = 0;
-  h->stage_slots(a);
-  // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
   double* rhs = (double*)(h->ws + h->o_rhs);
-  if (!h->flat)
-    hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, rhs_dev, a, rhs,
-                       x_dev, ctl, RESET_STAGE | RESET_CALL);
-  else
-    hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, rhs_dev, a, rhs,
-                       x_dev, ctl, RESET_STAGE | RESET_CALL);
-  HIPCHK(hipGetLastError());
-  int rc = h->run_solve(h->sig_idx[stage], MPRK_MAX_STAGES, rhs, x_dev, (double*)(h->ws + h->o_scr),
-                        FTerms{});
-  if (rc) return rc;
-  if ((rc = h->read_top())) return rc;
+  for (const double* b = rhs_dev;; b = rhs) {
+    CombArgs a{};
+    a.nv = 0;
+    h->stage_slots(a);
+    // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
+    if (!h->flat)
+      hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,
+                         x_dev, ctl, RESET_STAGE | RESET_CALL);
+    else
+      hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,
+                         x_dev, ctl, RESET_STAGE | RESET_CALL);
+    HIPCHK(hipGetLastError());
+    int rc = h->run_solve(h->sig_idx[stage], MPRK_MAX_STAGES, rhs, x_dev, (double*)(h->ws + h->o_scr),
+                          FTerms{});
+    if (rc) return rc;
+    if ((rc = h->read_top())) return rc;
+    if (!h->top->bar.error) break;
+    // (timed out: once more, without the one-launch stage; from the copy, as x may be the caller's rhs)
+    if ((rc = h->drop_one_launch())) return rc;
+  }
   const CtlHead& hd = h->top->head;
   h->missed_base = h->top->missed;  // a missed solve here is reported in info, not by the next mprk_step
   if (info) {

@@ -73,9 +73,11 @@ struct mprk_handle {
   mprk::Launch ln_lp{}, ln_lp_red{};        // LP kernels (groups of vec_lp)
   int pstride = 8;   // level-1 partials per reduced value (max blocks of a reducing launch)
   int pstride2 = 1;  // level-2 partials per reduced value
-  // small CG problems: a whole stage in one launch (nwg = 0: the per-kernel path)
+  // small CG problems: a whole stage in one launch (nwg = 0: the per-kernel path), where the bound
+  // stream's device holds its workgroups at once and none has timed out since the bind
   mprk::StagePlan stage_plan{};
-  bool one_launch() const { return stage_plan.nwg > 0 && !prof_on; }
+  bool stage_fits = false;
+  bool one_launch() const { return stage_plan.nwg > 0 && stage_fits && !prof_on; }
   int bs = 0;
   int nblk = 0;
   long nnz = 0;
@@ -179,6 +181,8 @@ struct mprk_handle {
            const mprk_precisions& p, double dt_, hipStream_t s);
   ~mprk_handle();
   void plan_one_launch(bool cb);
+  bool stage_fits_device();
+  int drop_one_launch();
   void stage_slots(mprk::CombArgs& a) const;
   int make_device_resources();
   mprk::EngineCtx ctx() const;
