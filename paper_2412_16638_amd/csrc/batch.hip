@@ -687,12 +687,11 @@ struct mprk_batch {
   int capacity = 0;           // co-resident workgroups of the device for the kernel in use
   int cus = 0;                // compute units of the device
   int max_capacity = 0;       // largest capacity over the kernel variants (sizes the map)
-  hipEvent_t launched = nullptr;  // after the last step enqueued, where steps fill the device
+  DeviceGate* gate = nullptr;     // of the device bound on
+  hipEvent_t launched = nullptr;  // behind the last step enqueued
   ~mprk_batch() {
-    if (launched) {
-      gate_forget(launched);
-      (void)hipEventDestroy(launched);
-    }
+    if (gate) gate->forget(this);
+    if (launched) (void)hipEventDestroy(launched);
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (graph) (void)hipGraphDestroy(graph);
   }
@@ -1154,6 +1153,11 @@ extern "C" int32_t mprk_batch_bind(mprk_batch* b, double* const* u_dev, void* wo
   if (hfail) return set_error(MPRK_EINVAL, "singular block-Jacobi block in batch");
   const int rc = batch_upload_capture(b, hp, map);
   if (rc) return rc;
+  int dev = 0;
+  BHIP(hipGetDevice(&dev));
+  if (b->gate) b->gate->forget(b);
+  if (!(b->gate = device_gate(dev))) return set_error(MPRK_EDEVICE, "CU count query failed");
+  if (!b->launched) BHIP(hipEventCreateWithFlags(&b->launched, hipEventDisableTiming));
   b->good_seen.assign(b->count, 0);
   b->bad_seen.assign(b->count, 0);
   b->bound = true;
@@ -1200,10 +1204,11 @@ extern "C" int32_t mprk_batch_autotune(mprk_batch* b, double* exponent_out, int3
     for (int rep = 0; rep < 2 && !r; ++rep) {
       r = restore();
       if (r) break;
-      const std::unique_lock<std::mutex> turn = gate_batch_turn();  // (to the replay's end)
-      if (hipEventRecord(e0, b->stream) != hipSuccess || hipGraphLaunch(b->gexec, b->stream) != hipSuccess ||
-          hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
-        r = set_error(MPRK_EDEVICE, "autotune replay failed");
+      const int rl = b->gate->batch(b, b->stream, b->launched, b->G, true, [&] {
+        return hipEventRecord(e0, b->stream) != hipSuccess || hipGraphLaunch(b->gexec, b->stream) != hipSuccess ||
+               hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess;
+      });
+      if (rl) r = set_error(MPRK_EDEVICE, "autotune replay failed");
     }
     if (!r && hipEventElapsedTime(ms, e0, e1) != hipSuccess) r = set_error(MPRK_EDEVICE, "autotune timing failed");
     return r;
@@ -1295,17 +1300,14 @@ extern "C" int32_t mprk_batch_step(mprk_batch* b, int32_t nsteps) {
   if (!b) return set_error(MPRK_EINVAL, "NULL batch");
   if (!b->bound) return set_error(MPRK_ESTATE, "mprk_batch_step before mprk_batch_bind");
   if (nsteps < 0) return set_error(MPRK_EINVAL, "nsteps must be >= 0");
-  // more than two workgroups per CU leave one-launch stages no room: the two take turns
-  const bool fills = b->prec.storage == MPRK_FP16 || b->G > 2 * b->cus;
-  std::unique_lock<std::mutex> turn;
-  if (fills) {
-    if (!b->launched) BHIP(hipEventCreateWithFlags(&b->launched, hipEventDisableTiming));
-    turn = gate_batch_turn();
-  }
-  for (int n = 0; n < nsteps; ++n) BHIP(hipGraphLaunch(b->gexec, b->stream));
-  if (fills) {
-    BHIP(hipEventRecord(b->launched, b->stream));
-    gate_remember(b->launched);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(b->stream, &cap) != hipSuccess) (void)hipGetLastError();
+  for (int n = 0; n < nsteps; ++n) {
+    auto launch = [&] { return (int)hipGraphLaunch(b->gexec, b->stream); };
+    // (a captured launch runs when its graph does: nothing to order it by here)
+    const int rc = cap == hipStreamCaptureStatusNone
+                       ? b->gate->batch(b, b->stream, b->launched, b->G, false, launch) : launch();
+    if (rc) return set_error(MPRK_EDEVICE, std::string("batch step: ") + hipGetErrorString((hipError_t)rc));
   }
   return MPRK_OK;
 }

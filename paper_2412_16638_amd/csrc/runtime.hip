@@ -13,7 +13,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <condition_variable>
 #include <cstdio>
 #include <cstring>
 #include <deque>
@@ -836,6 +835,7 @@ void mprk_handle::plan_one_launch(bool cb) {
 // The workgroups of a one-launch stage wait for each other, so the device has to hold them at once:
 // three to a compute unit (cgstage.hpp), on a stream that reaches every unit.
 bool mprk_handle::stage_fits_device() {
+  gate = nullptr;
   if (stage_plan.nwg <= 1) return stage_plan.nwg == 1;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -849,7 +849,10 @@ bool mprk_handle::stage_fits_device() {
   } else {
     (void)hipGetLastError();
   }
-  return stage_plan.nwg <= STAGE_WGS_PER_CU * cus && eng->cg_stage_per_cu(ctx(), stage_plan) >= STAGE_WGS_PER_CU;
+  if (stage_plan.nwg > STAGE_WGS_PER_CU * cus || eng->cg_stage_per_cu(ctx(), stage_plan) < STAGE_WGS_PER_CU)
+    return false;
+  gate = device_gate(dev);
+  return gate != nullptr;
 }
 
 // After a one-launch stage has timed out (its workgroups found no room beside another process's, or a
@@ -1598,42 +1601,6 @@ int mprk_handle::graph_capture() {
   return MPRK_OK;
 }
 
-// Runs up to nsteps steps from the graph; *done = steps completed (combined).  The graph is
-// captured again when anything it depends on changed or when a steered solve needed more passes
-// or iterations than the capture enqueues.  A stage that missed inside the graph held its step:
-// *done < nsteps, and the caller continues on the steered path from there.
-int mprk_handle::graph_steps(int nsteps, int* done) {
-  *done = 0;
-  for (int i = 0; i < nstages; ++i)
-    if (implicit_[i]) {
-      int rc = update_hist(i);
-      if (rc) return rc;
-    }
-  if (!graph_ready()) return MPRK_OK;
-  bool same = gexec && gexec_epoch == graph_epoch;
-  for (int i = 0; i < nstages && same; ++i) {
-    if (!implicit_[i]) continue;
-    if (hist[i].passes > ghist[i].passes) same = false;
-    for (int p = 0; p < hist[i].passes && same && !one_launch(); ++p)
-      if (hist[i].iters[p] > ghist[i].iters[p]) same = false;
-  }
-  if (!same) {
-    int rc = graph_capture();
-    if (rc) return rc;
-  }
-  Ctl* ctl = (Ctl*)(ws + o_ctl);
-  hipLaunchKernelGGL(k_release_halt, dim3(1), dim3(64), 0, stream, ctl);
-  HIPCHK(hipGetLastError());
-  for (int n = 0; n < nsteps; ++n) HIPCHK(hipGraphLaunch(gexec, stream));
-  // counters: completed steps; a miss inside the graph is not reported (its steps are re-run)
-  int rc = sync_counters();
-  // the stage records of the last replayed step, for the statistics
-  if (rc == MPRK_OK || rc == MPRK_ENONFINITE) keep_records();
-  *done = last_good;
-  graph_steps_last = last_good;
-  return rc;
-}
-
 // The control record's prefix (head, counters, stage records) in one copy to pinned memory; waits
 // for the stream.
 int mprk_handle::read_top() {
@@ -1684,54 +1651,108 @@ void mprk_handle::keep_history() {
   }
 }
 
-// Workgroups of one-launch stages in flight in this process: their workgroups wait for each other
-// inside a launch, so all launched at a time have to fit the device together, also beside a batched
-// step of two workgroups per CU; a batch that takes more of the device takes turns with them.  A call waits here until the others in flight leave it room.
-namespace {
-struct StageGate {
-  std::mutex mu;
-  std::condition_variable cv;
-  int used = 0;
-  std::vector<hipEvent_t> batches;  // steps of batches that leave no room, perhaps still running
-};
-StageGate g_gate;
-constexpr int GATE_WGS = 192;
+namespace mprk {
 
+DeviceGate* device_gate(int dev) {
+  static std::mutex mu;
+  static std::map<int, DeviceGate*> gates;
+  std::lock_guard<std::mutex> lk(mu);
+  DeviceGate*& g = gates[dev];
+  int cus = 0;
+  if (!g && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+    g = new (std::nothrow) DeviceGate(STAGE_WGS_PER_CU * cus);
+  return g;
+}
+
+// A call of a handle whose stages wait for each other inside a launch.  A long call gives way to
+// calls that wait to enter, and is never enqueued far ahead of the device, so that they wait for a
+// few dozen steps and not for its end.
 struct GateHold {
-  int n;
-  explicit GateHold(const mprk_handle* h)
-      : n(h->one_launch() && h->stage_plan.nwg > 1 ? h->stage_plan.nwg : 0) {
-    if (!n) return;
-    std::unique_lock<std::mutex> lk(g_gate.mu);
-    g_gate.cv.wait(lk, [&] { return g_gate.used + n <= GATE_WGS; });
-    for (hipEvent_t e : g_gate.batches) (void)hipEventSynchronize(e);
-    g_gate.batches.clear();
-    g_gate.used += n;
+  static constexpr int RUN = 16;  // steps enqueued between two looks
+  mprk_handle* h;
+  DeviceGate::Call call{};
+  bool in = false;
+  bool idle = true;  // nothing of this call is in flight
+  int steps = 0;
+
+  explicit GateHold(mprk_handle* h_) : h(h_) {
+    if (!h->gate || !h->one_launch() || h->stage_plan.nwg <= 1) return;
+    call = DeviceGate::Call{h->stream, h->stage_plan.nwg};
+    h->gate->enter(call);
+    in = true;
   }
+  GateHold(const GateHold&) = delete;
   ~GateHold() {
-    if (!n) return;
-    {
-      std::lock_guard<std::mutex> lk(g_gate.mu);
-      g_gate.used -= n;
+    if (!in) return;
+    if (!idle) (void)hipStreamSynchronize(h->stream);  // (an error return: launches may be running)
+    h->gate->leave(call);
+  }
+  // one step (or solve) around its launches
+  template <class F>
+  int step(F&& launches) {
+    if (!in || !h->one_launch()) return launches();
+    if (steps > 0 && steps % RUN == 0) {
+      const int e = steps / RUN % 2;
+      if (h->gate->crowded()) {
+        HIPCHK(hipStreamSynchronize(h->stream));
+        h->gate->leave(call);
+        h->gate->enter(call);
+      } else {  // at most two runs ahead
+        HIPCHK(hipEventRecord(h->ev[e], h->stream));
+        if (steps > RUN) HIPCHK(hipEventSynchronize(h->ev[1 - e]));
+      }
     }
-    g_gate.cv.notify_all();
+    ++steps;
+    idle = false;
+    const int rg = h->gate->begin_step(call);
+    const int rc = rg ? set_error(MPRK_EDEVICE, "a stream could not wait for a batch's event") : launches();
+    h->gate->end_step();
+    return rc;
   }
 };
-}  // namespace
 
-// A batch's launches go out while no one-launch stage is in flight and the lock is held.
-std::unique_lock<std::mutex> gate_batch_turn() {
-  std::unique_lock<std::mutex> lk(g_gate.mu);
-  g_gate.cv.wait(lk, [] { return g_gate.used == 0; });
-  return lk;
-}
-void gate_remember(hipEvent_t e) {
-  if (std::find(g_gate.batches.begin(), g_gate.batches.end(), e) == g_gate.batches.end())
-    g_gate.batches.push_back(e);
-}
-void gate_forget(hipEvent_t e) {
-  std::lock_guard<std::mutex> lk(g_gate.mu);
-  g_gate.batches.erase(std::remove(g_gate.batches.begin(), g_gate.batches.end(), e), g_gate.batches.end());
+}  // namespace mprk
+
+// Runs up to nsteps steps from the graph; *done = steps completed (combined).  The graph is
+// captured again when anything it depends on changed or when a steered solve needed more passes
+// or iterations than the capture enqueues.  A stage that missed inside the graph held its step:
+// *done < nsteps, and the caller continues on the steered path from there.
+int mprk_handle::graph_steps(int nsteps, int* done, GateHold& gate_hold) {
+  *done = 0;
+  for (int i = 0; i < nstages; ++i)
+    if (implicit_[i]) {
+      int rc = update_hist(i);
+      if (rc) return rc;
+    }
+  if (!graph_ready()) return MPRK_OK;
+  bool same = gexec && gexec_epoch == graph_epoch;
+  for (int i = 0; i < nstages && same; ++i) {
+    if (!implicit_[i]) continue;
+    if (hist[i].passes > ghist[i].passes) same = false;
+    for (int p = 0; p < hist[i].passes && same && !one_launch(); ++p)
+      if (hist[i].iters[p] > ghist[i].iters[p]) same = false;
+  }
+  if (!same) {
+    int rc = graph_capture();
+    if (rc) return rc;
+  }
+  Ctl* ctl = (Ctl*)(ws + o_ctl);
+  hipLaunchKernelGGL(k_release_halt, dim3(1), dim3(64), 0, stream, ctl);
+  HIPCHK(hipGetLastError());
+  for (int n = 0; n < nsteps; ++n) {
+    const int rl = gate_hold.step([&]() -> int {
+      HIPCHK(hipGraphLaunch(gexec, stream));
+      return MPRK_OK;
+    });
+    if (rl) return rl;
+  }
+  // counters: completed steps; a miss inside the graph is not reported (its steps are re-run)
+  int rc = sync_counters();
+  // the stage records of the last replayed step, for the statistics
+  if (rc == MPRK_OK || rc == MPRK_ENONFINITE) keep_records();
+  *done = last_good;
+  graph_steps_last = last_good;
+  return rc;
 }
 
 extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) {
@@ -1739,11 +1760,11 @@ extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) 
   if (!h->bound) return set_error(MPRK_ESTATE, "mprk_step before mprk_bind");
   if (int rcw = h->check_ws()) return rcw;
   if (nsteps < 0) return set_error(MPRK_EINVAL, "nsteps must be >= 0");
-  const GateHold gate(h);
+  GateHold gate(h);
   int done = 0, missed = 0, held = 0;
   h->graph_steps_last = 0;
   if (h->graph_on && nsteps > 0) {
-    int rc = h->graph_steps(nsteps, &done);
+    int rc = h->graph_steps(nsteps, &done, gate);
     if (rc == MPRK_ENONFINITE) {
       if (stats) h->fill_stats(stats);
       return set_error(rc, "non-finite residual: u left at the last completed step");
@@ -1756,10 +1777,11 @@ extern "C" int32_t mprk_step(mprk_handle* h, int32_t nsteps, mprk_stats* stats) 
   int rc = MPRK_OK;
   for (;;) {
     for (int n = done; n < nsteps; ++n) {
-      rc = h->enqueue_step(n == done);
+      rc = gate.step([&] { return h->enqueue_step(n == done); });
       if (rc) return rc;
     }
     rc = h->sync_counters();
+    gate.idle = true;
     if (rc && rc != MPRK_ENONFINITE) return rc;
     if (!h->top->bar.error) break;
     // the steps from the one that timed out on are run again, without one-launch stages
@@ -1791,25 +1813,28 @@ extern "C" int32_t mprk_solve(mprk_handle* h, int32_t stage, const double* rhs_d
   if (int rcw = h->check_ws()) return rcw;
   if (stage < 0 || stage >= h->nstages || !h->implicit_[stage])
     return set_error(MPRK_EINVAL, "stage must be an implicit stage of the tableau");
-  const GateHold gate(h);
+  GateHold gate(h);
   Ctl* ctl = (Ctl*)(h->ws + h->o_ctl);
   double* rhs = (double*)(h->ws + h->o_rhs);
   for (const double* b = rhs_dev;; b = rhs) {
-    CombArgs a{};
-    a.nv = 0;
-    h->stage_slots(a);
-    // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
-    if (!h->flat)
-      hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,
-                         x_dev, ctl, RESET_STAGE | RESET_CALL);
-    else
-      hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,
-                         x_dev, ctl, RESET_STAGE | RESET_CALL);
-    HIPCHK(hipGetLastError());
-    int rc = h->run_solve(h->sig_idx[stage], MPRK_MAX_STAGES, rhs, x_dev, (double*)(h->ws + h->o_scr),
+    int rc = gate.step([&]() -> int {
+      CombArgs a{};
+      a.nv = 0;
+      h->stage_slots(a);
+      // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
+      if (!h->flat)
+        hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,
+                           x_dev, ctl, RESET_STAGE | RESET_CALL);
+      else
+        hipLaunchKernelGGL((k_stage_rhs<4, 1>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,
+                           x_dev, ctl, RESET_STAGE | RESET_CALL);
+      HIPCHK(hipGetLastError());
+      return h->run_solve(h->sig_idx[stage], MPRK_MAX_STAGES, rhs, x_dev, (double*)(h->ws + h->o_scr),
                           FTerms{});
+    });
     if (rc) return rc;
     if ((rc = h->read_top())) return rc;
+    gate.idle = true;
     if (!h->top->bar.error) break;
     // (timed out: once more, without the one-launch stage; from the copy, as x may be the caller's rhs)
     if ((rc = h->drop_one_launch())) return rc;

@@ -4,12 +4,12 @@
 #include <hip/hip_runtime.h>
 
 #include <memory>
-#include <mutex>
 #include <string>
 #include <vector>
 
 #include "../../include/mprk.h"
 #include "engine.hpp"
+#include "gate.hpp"
 
 namespace mprk {
 
@@ -27,10 +27,25 @@ constexpr int NSLOT = 64;  // pinned poll slots
 
 }  // namespace mprk
 
-// One-launch stages and batches that fill the device take turns (runtime.hip).
-std::unique_lock<std::mutex> gate_batch_turn();
-void gate_remember(hipEvent_t e);  // (the turn is held)
-void gate_forget(hipEvent_t e);
+namespace mprk {
+
+struct HipGateApi {
+  using Stream = hipStream_t;
+  using Event = hipEvent_t;
+  static int record(Event e, Stream s) { return (int)hipEventRecord(e, s); }
+  static int wait(Stream s, Event e) { return (int)hipStreamWaitEvent(s, e, 0); }
+  static bool done(Event e) {
+    const hipError_t r = hipEventQuery(e);
+    if (r == hipErrorNotReady) (void)hipGetLastError();
+    return r != hipErrorNotReady;
+  }
+};
+using DeviceGate = Gate<HipGateApi>;
+// The gate of a device (kept for the life of the process); nullptr if it cannot be asked for its size.
+DeviceGate* device_gate(int dev);
+struct GateHold;  // a call inside the gate (runtime.hip)
+
+}  // namespace mprk
 
 struct mprk_handle {
   // problem
@@ -77,6 +92,7 @@ struct mprk_handle {
   // stream's device holds its workgroups at once and none has timed out since the bind
   mprk::StagePlan stage_plan{};
   bool stage_fits = false;
+  mprk::DeviceGate* gate = nullptr;  // of the device bound on, for stages of several workgroups
   bool one_launch() const { return stage_plan.nwg > 0 && stage_fits && !prof_on; }
   int bs = 0;
   int nblk = 0;
@@ -202,7 +218,7 @@ struct mprk_handle {
   bool graph_ready() const;
   int graph_capture();
   void graph_drop();
-  int graph_steps(int nsteps, int* done);
+  int graph_steps(int nsteps, int* done, mprk::GateHold& gate_hold);
   int enqueue_step(bool first_of_call);
   int read_top();
   void keep_records();
