@@ -239,7 +239,7 @@ class EngineT final : public Engine {
   }
   hipError_t cg_begin(const EngineCtx& c, const SolveCfg& cfg, const BJDesc& dinv) override {
     if (c.fdm_on) {
-      dispatch_vec<1>(c, [&](auto vec, auto fl) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         constexpr int VEC = decltype(vec)::value;
         constexpr int FL = decltype(fl)::value;
         MPRK_LAUNCH_KC(c, KC_CG_BEGIN, (k_cg_begin_ext<S, C, VEC, FL>), c.ln_red, c.ln_red, c.res, (S*)c.r,
@@ -249,14 +249,14 @@ class EngineT final : public Engine {
       cg_rz_t<1>(c);
       return hipGetLastError();
     }
-    dispatch_vec_bs<1>(c, [&](auto vec, auto bs, auto fl) {
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
       cg_begin_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, cfg, dinv);
     });
     return hipGetLastError();
   }
   template <int BEGIN>
   void cg_rz_t(const EngineCtx& c) {
-    dispatch_vec<1>(c, [&](auto vec, auto fl) {
+    dispatch_vec(c, [&](auto vec, auto fl) {
       constexpr int VEC = decltype(vec)::value;
       constexpr int FL = decltype(fl)::value;
       MPRK_LAUNCH_KC(c, KC_CG_RZ, (k_cg_rz<S, C, VEC, BEGIN, FL>), c.ln_red, c.ln_red, (const S*)c.r,
@@ -295,12 +295,12 @@ class EngineT final : public Engine {
     if (c.fmt == 1) {
       cg_dir_t<1, 1, 0>(c, cfg, Mc, z, pold, pnew);
     } else {
-      dispatch_vec<1>(c, [&](auto vec, auto fl) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         cg_dir_t<decltype(vec)::value, 0, decltype(fl)::value>(c, cfg, Mc, z, pold, pnew);
       });
     }
     if (c.fdm_on) {
-      dispatch_vec<1>(c, [&](auto vec, auto fl) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         constexpr int VEC = decltype(vec)::value;
         constexpr int FL = decltype(fl)::value;
         MPRK_LAUNCH_KC(c, KC_CG_UPD, (k_cg_upd_ext<S, C, VEC, FL>), c.ln_red, c.ln_red, (S*)c.x,
@@ -308,7 +308,7 @@ class EngineT final : public Engine {
       });
       return hipGetLastError();
     }
-    dispatch_vec_bs<1>(c, [&](auto vec, auto bs, auto fl) {
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
       cg_upd_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, cfg, pnew, dinv);
     });
     return hipGetLastError();
@@ -469,7 +469,7 @@ class EngineT final : public Engine {
     return hipGetLastError();
   }
   hipError_t cg_finish(const EngineCtx& c) override {
-    dispatch_vec<1>(c, [&](auto vec, auto fl) {
+    dispatch_vec(c, [&](auto vec, auto fl) {
       MPRK_LAUNCH_KC(c, KC_PROMOTE, (k_promote<S, C, decltype(vec)::value, decltype(fl)::value>), c.ln_vec,
                      c.ln_vec, c.y, (const S*)c.x, c.ctl);
     });
@@ -646,7 +646,7 @@ class EngineT final : public Engine {
     if (c.fmt == 1) {
       apply_m_t<1, 1, 0>(c, Mc, sigma, x, y);
     } else {
-      dispatch_vec<1>(c, [&](auto vec, auto fl) {
+      dispatch_vec(c, [&](auto vec, auto fl) {
         apply_m_t<decltype(vec)::value, 0, decltype(fl)::value>(c, Mc, sigma, x, y);
       });
     }
@@ -664,7 +664,7 @@ class EngineT final : public Engine {
   }
   hipError_t apply_bj(const EngineCtx& c, const BJDesc& dinv, const void* x, void* y) override {
     if (c.bs == 0) return hipErrorInvalidValue;
-    dispatch_vec_bs<1>(c, [&](auto vec, auto bs, auto fl) {
+    dispatch_vec_bs(c, [&](auto vec, auto bs, auto fl) {
       apply_bj_t<decltype(vec)::value, decltype(bs)::value, decltype(fl)::value>(c, dinv, x, y);
     });
     return hipGetLastError();
@@ -675,25 +675,24 @@ class EngineT final : public Engine {
   struct IC {
     static constexpr int value = V;
   };
-  // the group widths in use: 16 bytes of FP16 (8) where 8 | nx, else 4 where 4 | nx, else flat
-  // groups of 8; 4 (flat or not) for the wider types
-  // ONE: a caller that CG uses (vec = 1: CG on a small grid of flat groups)
-  template <int ONE = 0, typename F>
+  // the group widths in use: flat groups of one value (small grids), 16 bytes of FP16 (8) where 8 | nx,
+  // else 4 where 4 | nx, else flat groups of 8; 4 (flat or not) for the wider types
+  template <typename F>
   static void dispatch_vec(const EngineCtx& c, F&& f) {
-    if constexpr (sizeof(S) == 2) {
-      if (ONE && c.vec == 1) f(IC<ONE ? 1 : 8>{}, IC<1>{});
-      else if (c.flat) f(IC<8>{}, IC<1>{});
+    if (c.vec == 1) {
+      f(IC<1>{}, IC<1>{});
+    } else if constexpr (sizeof(S) == 2) {
+      if (c.flat) f(IC<8>{}, IC<1>{});
       else if (c.vec == 8) f(IC<8>{}, IC<0>{});
       else f(IC<4>{}, IC<0>{});
     } else {
-      if (ONE && c.vec == 1) f(IC<ONE ? 1 : 4>{}, IC<1>{});
-      else if (c.flat) f(IC<4>{}, IC<1>{});
+      if (c.flat) f(IC<4>{}, IC<1>{});
       else f(IC<4>{}, IC<0>{});
     }
   }
-  template <int ONE = 0, typename F>
+  template <typename F>
   static void dispatch_vec_bs(const EngineCtx& c, F&& f) {
-    dispatch_vec<ONE>(c, [&](auto vec, auto fl) {
+    dispatch_vec(c, [&](auto vec, auto fl) {
       switch (c.bs) {
         case 0: f(vec, IC<0>{}, fl); break;
         case 1: f(vec, IC<1>{}, fl); break;

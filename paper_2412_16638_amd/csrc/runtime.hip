@@ -563,12 +563,24 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   flat = g.nx % 4 != 0;
   vec_lp = (p.storage == MPRK_FP16 && g.nx % 8 != 4) ? 8 : 4;
   flat_lp = g.nx % vec_lp != 0;
-  // CG on a small grid of flat groups: one value per thread.  A wave whose groups cross a plane's
-  // edge makes two trips to memory more, which few waves cannot hide: a heat step of 51^3 in FP16
-  // 873 us with groups of eight, 732 with one value, 75^3 1076 and 1067, 83^3 1216 and 1280; of
-  // 54^3 in FP32 1160 with groups of four, 1095 with one value, 75^3 1583 and 1618; in FP64 1667
-  // and 1532, 2587 and 2671.
+  // A small grid of flat groups: one value per thread.  A wave whose groups cross a plane's edge makes
+  // two trips to memory more, which few waves cannot hide.  CG: a heat step of 51^3 in FP16 873 us
+  // with groups of eight, 732 with one value, 75^3 1076 and 1067, 83^3 1216 and 1280; of 54^3 in FP32
+  // 1160 with groups of four, 1095 with one value, 75^3 1583 and 1618; in FP64 1667 and 1532, 2587
+  // and 2671.  GMRES with the stencil: an advection-diffusion step of 21^3 in FP16 310 us with groups
+  // of eight, 249 with one value, 54^3 352 and 322, 79^3 396 and 390, 87^3 421 and 430; in FP64 of
+  // 21^3 520 with groups of four, 431 with one value, 50^3 860 and 802, 66^3 1080 and 1047, 70^3 1104
+  // and 1121.  Between 2^14 and 2^16 unknowns groups of four are one group of a reduction's
+  // partials where single values are not (33^3 in FP64 645 and 677), so these keep them.
   if (flat_lp && p.krylov == MPRK_CG && N <= (p.storage == MPRK_FP16 ? 1 << 19 : 3 << 17)) vec_lp = 1;
+  if (flat_lp && p.krylov == MPRK_GMRES && o.format == MPRK_FMT_STENCIL) {
+    if (p.storage == MPRK_FP16 ? N <= 1 << 19
+                               : N <= 1 << 14 || (N > 1 << 16 && N <= 5 << 16))
+      vec_lp = 1;
+  }
+  // An assembled matrix in FP64 keeps one value at every size: each lane would read four rows of the
+  // per-block inverses (a heat step of 95^3 7.3 ms with one value, 9.6 with groups of four).
+  if (flat_lp && o.format == MPRK_FMT_CSR && p.storage == MPRK_FP64) vec_lp = 1;
   vec_ad = flat_lp ? 1 : vec_lp;
   Kc = operator_coef(g, o);
   // FP64 arithmetic over FP32 / FP16 storage: the compressed-basis variants
@@ -1237,6 +1249,9 @@ int mprk_handle::launch_residual(const SolveCfg& cfg, const double* rhs, double*
   else if (zm_lz > 0)  // (zm_lz > 0 implies groups within x-rows)
     PLAUNCH(KC_RESIDUAL, (k_residual_zm<4>), dim3(zl_res.G), dim3(TPB), zmarch_lds(geo, zl_res, 8), stream,
             zl_res, geo, Kc, y, rhs, kout, res, fx, cfg, ctl, rd);
+  else if (vec_lp == 1)  // (the FP64 groups of four have the same trips)
+    PLAUNCH(KC_RESIDUAL, (k_residual<1, 0, 0>), dim3(ln_row_red.G), dim3(TPB), 0, stream, ln_row_red, geo, Kc, csr,
+                       kval, y, rhs, kout, res, fx, cfg, ctl, rd);
   else if (!flat)
     PLAUNCH(KC_RESIDUAL, (k_residual<4, 0, 0>), dim3(ln_vec_red.G), dim3(TPB), 0, stream, ln_vec_red, geo, Kc, csr,
                        kval, y, rhs, kout, res, fx, cfg, ctl, rd);
