@@ -222,7 +222,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, BS, VEC>())) void kb_stage(BA
 #pragma unroll
       for (int v = 0; v < VEC; ++v) rv[v] = valid ? rnd<S, C>((C)(rs[v] * inv)) : C(0);
       if constexpr (BS > 0) {
-        bj_apply_lane<C, S, VEC, BS, 2, 1>(dinv, e, valid, rv, zv);
+        bj_apply_lane<C, S, VEC, BS, 3, 1>(dinv, e, valid, rv, zv);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) zv[v] = rnd<S, C>(zv[v]);
       } else {
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, BS, VEC>())) void kb_stage(BA
         loadv<C, S, VEC>(r + el, rv);
         loadv<C, S, VEC>(x + el, xv);
         BJRows<S, VEC, BS == 0 ? 1 : BS> R;
-        if constexpr (BS > 0) bj_load<S, VEC, BS, 2>(dinv, e, valid, R);
+        if constexpr (BS > 0) bj_load<S, VEC, BS, 3>(dinv, e, valid, R);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
           xv[v] = rnd2<S, C>(its == 0 ? alpha * pv[v] : xv[v] + alpha * pv[v]);
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(TPB, (kb_min_waves<S, BS, VEC>())) void kb_stage(BA
           else store_shared_group<S, C, VEC>(r + r0, e - r0, P.chunk, rv);  // z aliases r
         }
         if constexpr (BS > 0) {
-          bj_mul<C, S, VEC, BS, 2, 1>(dinv, e, R, valid, rv, zv);
+          bj_mul<C, S, VEC, BS, 3, 1>(dinv, e, R, valid, rv, zv);
 #pragma unroll
           for (int v = 0; v < VEC; ++v) zv[v] = rnd<S, C>(zv[v]);
           if (valid) store_shared_group<S, C, VEC>(z + r0, e - r0, P.chunk, zv);
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(TPB, (kb_rows_min_waves<RU>())) void kb_stage_rows(
       C rv[1], zv[1];
       rv[0] = valid ? rnd<S, C>((C)(P.res[row] * inv)) : C(0);
       if constexpr (BS > 0) {
-        bj_apply_lane<C, S, 1, BS, 2, 1>(dinv, row, valid, rv, zv);
+        bj_apply_lane<C, S, 1, BS, 3, 1>(dinv, row, valid, rv, zv);
         zv[0] = rnd<S, C>(zv[0]);
       } else {
         zv[0] = rv[0];
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(TPB, (kb_rows_min_waves<RU>())) void kb_stage_rows(
           xo[k] = (C)x[row[k]];
           ro[k] = (C)r[row[k]];
           qo[k] = (C)q[row[k]];
-          if constexpr (BS > 0) bj_load<S, 1, BS, 2>(dinv, row[k], val[k], R[k]);
+          if constexpr (BS > 0) bj_load<S, 1, BS, 3>(dinv, row[k], val[k], R[k]);
         }
 #pragma unroll
         for (int k = 0; k < RU; ++k) {
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(TPB, (kb_rows_min_waves<RU>())) void kb_stage_rows(
             else store_shared(r + row[k], (S)rv[0]);  // z aliases r
           }
           if constexpr (BS > 0) {
-            bj_mul<C, S, 1, BS, 2, 1>(dinv, row[k], R[k], val[k], rv, zv);
+            bj_mul<C, S, 1, BS, 3, 1>(dinv, row[k], R[k], val[k], rv, zv);
             zv[0] = rnd<S, C>(zv[0]);
             if (val[k]) store_shared(z + row[k], (S)zv[0]);
           } else {

@@ -864,9 +864,8 @@ __device__ __forceinline__ void bj_row_adaptive(const void* base, int tag, size_
 }
 
 // Offsets (in entries) of the stored inverse rows of this lane's VEC rows e .. e+VEC-1; an
-// invalid lane gets offset 0 (the first stored row) so that its loads stay in bounds.  The last
-// group of a flat grid may reach past the last block: idx has no entry there, and its rows (whose
-// inputs are zero) take the last block's.
+// invalid lane gets offset 0 (the first stored row) so that its loads stay in bounds.  (The last
+// group of a flat grid may reach past the last block: idx has entries for whole groups.)
 template <typename S, int VEC, int BS>
 __device__ __forceinline__ void bj_offsets(const BJ<S>& dinv, int e, bool valid, size_t (&off)[VEC]) {
   if (dinv.mode == 3) {
@@ -879,7 +878,7 @@ __device__ __forceinline__ void bj_offsets(const BJ<S>& dinv, int e, bool valid,
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       const int row = e + i;
-      const int b = (dinv.mode == 2 || !valid) ? 0 : dinv.idx[min(row, dinv.N - 1) / BS];
+      const int b = (dinv.mode == 2 || !valid) ? 0 : dinv.idx[row / BS];
       off[i] = ((size_t)b * BS + (row & (BS - 1))) * BS;
     }
   }
@@ -997,9 +996,9 @@ __device__ __forceinline__ void bj_decode_narrow(const Vec<S, BS>& row, int tag,
 // inverse of the blocks inside an x-row is the same for every lane, so its entries are read
 // through the scalar cache into scalar registers and cost the vector memory path nothing; only
 // lanes whose block an x-row ends in read their own rows.  Mode 0 (the batched form's grids of
-// x-rows shorter than a block) has a slot per block, which all but the first block read so.
+// x-rows shorter than a block; AD = 3) has a slot per block, which all but the first block read so.
 // RND: as bj_row_dot.
-template <typename C, typename S, int VEC, int BS, int RND>
+template <typename C, typename S, int VEC, int BS, int AD, int RND>
 __device__ __forceinline__ void bj_table_mul(const BJ<S>& dinv, int e, bool valid, const C (&r)[VEC],
                                              C (&z)[VEC]) {
   static_assert(BS <= VEC, "a lane holds whole blocks");
@@ -1019,11 +1018,16 @@ __device__ __forceinline__ void bj_table_mul(const BJ<S>& dinv, int e, bool vali
   __builtin_memcpy(T, &raw, sizeof(T));
 #pragma unroll
   for (int q = 0; q < VEC; ++q) z[q] = bj_row_dot<C, S, VEC, BS, RND>(T[q % BS], q, r, nullptr);
-  if (dinv.mode != 6 && BS > 1) {
+  if ((AD == 3 ? dinv.mode != 6 : dinv.mode == 5) && BS > 1) {
 #pragma unroll
     for (int b = 0; b < VEC / BS; ++b) {
-      const int b0 = e + b * BS;  // (past the end in the grid's last group: its inputs are zero)
-      const int slot = valid && b0 < dinv.N ? bj_slot_of<BS>(dinv.mode, b0, dinv.nx, dinv.N, dinv.dx) : 0;
+      const int b0 = e + b * BS;
+      int slot = 0;
+      if constexpr (AD == 3) {  // (past the end in the grid's last group, inputs are zero)
+        slot = valid && b0 < dinv.N ? bj_slot_of<BS>(dinv.mode, b0, dinv.nx, dinv.N, dinv.dx) : 0;
+      } else {
+        slot = valid ? bj_slot_of<BS>(5, b0, dinv.nx, dinv.N, dinv.dx) : 0;
+      }
       if (slot > 0) {
         const S* rows = dinv.inv + (size_t)slot * BS * BS;
 #pragma unroll
@@ -1038,12 +1042,12 @@ __device__ __forceinline__ void bj_table_mul(const BJ<S>& dinv, int e, bool vali
 }
 
 // AD = 1: the adaptive-precision layout (mode 4) is possible; AD = 2: the table of modes 5 and
-// 6.  Kernels are instantiated apart for them, so that their code costs the other layouts no
-// registers.
+// 6; AD = 3: that table or mode 0 (the batched form).  Kernels are instantiated apart for them, so
+// that their code costs the other layouts no registers.
 template <typename S, int VEC, int BS, int AD = 0>
 __device__ __forceinline__ void bj_load(const BJ<S>& dinv, int e, bool valid, BJRows<S, VEC, BS>& R) {
   R.late = false;
-  if constexpr (AD == 2) {
+  if constexpr (AD >= 2) {
     if constexpr (BS > VEC) {  // a block spans lanes: each reads its rows of the block's slot
       const int slot = valid ? bj_slot_of<BS>(dinv.mode, e & ~(BS - 1), dinv.nx, dinv.N, dinv.dx) : 0;
       const S* rows = dinv.inv + ((size_t)slot * BS + (e & (BS - 1))) * BS;
@@ -1094,8 +1098,8 @@ __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool val
 template <typename C, typename S, int VEC, int BS, int AD = 0, int RND = 0>
 __device__ __forceinline__ void bj_mul(const BJ<S>& dinv, int e, const BJRows<S, VEC, BS>& R,
                                        bool valid, const C (&r)[VEC], C (&z)[VEC]) {
-  if constexpr (AD == 2 && BS <= VEC) {
-    bj_table_mul<C, S, VEC, BS, RND>(dinv, e, valid, r, z);
+  if constexpr (AD >= 2 && BS <= VEC) {
+    bj_table_mul<C, S, VEC, BS, AD, RND>(dinv, e, valid, r, z);
     return;
   }
   if (AD == 1 && dinv.mode == 4 && R.late) {
@@ -1142,8 +1146,8 @@ __device__ __forceinline__ void bj_mul(const BJRows<S, VEC, BS>& R, bool valid, 
 template <typename C, typename S, int VEC, int BS, int AD, int RND>
 __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool valid,
                                               const C (&r)[VEC], C (&z)[VEC]) {
-  if constexpr (AD == 2 && BS <= VEC) {
-    bj_table_mul<C, S, VEC, BS, RND>(dinv, e, valid, r, z);
+  if constexpr (AD >= 2 && BS <= VEC) {
+    bj_table_mul<C, S, VEC, BS, AD, RND>(dinv, e, valid, r, z);
     return;
   }
   C rb[BS > VEC ? BS : 1];
@@ -1171,7 +1175,7 @@ __device__ __forceinline__ void bj_apply_lane(const BJ<S>& dinv, int e, bool val
     return;
   }
   size_t off[VEC];
-  if constexpr (AD == 2) {
+  if constexpr (AD >= 2) {
     const int slot = valid ? bj_slot_of<BS>(dinv.mode, e & ~(BS - 1), dinv.nx, dinv.N, dinv.dx) : 0;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) off[i] = ((size_t)slot * BS + (e & (BS - 1)) + i) * BS;

@@ -113,7 +113,7 @@ struct mprk_handle {
     bool table() const { return mode == 1 || mode == 2 || mode == 5 || mode == 6; }  // slots hold distinct inverses
     size_t o_inv = 0, o_reps = 0, o_idx = 0, o_tag = 0, o_aoff = 0;
     std::vector<int> reps; // representative block of each slot (modes 1, 2, 5, 6)
-    std::vector<int> idx;  // slot of each block (mode 1)
+    std::vector<int> idx;  // slot of each block, of whole groups of vec_lp rows (mode 1)
     std::vector<int> tag;  // mode 4: storage type of each chunk (0 FP8 E4M3, 1 FP16, 2 FP32, 3 FP64)
     std::vector<long long> aoff;  // mode 4: byte offset of each chunk in the inverse area
   };
