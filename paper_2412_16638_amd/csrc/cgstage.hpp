@@ -91,17 +91,7 @@ template <typename S, typename C, int BS, bool many>
 __global__ __launch_bounds__(TPB, STAGE_WGS_PER_CU) void k_cg_stage(
     StagePlan pl, Geo geo, Coef<double> K, double* y, const double* __restrict__ rhs, double* kout, S* z,
     BJ<S> dinv, FTerms fx, SolveCfg cfg, Ctl* ctl, double* part, int slot) {
-  // the stage's record for the host (one thread)
-  auto keep_record = [&]() {
-    const long long* head = reinterpret_cast<const long long*>(ctl);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ctl->srec[slot][i] = head[i];
-  };
-  if (many && ctl->bar.error) return;  // a stage of this call timed out (the host starts it again)
-  if (ctl->outer_done) {  // (a halted call: uniform over the grid, written before the launch)
-    if (blockIdx.x == 0 && threadIdx.x == 0 && slot < MAXSTG) keep_record();
-    return;
-  }
+  if (ctl->outer_done) return;  // (a halted call: uniform over the grid, written before the launch)
   constexpr int VEC = 4, T = TPB;
   extern __shared__ double stage_lds[];
   double* yl = stage_lds;
@@ -301,7 +291,11 @@ __global__ __launch_bounds__(TPB, STAGE_WGS_PER_CU) void k_cg_stage(
       __syncthreads();
     }
   }
-  if (lead && slot < MAXSTG) keep_record();
+  if (lead && slot < MAXSTG) {
+    const long long* head = reinterpret_cast<const long long*>(ctl);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ctl->srec[slot][i] = head[i];
+  }
 }
 
 }  // namespace mprk

@@ -249,8 +249,6 @@ __device__ __forceinline__ void group_exchange(const double (&v)[ND], unsigned l
         __hip_atomic_store(&bar->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;
       }
-      // (where another workgroup has timed out the rest need not)
-      if ((spins & 1023) == 1023 && load_u32_dev((const unsigned*)&bar->error) != 0) break;
       if (wait) {
         bool all = true;
 #pragma unroll

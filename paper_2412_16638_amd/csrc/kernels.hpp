@@ -47,6 +47,7 @@ struct CombArgs {
   double pc2;
   unsigned long long* empty;  // slots of the one-launch stage that follows, emptied here
   int nempty;
+  long long* rec;  // that stage's record, cleared here: a halted stage leaves it so
 };
 
 // ------------------------------------------------------------------------------------------
@@ -55,8 +56,8 @@ struct CombArgs {
 
 // rhs = u + sum_j c_j v_j ; y = rhs, or rhs + pc pv with a start value pv.  reset: RESET_STAGE
 // clears the stage record, RESET_STEP also the step's gating flags, RESET_CALL the strict halt of
-// an earlier call.  A halted call opens every later stage finished, so its solve kernels return
-// at once.
+// an earlier call.  A halted call, and one with a one-launch stage that timed out, opens every later
+// stage finished, so its solve kernels return at once.
 template <int VEC, int FL>
 __global__ __launch_bounds__(TPB) void k_stage_rhs(Launch ln, const double* __restrict__ u,
                                                    CombArgs a, double* __restrict__ rhs,
@@ -64,9 +65,10 @@ __global__ __launch_bounds__(TPB) void k_stage_rhs(Launch ln, const double* __re
   count_work(ctl, KC_STAGE_RHS);
   if (a.empty && blockIdx.x == 0)
     for (int i = threadIdx.x; i < a.nempty; i += TPB) a.empty[i] = GRP_EMPTY;
+  if (a.rec && blockIdx.x == 0 && threadIdx.x < 8) a.rec[threadIdx.x] = 0;
   if (reset && blockIdx.x == 0 && threadIdx.x == 0) {
     if (reset & RESET_CALL) ctl->halt = 0;
-    ctl->outer_done = ctl->halt;
+    ctl->outer_done = ctl->halt | ctl->bar.error;
     ctl->inner_done = 0;
     ctl->passes = 0;
     ctl->iters = 0;

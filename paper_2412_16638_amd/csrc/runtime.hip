@@ -882,9 +882,12 @@ int mprk_handle::drop_one_launch() {
   return MPRK_OK;
 }
 
-// The exchange slots the stage's launch expects empty.
-void mprk_handle::stage_slots(CombArgs& a) const {
-  if (!one_launch() || stage_plan.nwg == 1) return;
+// What a one-launch stage expects of the launch before it: empty exchange slots, a cleared record.
+void mprk_handle::stage_slots(CombArgs& a, int slot) const {
+  if (!one_launch()) return;
+  // (strict, which captured steps are, is what skips a stage)
+  if ((prec.strict || capturing) && slot < MAXSTG) a.rec = ((Ctl*)(ws + o_ctl))->srec[slot];
+  if (stage_plan.nwg == 1) return;
   a.empty = (unsigned long long*)(ws + o_part);
   a.nempty = 3 * GRP_ND * stage_plan.nwg;
 }
@@ -1254,7 +1257,7 @@ int mprk_handle::launch_residual(const SolveCfg& cfg, const double* rhs, double*
   else if (zm_lz > 0)  // (zm_lz > 0 implies groups within x-rows)
     PLAUNCH(KC_RESIDUAL, (k_residual_zm<4>), dim3(zl_res.G), dim3(TPB), zmarch_lds(geo, zl_res, 8), stream,
             zl_res, geo, Kc, y, rhs, kout, res, fx, cfg, ctl, rd);
-  else if (vec_lp == 1)  // (the FP64 groups of four have the same trips)
+  else if (vec_lp == 1 && (N <= 1 << 14 || N > 1 << 16))  // (FP64 groups of four have the same trips)
     PLAUNCH(KC_RESIDUAL, (k_residual<1, 0, 0>), dim3(ln_row_red.G), dim3(TPB), 0, stream, ln_row_red, geo, Kc, csr,
                        kval, y, rhs, kout, res, fx, cfg, ctl, rd);
   else if (!flat)
@@ -1422,7 +1425,7 @@ int mprk_handle::enqueue_step(bool first_of_call) {
   for (int i = 0; i < s; ++i) {
     CombArgs a{};
     a.nv = 0;
-    stage_slots(a);
+    stage_slots(a, i);
     for (int j = 0; j < i; ++j) {
       const double ah = tab.a_hi[i * s + j], al = tab.a_lo[i * s + j];
       if (!implicit_[j]) {  // f^eps = f for an explicit stage
@@ -1840,7 +1843,7 @@ extern "C" int32_t mprk_solve(mprk_handle* h, int32_t stage, const double* rhs_d
     int rc = gate.step([&]() -> int {
       CombArgs a{};
       a.nv = 0;
-      h->stage_slots(a);
+      h->stage_slots(a, MPRK_MAX_STAGES);
       // x = rhs (initial guess), rhs copy into the workspace; resets the stage record
       if (!h->flat)
         hipLaunchKernelGGL((k_stage_rhs<4, 0>), dim3(h->ln_vec.G), dim3(TPB), 0, h->stream, h->ln_vec, b, a, rhs,

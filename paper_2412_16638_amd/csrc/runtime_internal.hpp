@@ -199,7 +199,7 @@ struct mprk_handle {
   void plan_one_launch(bool cb);
   bool stage_fits_device();
   int drop_one_launch();
-  void stage_slots(mprk::CombArgs& a) const;
+  void stage_slots(mprk::CombArgs& a, int slot) const;
   int make_device_resources();
   mprk::EngineCtx ctx() const;
   int poll_enqueue(int* slot);
