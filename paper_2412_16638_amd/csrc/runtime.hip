@@ -664,151 +664,159 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   } else {
     kscale = 1.0;
   }
-  // layout
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    size_t o2 = off;
-    off += align256(bytes);
-    return o2;
-  };
-  const size_t v64 = (size_t)N * 8;
-  const size_t vlp = align256((size_t)N * lp_bytes);
-  o_rhs = take(v64);
-  o_y = take(v64);
-  o_res = take(v64);
-  kstride = flat ? (v64 + 127) & ~(size_t)127 : v64;  // (flat groups: every vector starts on a cache line)
-  o_k = take(kstride * nstages);
-  o_keps = need_keps ? take(kstride * nstages) : 0;
-  o_scr = take(v64);  // scratch FP64 vector (solve output of k, verification)
-  fdm = p.precond == MPRK_PRECOND_FDM;
-  // the fast-diagonalisation inverse is exact for the operators it accepts: one Krylov iteration
-  // per pass, so no predicted iteration beyond the last solve's count
-  predict_margin = fdm ? 0 : 1;
-  // the start value of the stage solves (the automatic choice follows what saved outer passes):
-  // with GMRES the previous stage's slope, and under the FDM preconditioner, whose passes reduce
-  // the residual furthest, also the first stage from f(u); with CG (symmetric, diffusion
-  // operators) the slopes extrapolated linearly in c, which the previous slope alone did not
-  // make close enough; the FDM-preconditioned CG already needs one pass, and the one-solve
-  // mode's result would depend on the start value
-  start_mode = p.stage_start;
-  if (start_mode == MPRK_START_AUTO) {
-    start_mode = MPRK_START_RHS;
-    if (p.refine_max > 0 && p.krylov == MPRK_GMRES)
-      start_mode = fdm ? MPRK_START_SLOPE_EVAL : MPRK_START_SLOPE;
-    else if (p.refine_max > 0 && !fdm)
-      start_mode = MPRK_START_EXTRAP;
-  }
-  start_slope = start_mode >= MPRK_START_SLOPE;
-  start_eval = start_mode == MPRK_START_SLOPE_EVAL || start_mode == MPRK_START_EXTRAP;
-  start_first_eval = start_mode == MPRK_START_SLOPE_EVAL;
-  start_extrap = start_mode == MPRK_START_EXTRAP;
-  if (p.krylov == MPRK_CG) {
-    o_r = take(vlp);
-    o_z = (bs || fdm) ? take(vlp) : o_r;
-    o_p0 = take(vlp);
-    o_p1 = take(vlp);
-    o_q = take(vlp);
-    o_x = take(vlp);
-    o_V = 0;
-  } else {
-    o_V = take(vlp * (size_t)(p.restart + 1));
-    // (with the stored directions below, the tiled forms alone read z)
-    o_z = fdm || (bs && gform_ok != 1) ? take(vlp) : 0;
-    // the stored preconditioned directions BJ(V_0) .. BJ(V_m) of the gather form
-    o_Zb = (bs && !fdm) ? take(vlp * (size_t)(p.restart + 1)) : 0;
-    o_r = o_p0 = o_p1 = o_q = o_x = 0;
-    if (gform_ok & 4) {  // folded form: products alternate between W0 and W1 (W1 reuses BJ(V_0)'s)
-      o_w0 = take(vlp);
-      o_w1 = bs ? o_z : take(vlp);
+  // layout.  A workspace a little past the library's static scratch is laid out again without the
+  // room that its kernels do not use, so that flat groups, whose padding adds up to some 13 KB, do
+  // not keep a problem out that fitted.  (Not everywhere: with the partials cut to CG's 4 values a
+  // heat step of 128^3 in FP32 takes 3925 us, with room for 34 it takes 3880.)
+  auto lay_out = [&](bool tight) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      size_t o2 = off;
+      off += align256(bytes);
+      return o2;
+    };
+    const size_t v64 = (size_t)N * 8;
+    const size_t vlp = align256((size_t)N * lp_bytes);
+    o_rhs = take(v64);
+    o_y = take(v64);
+    o_res = take(v64);
+    kstride = flat ? align256(v64) : v64;  // (flat groups: every vector starts on a group)
+    o_k = take(kstride * nstages);
+    o_keps = need_keps ? take(kstride * nstages) : 0;
+    o_scr = take(v64);  // scratch FP64 vector (solve output of k, verification)
+    fdm = p.precond == MPRK_PRECOND_FDM;
+    // the fast-diagonalisation inverse is exact for the operators it accepts: one Krylov iteration
+    // per pass, so no predicted iteration beyond the last solve's count
+    predict_margin = fdm ? 0 : 1;
+    // the start value of the stage solves (the automatic choice follows what saved outer passes):
+    // with GMRES the previous stage's slope, and under the FDM preconditioner, whose passes reduce
+    // the residual furthest, also the first stage from f(u); with CG (symmetric, diffusion
+    // operators) the slopes extrapolated linearly in c, which the previous slope alone did not
+    // make close enough; the FDM-preconditioned CG already needs one pass, and the one-solve
+    // mode's result would depend on the start value
+    start_mode = p.stage_start;
+    if (start_mode == MPRK_START_AUTO) {
+      start_mode = MPRK_START_RHS;
+      if (p.refine_max > 0 && p.krylov == MPRK_GMRES)
+        start_mode = fdm ? MPRK_START_SLOPE_EVAL : MPRK_START_SLOPE;
+      else if (p.refine_max > 0 && !fdm)
+        start_mode = MPRK_START_EXTRAP;
     }
-  }
-  vstride = vlp / lp_bytes;
-  plan_one_launch(cb);
-  bjsets.assign(bs ? sigmas.size() : 0, BJSet());
-  for (size_t q = 0; q < bjsets.size(); ++q) {
-    BJSet& B = bjsets[q];
-    // the matrix-free operator's blocks come from a table of its distinct ones, whose slots
-    // follow from the row number (no pass over the blocks): every block alike when bs | nx, else
-    // one slot per place where an x-row can end inside a block (nx > bs, so that at most one does)
-    // (FP16 CG on groups of 4 keeps one inverse per block: the rounding of its update is the
-    // compiler's choice there and would move with the kernel)
-    const bool own = p.storage == MPRK_FP16 && p.compute == MPRK_FP32 && p.krylov == MPRK_CG && vec_lp == 4;
-    if (o.format == MPRK_FMT_STENCIL && !(p.bj_adapt_tol > 0.0) && !own && (g.nx % bs == 0 || g.nx > bs)) {
-      B.mode = g.nx % bs == 0 ? 6 : 5;
-      bj_table_reps(geo, bs, B.mode, B.reps);
-      B.nslot = (int)B.reps.size();
-    } else if (p.bj_shared) {
-      bj_dedup(geo, Kc, sigmas[q], bs, B.reps, B.idx);
-      B.nslot = (int)B.reps.size();
-      B.mode = B.nslot == 1 ? 2 : 1;
-      if (B.mode == 2) B.idx.clear();
-      // (the last lane looks up whole groups of vec_lp rows; those past the last block take its slot,
-      // their inputs are zero)
-      else B.idx.resize(((size_t)(N + vec_lp - 1) / vec_lp * vec_lp + bs - 1) / bs, B.idx.back());
+    start_slope = start_mode >= MPRK_START_SLOPE;
+    start_eval = start_mode == MPRK_START_SLOPE_EVAL || start_mode == MPRK_START_EXTRAP;
+    start_first_eval = start_mode == MPRK_START_SLOPE_EVAL;
+    start_extrap = start_mode == MPRK_START_EXTRAP;
+    if (p.krylov == MPRK_CG) {
+      o_r = take(vlp);
+      o_z = (bs || fdm) ? take(vlp) : o_r;
+      o_p0 = take(vlp);
+      o_p1 = take(vlp);
+      o_q = take(vlp);
+      o_x = take(vlp);
+      o_V = 0;
     } else {
-      B.nslot = nblk;
-      B.mode = p.bj_adapt_tol > 0.0 ? 4 : 3;  // rows interleaved for lanes of vec_lp rows
-    }
-    if (B.mode == 4) {
-      bj_adaptive_layout(geo, Kc, sigmas[q], bs, vec_ad, p.bj_adapt_tol, B.tag, B.aoff);
-      B.o_inv = take((size_t)B.aoff.back());
-      B.aoff.pop_back();
-      B.o_tag = take(B.tag.size() * 4);
-      B.o_aoff = take(B.aoff.size() * 8);
-      continue;
-    }
-    // (bj_shared = 0 keeps its documented footprint, one inverse per block, in every format)
-    const int lanes = B.mode == 3 || !flat_lp ? vec_lp : 1;
-    const size_t rows = B.mode == 3 || !p.bj_shared
-                            ? std::max({(size_t)nblk * bs, bj_chunks((long)nblk * bs, lanes),
-                                        (size_t)B.nslot * bs})
-                            : (size_t)B.nslot * bs;
-    B.o_inv = take(rows * bs * lp_bytes);
-    // (the slots' rows go behind the table where that footprint has room)
-    const size_t used = align256((size_t)B.nslot * bs * bs * lp_bytes);
-    if (B.table())
-      B.o_reps = used + (size_t)B.nslot * 4 <= rows * bs * lp_bytes ? B.o_inv + used : take((size_t)B.nslot * 4);
-    if (B.mode == 1) B.o_idx = take(B.idx.size() * 4);
-  }
-  if (o.format == MPRK_FMT_CSR) {
-    o_rowptr = take((size_t)(N + 1) * 4);
-    o_col = take((size_t)nnz * 4);
-    o_kval = take((size_t)nnz * 8);
-    o_mval = take((size_t)nnz * lp_bytes);
-  }
-  fdm_cx = fdm && o.kind != MPRK_OP_HEAT;
-  if (fdm) {
-    const size_t cb = p.compute == MPRK_FP64 ? 8 : 4;
-    const int n3[3] = {g.nx, g.ny, g.nz};
-    for (int d = 0; d < 3; ++d) {
-      o_fdm_Q[d] = take((size_t)n3[d] * fdm_ldq(n3[d]) * cb);  // rows padded to fdm_ldq
-      o_fdm_lam[d] = take((size_t)n3[d] * 8);
-      if (fdm_cx) {
-        o_fdm_Qi[d] = take((size_t)n3[d] * fdm_ldq(n3[d]) * cb);
-        o_fdm_lami[d] = take((size_t)n3[d] * 8);
+      o_V = take(vlp * (size_t)(p.restart + 1));
+      // (with the stored directions below, the tiled forms alone read z)
+      o_z = fdm || (bs && !(tight && gform_ok == 1)) ? take(vlp) : 0;
+      // the stored preconditioned directions BJ(V_0) .. BJ(V_m) of the gather form
+      o_Zb = (bs && !fdm) ? take(vlp * (size_t)(p.restart + 1)) : 0;
+      o_r = o_p0 = o_p1 = o_q = o_x = 0;
+      if (gform_ok & 4) {  // folded form: products alternate between W0 and W1 (W1 reuses BJ(V_0)'s)
+        o_w0 = take(vlp);
+        o_w1 = bs ? o_z : take(vlp);
       }
     }
-    for (int k = 0; k < 2; ++k) {
-      o_fdm_t[k] = take((size_t)N * cb);
-      if (fdm_cx) o_fdm_ti[k] = take((size_t)N * cb);
+    vstride = vlp / lp_bytes;
+    plan_one_launch(cb);
+    bjsets.assign(bs ? sigmas.size() : 0, BJSet());
+    for (size_t q = 0; q < bjsets.size(); ++q) {
+      BJSet& B = bjsets[q];
+      // the matrix-free operator's blocks come from a table of its distinct ones, whose slots
+      // follow from the row number (no pass over the blocks): every block alike when bs | nx, else
+      // one slot per place where an x-row can end inside a block (nx > bs, so that at most one does)
+      // (FP16 CG on groups of 4 keeps one inverse per block: the rounding of its update is the
+      // compiler's choice there and would move with the kernel)
+      const bool own = p.storage == MPRK_FP16 && p.compute == MPRK_FP32 && p.krylov == MPRK_CG && vec_lp == 4;
+      if (o.format == MPRK_FMT_STENCIL && !(p.bj_adapt_tol > 0.0) && !own && (g.nx % bs == 0 || g.nx > bs)) {
+        B.mode = g.nx % bs == 0 ? 6 : 5;
+        bj_table_reps(geo, bs, B.mode, B.reps);
+        B.nslot = (int)B.reps.size();
+      } else if (p.bj_shared) {
+        bj_dedup(geo, Kc, sigmas[q], bs, B.reps, B.idx);
+        B.nslot = (int)B.reps.size();
+        B.mode = B.nslot == 1 ? 2 : 1;
+        if (B.mode == 2) B.idx.clear();
+        // (the last lane looks up whole groups of vec_lp rows; those past the last block take its slot,
+        // their inputs are zero)
+        else B.idx.resize(((size_t)(N + vec_lp - 1) / vec_lp * vec_lp + bs - 1) / bs, B.idx.back());
+      } else {
+        B.nslot = nblk;
+        B.mode = p.bj_adapt_tol > 0.0 ? 4 : 3;  // rows interleaved for lanes of vec_lp rows
+      }
+      if (B.mode == 4) {
+        bj_adaptive_layout(geo, Kc, sigmas[q], bs, vec_ad, p.bj_adapt_tol, B.tag, B.aoff);
+        B.o_inv = take((size_t)B.aoff.back());
+        B.aoff.pop_back();
+        B.o_tag = take(B.tag.size() * 4);
+        B.o_aoff = take(B.aoff.size() * 8);
+        continue;
+      }
+      // (bj_shared = 0 keeps its documented footprint, one inverse per block, in every format)
+      const int lanes = tight && B.mode != 3 && flat_lp ? 1 : vec_lp;
+      const size_t rows = B.mode == 3 || !p.bj_shared
+                              ? std::max({(size_t)nblk * bs, bj_chunks((long)nblk * bs, lanes),
+                                          (size_t)B.nslot * bs})
+                              : (size_t)B.nslot * bs;
+      B.o_inv = take(rows * bs * lp_bytes);
+      // (the slots' rows go behind the table where that footprint has room)
+      const size_t used = align256((size_t)B.nslot * bs * bs * lp_bytes);
+      if (B.table())
+        B.o_reps = used + (size_t)B.nslot * 4 <= rows * bs * lp_bytes ? B.o_inv + used : take((size_t)B.nslot * 4);
+      if (B.mode == 1) B.o_idx = take(B.idx.size() * 4);
     }
-    // real data: x frequencies 0 .. nx/2 suffice (rounded up to 4 for aligned rows; needs nx >= 4)
-    const int H = (g.nx / 2 + 1 + 3) & ~3;
-    fdm_half = fdm_cx && H <= g.nx ? H : 0;
-    if (fdm_half)
-      for (int k = 0; k < 2; ++k) o_fdm_Qw[k] = take((size_t)g.nx * fdm_ldq(g.nx) * cb);
+    if (o.format == MPRK_FMT_CSR) {
+      o_rowptr = take((size_t)(N + 1) * 4);
+      o_col = take((size_t)nnz * 4);
+      o_kval = take((size_t)nnz * 8);
+      o_mval = take((size_t)nnz * lp_bytes);
+    }
+    fdm_cx = fdm && o.kind != MPRK_OP_HEAT;
+    if (fdm) {
+      const size_t cb = p.compute == MPRK_FP64 ? 8 : 4;
+      const int n3[3] = {g.nx, g.ny, g.nz};
+      for (int d = 0; d < 3; ++d) {
+        o_fdm_Q[d] = take((size_t)n3[d] * fdm_ldq(n3[d]) * cb);  // rows padded to fdm_ldq
+        o_fdm_lam[d] = take((size_t)n3[d] * 8);
+        if (fdm_cx) {
+          o_fdm_Qi[d] = take((size_t)n3[d] * fdm_ldq(n3[d]) * cb);
+          o_fdm_lami[d] = take((size_t)n3[d] * 8);
+        }
+      }
+      for (int k = 0; k < 2; ++k) {
+        o_fdm_t[k] = take((size_t)N * cb);
+        if (fdm_cx) o_fdm_ti[k] = take((size_t)N * cb);
+      }
+      // real data: x frequencies 0 .. nx/2 suffice (rounded up to 4 for aligned rows; needs nx >= 4)
+      const int H = (g.nx / 2 + 1 + 3) & ~3;
+      fdm_half = fdm_cx && H <= g.nx ? H : 0;
+      if (fdm_half)
+        for (int k = 0; k < 2; ++k) o_fdm_Qw[k] = take((size_t)g.nx * fdm_ldq(g.nx) * cb);
+    }
+    o_ctl = take(sizeof(Ctl));
+    o_flag = take(256);
+    // values of one reduction: one per basis vector and, in the tiled forms, two norms
+    const size_t nred = !tight ? MAXRED : p.krylov == MPRK_CG ? 4 : std::max(4, p.restart + (gform_ok == 1 ? 1 : 2));
+    o_part = take(nred * pstride * 8);
+    o_part2 = take(nred * pstride2 * 8);
+    o_tick = take(red_ticks(pstride) * 4);
+    return off;
+  };
+  constexpr size_t scratch = MPRK_STATIC_SCRATCH_BYTES;
+  ws_bytes = lay_out(false);
+  if (flat && ws_bytes > scratch && ws_bytes <= scratch + (256 << 10)) {
+    ws_bytes = lay_out(true);
+    if (ws_bytes > scratch) ws_bytes = lay_out(false);
   }
-  o_ctl = take(sizeof(Ctl));
-  o_flag = take(256);
-  // values of one reduction: on flat grids, whose slope vectors are padded, no more than the problem's
-  // kernels reduce (the residual's three; in GMRES one per basis vector; the exchange slots of a
-  // one-launch stage, 12 a workgroup of up to 1024 unknowns, fit too).  Elsewhere room for the largest
-  // problem's: with the smaller array a heat step of 128^3 in FP32 takes 3925 us, with it 3880.
-  const size_t nred = !flat ? MAXRED : p.krylov == MPRK_CG ? 4 : std::max(4, p.restart + 1);
-  o_part = take(nred * pstride * 8);
-  o_part2 = take(nred * pstride2 * 8);
-  o_tick = take(red_ticks(pstride) * 4);
-  ws_bytes = off;
   // per-sigma solve configurations
   cfgs.clear();
   for (double sg : sigmas) {
