@@ -329,6 +329,12 @@ int32_t mprk_set_reaction(mprk_handle *h, double r1, double r2, double r3);
  * small device-side status records; all arithmetic runs in the library's kernels on the
  * bound stream.  The call waits for the stream before it returns (it reads the device's step
  * and convergence counters) and fills stats_or_null if given.
+ * A small CG problem (FP64 or FP32 with its own arithmetic, matrix-free, at most 128 x 1024
+ * unknowns) runs each stage as one launch whose workgroups wait for each other.  Calls of several
+ * threads whose workgroups do not fit the device together enter in the order they came and take
+ * turns; batches are ordered among them on the device.  Should such a wait time out all the same
+ * (other processes on the device), the call runs the steps concerned again on the per-kernel
+ * path, which the handle then keeps until the next bind.
  * Errors: MPRK_ESTATE (not bound), MPRK_ENONFINITE (u left at the last good step),
  * MPRK_ENOTCONV (strict only), MPRK_EDEVICE. */
 int32_t mprk_step(mprk_handle *h, int32_t nsteps, mprk_stats *stats_or_null);
@@ -389,7 +395,9 @@ enum { MPRK_KC_STAGE_RHS = 0, MPRK_KC_RESIDUAL, MPRK_KC_CG_BEGIN, MPRK_KC_CG_DIR
 
 /* Per-kernel timing.  enable = 1 waits for the stream, clears the records and starts
  * recording a HIP event immediately before and after every kernel the handle launches (on its
- * stream); enable = 0 stops recording (records are kept for mprk_profile_read). */
+ * stream); enable = 0 stops recording (records are kept for mprk_profile_read).  A small CG
+ * problem whose stages run as one launch each takes the per-kernel path meanwhile, so its classes
+ * are those of that path. */
 int32_t mprk_profile(mprk_handle *h, int32_t enable);
 
 /* Waits for the stream and returns, for kernel class `kclass` since the last mprk_profile(h, 1):

@@ -8,11 +8,12 @@
 // iteration costs two exchanges and one read of z, and the host waits once per call.  Each
 // workgroup keeps its part of x, r and q in registers, and the search direction on its part and
 // the planes beside it in LDS, where p = z + beta p is formed again from z, so z is all that
-// travels.  Three workgroups to a CU (168 registers), so that 192 of them always find room beside
-// a batched step's two.
+// travels.  Three workgroups to a CU by registers (FP32 117 to 131, FP64 140 to 168) and LDS; gate.hpp
+// keeps what waits for each other within what the device holds.
 //
-// A step of heat with SDIRK3 and block-Jacobi (8), per-kernel path -> here: FP32
-// 16^3 569 -> 239 us, 37^3 820 -> 571, 50^3 1056 -> 778; FP64 27^3 924 -> 653, 50^3 1371 -> 1125.
+// A step of heat with SDIRK3 and block-Jacobi (8), per-kernel path -> here: FP32 8^3 440 -> 105 us,
+// 16^3 505 -> 200, 37^3 840 -> 545, 50^3 1020 -> 740; FP64 8^3 465 -> 120, 27^3 875 -> 640,
+// 50^3 1380 -> 1130.
 // With a counter barrier, p and q in memory and caches invalidated at each barrier 37^3 took 902.
 #pragma once
 
@@ -176,7 +177,8 @@ __global__ __launch_bounds__(TPB, STAGE_WGS_PER_CU) void k_cg_stage(
     double a2[2] = {0.0, 0.0};
     // z = BJ(r) (r itself without one), its part of (r, z) and (r, r).  (A thread's rows of the
     // inverse and its neighbours' places are the same in every iteration, but kept over the loop
-    // they spill: the opaque copies have each iteration form them again.)
+    // they spill: the opaque copies have each iteration form them again.  FP64 with blocks of 8 spills
+    // 10 to 12 registers all the same.)
     auto precondition = [&]() {
       C zv[VEC];
       if constexpr (BS > 0) {

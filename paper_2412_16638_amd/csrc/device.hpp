@@ -404,7 +404,8 @@ __device__ __forceinline__ double load_dev(const double* p) {
 // Grid reduction of nd (<= ND <= 64) per-thread values in fixed order: wave64 shuffle tree,
 // block sum over the waves, one partial per block; the last block of each group of RGRP blocks
 // sums the group's partials (one wave, lane = block within the group); the last group to finish
-// sums the group sums (a grid of one group, at most RGRP blocks, is done after the first level).  Returns true in that final block, where tot[0..nd) (shared memory)
+// sums the group sums (a grid of one group, at most RGRP blocks, is done after the first level).
+// Returns true in that final block, where tot[0..nd) (shared memory)
 // holds the totals.  The order of every addition depends only on G and the block indices, so
 // results are bitwise reproducible for a given launch shape.
 template <int ND>

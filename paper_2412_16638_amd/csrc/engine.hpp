@@ -65,7 +65,7 @@ struct EngineCtx {
   hipStream_t stream;
   Geo geo;
   int fmt;            // 0 stencil, 1 CSR
-  int vec;            // values per group of the LP kernels: 8 or 4
+  int vec;            // values per group of the LP kernels: 8, 4, or 1 (some flat grids)
   int flat;           // groups are flat (vec does not divide nx)
   Launch ln_vec;      // groups of `vec` elements (streaming kernels)
   Launch ln_row;      // CSR rows (VEC = 1)

@@ -610,7 +610,7 @@ __global__ __launch_bounds__(TPB) void k_cg_dir(Launch ln, Geo geo, Coef<C> M, C
     if (g >= ln.ng) break;
     C p[VEC], w[VEC];
     mlp_group<S, C, VEC, FMT, FL>(geo, M, msig, g, csum, f, p, w);
-    if constexpr (FL) {  // (zero past the end: the vectors are padded)
+    if constexpr (FL) {  // (stencil: zero past the end, the vectors are padded; CSR has rows alone)
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
         w[v] = rnd<S, C>(w[v]);

@@ -448,7 +448,6 @@ extern "C" int32_t mprk_precisions_default(int32_t storage, int32_t krylov, mprk
 // create / layout
 // ------------------------------------------------------------------------------------------
 
-
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 static int validate(const mprk_grid* g, const mprk_operator* op, const mprk_tableau* tab,
@@ -840,9 +839,9 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
 }
 
 // Small CG problems on the matrix-free stencil run each stage as one launch (cgstage.hpp): faster
-// at every size it holds (a step of 8^3 FP32 131 us, 50^3 742 against 1056), so the line lies where
-// its workgroups or their LDS end.  Not FP16 storage: its per-kernel path adds the products of a group in FP32 on even grids, and the
-// two forms would round differently.
+// at every size it holds (a step of FP32 heat of 8^3 105 us against 440, of 50^3 740 against 1020), so
+// the line lies where its workgroups or their LDS end.  Not FP16 storage: its per-kernel path adds the
+// products of a group in FP32 on even grids, and the two forms would round differently.
 void mprk_handle::plan_one_launch(bool cb) {
   stage_plan = StagePlan{0, 0, 0};
   if (prec.krylov != MPRK_CG || op.format != MPRK_FMT_STENCIL || fdm || cb ||

@@ -58,7 +58,8 @@ struct mprk_handle {
   mprk::Geo geo{};
   int N = 0;
   // values per group of the FP64 kernels (4) and of the LP kernels (8 for FP16 storage unless
-  // nx % 8 == 4, else 4), and whether those groups are flat (the width does not divide nx)
+  // nx % 8 == 4, else 4; 1 on some flat grids, see init), and whether those groups are flat (the width
+  // does not divide nx)
   int vec = 4, vec_lp = 4;
   int flat = 0, flat_lp = 0;
   int vec_ad = 1;   // rows per lane of the adaptive block-Jacobi layout (8, 4, or 1 if flat)
