@@ -127,7 +127,8 @@ def fdm_apply_flops(p) -> float:
     (periodic advection, real data): the x transforms keep H = nx/2 + 1 frequencies rounded up
     to 4 (all nx below nx = 4); forward x real x complex (4 H), y and z forward and back complex x
     complex on H of nx x-slices (8 n H / nx each), backward x only the real part (4 H).  The
-    kernels execute 3 real products per complex one in the middle four, 3/4 of their count."""
+    kernels fold the middle four by the DFT's symmetry and execute about a quarter of their
+    count (fdm_executed_share)."""
     n = p.n
     if p.kind == 0:
         return 4.0 * 3 * n
@@ -135,6 +136,16 @@ def fdm_apply_flops(p) -> float:
     if H > n:
         H = n
     return 8.0 * H + 16.0 * (n + n) * H / n
+
+
+def fdm_executed_share(p) -> float:
+    """Share of fdm_apply_flops that the kernels execute: all of the real and the x contractions;
+    four real products of (n/2 + 1)^2 in place of four of n^2 in a folded y or z contraction."""
+    if p.kind == 0:
+        return 1.0
+    total = fdm_apply_flops(p)
+    x = 8.0 * min((p.n // 2 + 1 + 3) & ~3, p.n)
+    return (x + (total - x) * ((p.n // 2 + 1) / p.n) ** 2) / total
 
 
 def workload_name(args) -> str:
@@ -512,6 +523,7 @@ def main():
         peak = MFMA_PEAK['fp64' if args.compute == 'fp64' else p.precision]
         roofline = {'bound': 'mfma', 'kernel': kc, 'achieved': round(achieved, 2), 'peak': peak,
                     'unit': 'TFLOP/s', 'frac': round(achieved / peak, 4), 'traffic': None,
+                    'executed_share': round(fdm_executed_share(p), 4),
                     'flops_per_launch': flops_per_launch, 'avg_launch_us': round(avg_ms * 1e3, 2),
                     'launches': r['launches'], 'worked': r['worked']}
     else:
