@@ -683,7 +683,7 @@ struct mprk_batch {
   // of the last step; used by plan_groups while use_measured is set
   std::vector<double> measured_w;
   bool use_measured = false;
-  int ru = 4;                 // consecutive rows a thread handles together (1, 2, 4; FP16: rows, 2)
+  int ru = 4;                 // consecutive rows a thread handles together (1, 2, 4; FP16: rows)
   int capacity = 0;           // co-resident workgroups of the device for the kernel in use
   int cus = 0;                // compute units of the device
   int max_capacity = 0;       // largest capacity over the kernel variants (sizes the map)
@@ -783,7 +783,11 @@ extern "C" int32_t mprk_batch_create(int32_t count, const mprk_problem* problems
   b->probs.assign(problems, problems + count);
   b->tab = *tab;
   b->prec = *prec;
-  if (prec->storage == MPRK_FP16) b->ru = 2;
+  // FP64: groups of 2, whose 32-byte loads of a stencil group fit the registers of three workgroups a CU
+  // (ms a step, blocks of 8, one value per lane with a block's inverse each / groups of 4 / of 2: four
+  // problems of 20^3 to 60^3 5.03, 5.91, 5.01; three of 40^3 to 90^3 11.7, 13.1, 11.2; 64 of 24^3 to
+  // 48^3 12.4, 8.6, 7.0; 300 of 16^3 to 24^3, blocks of 2, 7.07, 7.70, 6.58)
+  if (prec->storage != MPRK_FP32) b->ru = 2;
   b->stream = (hipStream_t)hip_stream;
   for (int p = 0; p < count; ++p) {
     const mprk_problem& q = problems[p];
