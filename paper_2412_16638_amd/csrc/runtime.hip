@@ -580,6 +580,12 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   // An assembled matrix in FP64 keeps one value at every size: each lane would read four rows of the
   // per-block inverses (a heat step of 95^3 7.3 ms with one value, 9.6 with groups of four).
   if (flat_lp && o.format == MPRK_FMT_CSR && p.storage == MPRK_FP64) vec_lp = 1;
+  // FP64 arithmetic over FP16 storage: a group of eight holds sixteen registers a vector.  CG of 86^3
+  // takes 1480 us a step with one value, 2430 with groups of eight, 119^3 3475 and 4740; GMRES with
+  // blocks of 8 of 86^3 474 and 539, 119^3 849 and 885 (without a preconditioner 665 and 617).
+  if (flat_lp && p.storage == MPRK_FP16 && p.compute == MPRK_FP64 &&
+      (p.krylov == MPRK_CG || (o.format == MPRK_FMT_STENCIL && p.precond == MPRK_PRECOND_BJ && p.block > 2)))
+    vec_lp = 1;
   vec_ad = flat_lp ? 1 : vec_lp;
   Kc = operator_coef(g, o);
   // FP64 arithmetic over FP32 / FP16 storage: the compressed-basis variants

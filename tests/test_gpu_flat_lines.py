@@ -57,3 +57,23 @@ def test_operators_and_a_stage_solve(shape, storage):
         lim = st.prec.outer_tol * np.linalg.norm(rhs) + 32 * U[A.FP64] * np.linalg.norm(abs(Mx) @ np.abs(got))
         st.close()
         assert info['converged'] == 1 and np.linalg.norm(rhs - Mx @ got) <= lim, info
+
+
+@pytest.mark.parametrize("krylov_name", ['cg', 'gmres'])
+@pytest.mark.parametrize("over", [dict(precond='bj', block=8), dict(precond='bj', block=2), dict(precond='none')])
+@pytest.mark.parametrize("fmt", [A.FMT_STENCIL, A.FMT_CSR])
+def test_fp64_arithmetic_over_fp16_storage(krylov_name, over, fmt):
+    # past 2^19 unknowns, where FP16 takes groups of eight elsewhere; the stage system's residual test
+    shape = (83, 81, 79)
+    log_case('flat_lines_cb16', krylov=krylov_name, fmt=fmt, **over)
+    bc, kind, diff, b = ((W.DIRICHLET, W.HEAT, 1.5, (0.0, 0.0, 0.0)) if krylov_name == 'cg'
+                         else (W.PERIODIC, W.ADVDIFF, 0.3, (-1.0, 0.5, -0.25)))
+    st = M.Stepper(shape, bc, kind, diff, b, fmt, 'SDIRK3',
+                   M.precisions('fp16', krylov_name, compute=A.FP64, **over), 2e-4)
+    rhs = np.random.default_rng(8).standard_normal(st.N)
+    x, info = st.solve(0, torch.from_numpy(rhs).cuda())
+    Mx = operators.stage_matrix(operators.operator(shape, bc, kind, diff, b), st.dt * st.tab.a_lo[0])
+    got = x.cpu().numpy()
+    lim = st.prec.outer_tol * np.linalg.norm(rhs) + 32 * U[A.FP64] * np.linalg.norm(abs(Mx) @ np.abs(got))
+    st.close()
+    assert info['converged'] == 1 and np.linalg.norm(rhs - Mx @ got) <= lim, info
