@@ -564,27 +564,31 @@ int mprk_handle::init(const mprk_grid& g, const mprk_operator& o, const mprk_tab
   flat_lp = g.nx % vec_lp != 0;
   // A small grid of flat groups: one value per thread.  A wave whose groups cross a plane's edge makes
   // two trips to memory more, which few waves cannot hide.  CG: a heat step of 51^3 in FP16 873 us
-  // with groups of eight, 732 with one value, 75^3 1076 and 1067, 83^3 1216 and 1280; of 54^3 in FP32
-  // 1160 with groups of four, 1095 with one value, 75^3 1583 and 1618; in FP64 1667 and 1532, 2587
-  // and 2671.  GMRES with the stencil: an advection-diffusion step of 21^3 in FP16 310 us with groups
-  // of eight, 249 with one value, 54^3 352 and 322, 79^3 396 and 390, 87^3 421 and 430; in FP64 of
-  // 21^3 520 with groups of four, 431 with one value, 50^3 860 and 802, 66^3 1080 and 1047, 70^3 1104
-  // and 1121.  Between 2^14 and 2^16 unknowns groups of four are one group of a reduction's
-  // partials where single values are not (33^3 in FP64 645 and 677), so these keep them.
-  if (flat_lp && p.krylov == MPRK_CG && N <= (p.storage == MPRK_FP16 ? 1 << 19 : 3 << 17)) vec_lp = 1;
-  if (flat_lp && p.krylov == MPRK_GMRES && o.format == MPRK_FMT_STENCIL) {
-    if (p.storage == MPRK_FP16 ? N <= 1 << 19
-                               : N <= 1 << 14 || (N > 1 << 16 && N <= 5 << 16))
-      vec_lp = 1;
+  // with groups of eight, 732 with one value, 85^3 1350 and 1155, 89^3 1433 and 1359, 95^3 1481 and
+  // 1546; of 54^3 in FP32 1160 with groups of four, 1095 with one value, 75^3 1583 and 1618; in FP64
+  // 1667 and 1532, 2587 and 2671.  GMRES with the stencil: an advection-diffusion step of 21^3 in FP16
+  // 310 us with groups of eight, 249 with one value, 54^3 352 and 322, 79^3 396 and 390, 87^3 421 and
+  // 430 (with adaptive inverses 85^3 502 and 455); in FP64 of 21^3 520 with groups of four, 431 with
+  // one value, 50^3 860 and 802, 66^3 1080 and 1047, 70^3 1104 and 1121.  Between 2^14 and 2^16
+  // unknowns groups of four are one group of a reduction's partials where single values are not
+  // (33^3 in FP64 645 and 677), so these keep them.
+  const bool stencil = o.format == MPRK_FMT_STENCIL;
+  if (flat_lp && p.storage == MPRK_FP16) {
+    const bool far = p.krylov == MPRK_CG || (p.precond == MPRK_PRECOND_BJ && p.bj_adapt_tol > 0.0);
+    if ((p.krylov == MPRK_CG || stencil) && N <= (far ? 11 << 16 : 1 << 19)) vec_lp = 1;
+  } else if (flat_lp && p.krylov == MPRK_CG) {
+    if (N <= 3 << 17) vec_lp = 1;
+  } else if (flat_lp && stencil) {
+    if (N <= 1 << 14 || (N > 1 << 16 && N <= 5 << 16)) vec_lp = 1;
   }
   // An assembled matrix in FP64 keeps one value at every size: each lane would read four rows of the
   // per-block inverses (a heat step of 95^3 7.3 ms with one value, 9.6 with groups of four).
-  if (flat_lp && o.format == MPRK_FMT_CSR && p.storage == MPRK_FP64) vec_lp = 1;
+  if (flat_lp && !stencil && p.storage == MPRK_FP64) vec_lp = 1;
   // FP64 arithmetic over FP16 storage: a group of eight holds sixteen registers a vector.  CG of 86^3
   // takes 1480 us a step with one value, 2430 with groups of eight, 119^3 3475 and 4740; GMRES with
   // blocks of 8 of 86^3 474 and 539, 119^3 849 and 885 (without a preconditioner 665 and 617).
   if (flat_lp && p.storage == MPRK_FP16 && p.compute == MPRK_FP64 &&
-      (p.krylov == MPRK_CG || (o.format == MPRK_FMT_STENCIL && p.precond == MPRK_PRECOND_BJ && p.block > 2)))
+      (p.krylov == MPRK_CG || (stencil && p.precond == MPRK_PRECOND_BJ && p.block > 2)))
     vec_lp = 1;
   vec_ad = flat_lp ? 1 : vec_lp;
   Kc = operator_coef(g, o);

@@ -69,10 +69,13 @@ def test_shared_inverses_by_index(shape, storage, block):
     assert info['iters'] == jnfo['iters'] and np.array_equal(x, y)
 
 
-# the smallest odd grids on which CG takes groups of values (past 3 2^17 and, in FP16, 2^19 unknowns)
+# odd grids on which CG takes groups of values (past 3 2^17 and, in FP16, 11 2^16 unknowns) and, in
+# FP16, smaller ones
 @pytest.mark.parametrize("shape,storage,block", [((77, 73, 71), 'fp32', 2), ((77, 73, 71), 'fp32', 1),
                                                  ((77, 73, 71), 'fp64', 2), ((83, 81, 79), 'fp16', 4),
-                                                 ((83, 81, 79), 'fp16', 2), ((83, 81, 79), 'fp16', 1)])
+                                                 ((83, 81, 79), 'fp16', 2), ((83, 81, 79), 'fp16', 1),
+                                                 ((91, 91, 89), 'fp16', 4), ((91, 91, 89), 'fp16', 2),
+                                                 ((91, 91, 89), 'fp16', 1)])
 @pytest.mark.parametrize("fmt,over", [(A.FMT_CSR, {}), (A.FMT_CSR, {'bj_adapt_tol': 1e-1}),
                                       (A.FMT_STENCIL, {'bj_adapt_tol': 1e-1})])
 def test_cg_sums_of_the_last_group(shape, storage, block, fmt, over):

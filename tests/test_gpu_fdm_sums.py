@@ -14,7 +14,8 @@ M = pytest.importorskip('paper_2412_16638_amd')
 A = M._abi
 
 
-@pytest.mark.parametrize("storage,shape,seed", [('fp32', (77, 72, 72), 4), ('fp16', (83, 80, 80), 5)])
+@pytest.mark.parametrize("storage,shape,seed", [('fp32', (77, 72, 72), 4), ('fp16', (83, 80, 80), 5),
+                                                ('fp16', (91, 90, 90), 5)])
 def test_norm_is_an_fp64_sum(storage, shape, seed):
     # an absolute tolerance 1.5e-11 above and below the norm decides whether the first solve iterates;
     # the FP64 sums of the device and of numpy agree to about 1e-13, groups added in FP32 are 7e-11 and more off

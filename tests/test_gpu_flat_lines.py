@@ -77,3 +77,21 @@ def test_fp64_arithmetic_over_fp16_storage(krylov_name, over, fmt):
     lim = st.prec.outer_tol * np.linalg.norm(rhs) + 32 * U[A.FP64] * np.linalg.norm(abs(Mx) @ np.abs(got))
     st.close()
     assert info['converged'] == 1 and np.linalg.norm(rhs - Mx @ got) <= lim, info
+
+
+@pytest.mark.parametrize("shape", [(91, 89, 89), (91, 91, 89)])
+@pytest.mark.parametrize("krylov_name,over", [('cg', {}), ('cg', {'bj_adapt_tol': 1e-5}),
+                                              ('gmres', {'bj_adapt_tol': 1e-5})])
+def test_fp16_lines_of_cg_and_adaptive_inverses(shape, krylov_name, over):
+    # 11 2^16 unknowns: one value up to there, groups of eight past it; the residual test
+    log_case('flat_lines_fp16', shape=shape, krylov=krylov_name, **over)
+    bc, kind, diff, b = ((W.DIRICHLET, W.HEAT, 1.5, (0.0, 0.0, 0.0)) if krylov_name == 'cg'
+                         else (W.PERIODIC, W.ADVDIFF, 0.3, (-1.0, 0.5, -0.25)))
+    st = M.Stepper(shape, bc, kind, diff, b, A.FMT_STENCIL, 'SDIRK3', M.precisions('fp16', krylov_name, **over), 2e-4)
+    rhs = np.random.default_rng(8).standard_normal(st.N)
+    x, info = st.solve(0, torch.from_numpy(rhs).cuda())
+    Mx = operators.stage_matrix(operators.operator(shape, bc, kind, diff, b), st.dt * st.tab.a_lo[0])
+    got = x.cpu().numpy()
+    lim = st.prec.outer_tol * np.linalg.norm(rhs) + 32 * U[A.FP64] * np.linalg.norm(abs(Mx) @ np.abs(got))
+    st.close()
+    assert info['converged'] == 1 and np.linalg.norm(rhs - Mx @ got) <= lim, info
